@@ -141,12 +141,14 @@ sgpe_status sgpe_get_psi(sgpe_ctx* ctx, double* psi_host);
 
 /* Advance n >= 0 real-time steps (Sec. 3.2).  Asynchronous on the context's stream.  The
  * fused schedule is K(dt/2) [R(dt) K(dt)]^(n-1) R(dt) K(dt/2); its result equals n separate
- * K(dt/2) R(dt) K(dt/2) steps up to rounding.  Consecutive calls continue one schedule: on a
+ * K(dt/2) R(dt) K(dt/2) steps up to rounding.  K factors into an operator along x and one along y
+ * that commute, so a real-time step is one sweep over the state, along rows and columns in turn
+ * (n + 2 sweeps per call).  Consecutive calls continue one schedule: on a
  * context with the K-R-K splitting (either real-space form) on a complex64 state, or the default
  * splitting on a complex128 one, and a state it allocated itself, a call leaves its
- * last K(dt/2) and inverse x-transform pending, and the next step call of the same kind merges them
- * with its own first K(dt/2), so calls of n1 and n2 steps give bit for bit what one call of
- * n1 + n2 steps gives.  Every other call on the context (get_psi, energy, norm, the observables,
+ * last K(dt/2) (in imaginary time also the inverse x-transform) pending, and the next step call of the
+ * same kind merges it with its own first K(dt/2), so calls of n1 and n2 steps give bit for bit what one
+ * call of n1 + n2 steps gives.  Every other call on the context (get_psi, energy, norm, the observables,
  * synchronize, a step of the other kind, a schedule or splitting change, ...) completes the
  * pending half-step first, so no caller sees the difference.  A context on a caller's state buffer
  * (psi_dev at create) completes every call, so the buffer always holds the documented layout.
@@ -212,7 +214,9 @@ sgpe_status sgpe_relax_imag(sgpe_ctx* ctx, int64_t check_every, int64_t max_step
 /* Measurement helper: run n real-time (imag = 0) or imaginary-time (imag = 1) steady-state
  * steps with a HIP event pair around every kernel launch, and return the mean duration in
  * milliseconds of the row pass (x transforms + real-space exponential) and of the column pass
- * (y transforms + k-space propagator).  The state advances exactly as with sgpe_step_*(n).
+ * (y transforms + k-space propagator); in real time, where a step is one pass, of the steps taken
+ * along rows and along columns (the first is along columns; for n = 1 row_ms is the leading half op).
+ * The state advances exactly as with sgpe_step_*(n).
  * Synchronises.  Either output pointer may be NULL. */
 sgpe_status sgpe_profile_steps(sgpe_ctx* ctx, int32_t imag, int64_t n,
                                double* row_ms, double* col_ms);
@@ -235,10 +239,10 @@ sgpe_status sgpe_profile_kernels(sgpe_ctx* ctx, int32_t imag, int64_t n,
  * g_uu = g_dd = g_ud (the mean field is then a multiple of the total density, which the coupling
  * conserves); otherwise it is first order in the mean-field coupling, and N L N keeps the step
  * second order.  Imaginary time normalises after
- * every step in every variant.  Cost per step: two sweeps, except R-K-R in imaginary time (three:
- * the norm is needed between the two R halves of consecutive steps).  On a complex64 state K-R-K
- * with N L N runs the default's fused schedule with N L N in its row pass, so consecutive step calls
- * continue it as they do the default's; R-K-R runs a general row pass and completes every call.
+ * every step in every variant.  Cost per step: one sweep in real time; in imaginary time two, except
+ * R-K-R (three: the norm is needed between the two R halves of consecutive steps).  On a complex64
+ * state K-R-K with N L N runs the default's schedule with N L N as its R, so consecutive step calls
+ * continue it as they do the default's; R-K-R completes every call.
  * sgpe_profile_steps and sgpe_profile_kernels measure the default only and return SGPE_ESTATE
  * under a variant.  Takes effect for the next step call.
  * Errors: SGPE_EINVAL (NULL context, unknown value). */
@@ -349,7 +353,8 @@ sgpe_status sgpe_set_col_tile(sgpe_ctx* ctx, int32_t columns);
  * decomposition, so changing them changes results at the level of rounding.
  *   col_tile    columns per column-pass workgroup (power of two)
  *   row_iters   row groups per row-pass workgroup, 1 or 2: with 2, the next group's data is loaded
- *               while the current one is transformed (8 or 16 points per lane, <= 256 threads)
+ *               while the current one is transformed (8 or 16 points per lane, <= 256 threads);
+ *               imaginary time only (a real-time pass takes one group per workgroup)
  *   col_iters   the same for column tiles
  *   row_points  points per lane of the x transforms: 16, or 8 / 4 when nx <= 1024
  *   col_points  the same for the y transforms and ny
@@ -454,11 +459,12 @@ sgpe_status sgpe_batch_set_schedule(sgpe_batch* batch, int32_t k, const sgpe_sch
  * schedules stay).  Synchronises. */
 sgpe_status sgpe_batch_use_persistent(sgpe_batch* batch, int32_t on);
 
-/* Autotuner: for every class, time `steps` real-time steps under each supported schedule (points
- * per lane 4/8/16 in each pass, column tiles 1..16) and keep the fastest.  The instances' states
+/* Autotuner: for every class, time `steps` real-time and `steps` imaginary-time steps (without
+ * renormalisation) under each supported schedule (points per lane 4/8/16 in each pass, column tiles
+ * 1..16) and keep the fastest.  The instances' states
  * are saved before and restored after (so results do not depend on tuning); the captured graphs
- * are dropped.  best_ms, if not NULL, receives one value per class: the chosen schedule's time per
- * step of that class in milliseconds.  Synchronises. */
+ * are dropped.  best_ms, if not NULL, receives one value per class: the chosen schedule's mean time
+ * per step of that class in milliseconds.  Synchronises. */
 sgpe_status sgpe_batch_autotune(sgpe_batch* batch, int32_t steps, double* best_ms);
 
 #ifdef __cplusplus

@@ -50,8 +50,8 @@ def source_hash() -> str:
 
 # The sources the step kernels compile from (with the device compile flags): a record measured on
 # these kernels stays valid while this hash is unchanged, whatever happens to the host library.
-KERNEL_SOURCES = ("row_pass.hip", "col_pass.hip", "row_body.hpp", "col_body.hpp", "fft_device.hpp",
-                  "sgpe_internal.hpp")
+KERNEL_SOURCES = ("row_pass.hip", "col_pass.hip", "line_row.hip", "line_col.hip", "row_body.hpp", "col_body.hpp",
+                  "line_body.hpp", "line_launch.hpp", "fft_device.hpp", "sgpe_internal.hpp")
 
 
 def kernel_hash() -> str:

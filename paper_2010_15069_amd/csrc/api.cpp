@@ -331,105 +331,182 @@ sgpe::ColArgsT<T> col_args_t(const sgpe_ctx* c, bool imag, bool half) {
 
 ColArgs col_args(const sgpe_ctx* c, bool imag, bool half) { return col_args_t<float>(c, imag, half); }
 
-// The fused schedule on a complex128 state: the same sequence of passes as run_steps, with the
-// fp64 instantiations of the kernels (16 or 8 points per lane, no prefetch).
-static sgpe_status run_steps_c128(sgpe_ctx* c, int64_t n, bool imag) {
-  const double npts = double(c->p.nx) * double(c->p.ny);
-  hipStream_t s = c->stream;
-  sgpe::RowArgsT<double> ra = row_args_t<double>(c, 0.0);
-  // a pending tail of this kind continues as in run_steps; one of the other kind completes first
-  const int kind = imag ? 2 : 1;
-  if (c->tail_pending != 0 && c->tail_pending != kind) {
+// Line-pass arguments along columns (col) or rows with ops of K(pre), K(post) (LineOp) and n_r real-space
+// sub-steps R(h_sub) (h_sub <= 0: dt).  x is the axis along the line.
+template <class T>
+sgpe::LineArgsT<T> line_args_t(const sgpe_ctx* c, bool col, LineOp pre, LineOp post, int n_r, double h_sub) {
+  const sgpe_params& p = c->p;
+  const sgpe::RowArgsT<T> r = row_args_t<T>(c, h_sub);
+  sgpe::LineArgsT<T> a{};
+  a.psi = r.psi;
+  a.nx = p.nx;
+  a.lines = col ? c->cols : c->rows;
+  auto op = [&](LineOp o) -> const void* {
+    if (o == LINE_NONE) return nullptr;
+    const sgpe::ColArgsT<T> k = col_args_t<T>(c, false, o == LINE_HALF);
+    return col ? static_cast<const void*>(k.ky_tab) : static_cast<const void*>(k.kx_tab);
+  };
+  a.op_pre = op(pre);
+  a.op_post = op(post);
+  a.n_r = n_r;
+  a.hfrac = r.hfrac;
+  a.hdelta2 = r.hdelta2;
+  a.hg_uu = r.hg_uu;
+  a.hg_dd = r.hg_dd;
+  a.hg_ud = r.hg_ud;
+  a.tw = col ? col_args_t<T>(c, false, false).tw : r.tw;
+  a.x0 = col ? r.y0 : r.x0;
+  a.dx = col ? r.dy : r.dx;
+  a.y0 = col ? r.x0 : r.y0;
+  a.dy = col ? r.dx : r.dy;
+  a.hvx = col ? r.hvy : r.hvx;
+  a.hvy = col ? r.hvx : r.hvy;
+  a.hbx = col ? r.hby : r.hbx;
+  a.hby = col ? r.hbx : r.hby;
+  return a;
+}
+
+sgpe::LineArgs line_args(const sgpe_ctx* c, bool col, LineOp pre, LineOp post, int n_r, double h_sub) {
+  return line_args_t<float>(c, col, pre, post, n_r, h_sub);
+}
+
+// One line pass of the context on its stream.
+static hipError_t line_pass(const sgpe_ctx* c, bool col, LineOp pre, LineOp post, int n_r, double h_sub = 0.0) {
+  const int n = col ? c->p.ny : c->p.nx, n_lines = col ? c->p.nx : c->p.ny;
+  const int points = col ? c->col_points : c->row_points;
+  if (c->prec == SGPE_C128)
+    return sgpe::launch_line(line_args_t<double>(c, col, pre, post, n_r, h_sub), n, n_lines, col, c->full2x2, points,
+                             c->stream);
+  return sgpe::launch_line(line_args_t<float>(c, col, pre, post, n_r, h_sub), n, n_lines, col, c->full2x2,
+                           c->split_rs == SGPE_RSPLIT_NLN, points, c->stream);
+}
+
+// n real-time steps K(dt/2) R K(dt/2) in n + 2 sweeps (see line_launch.hpp), either precision and either
+// real-space split.  A context on its own state stops after the last R, which leaves K(dt/2) pending
+// (tail_pending, tail_col): a call that continues starts with the pending axis's op of the merged K(dt)
+// alone, and its passes go on from the other axis, so that calls of n1 and n2 steps do the arithmetic
+// of one call of n1 + n2.  With ev, a HIP event pair around the leading pass and each of the n others.
+static sgpe_status run_steps_real(sgpe_ctx* c, int64_t n, std::vector<hipEvent_t>* ev) {
+  if (c->tail_pending != 0 && (c->tail_pending != 1 || ev)) {
     const sgpe_status st = flush_tail(c);
     if (st != SGPE_OK) return st;
   }
-  const bool cont = c->tail_pending == kind;
+  size_t evi = 0;
+  auto mark = [&] {
+    if (ev) (void)hipEventRecord((*ev)[evi++], c->stream);
+  };
+  const bool cont = c->tail_pending == 1;
+  const bool defer = c->own_psi && !ev;
+  bool col = cont && c->tail_col;
+  c->tail_pending = 0;
+  mark();
+  hipError_t e = line_pass(c, col, cont ? LINE_FULL : LINE_HALF, LINE_NONE, 0);
+  mark();
+  for (int64_t i = 1; i <= n && e == hipSuccess; ++i) {
+    col = !col;
+    const bool last = i == n;
+    mark();
+    e = line_pass(c, col, (i == 1 && !cont) ? LINE_HALF : LINE_FULL, !last ? LINE_FULL : defer ? LINE_NONE : LINE_HALF,
+                  1);
+    mark();
+  }
+  if (e != hipSuccess) return status_of(e);
+  if (defer) {
+    c->tail_pending = 1;
+    c->tail_col = col;
+    return SGPE_OK;
+  }
+  return status_of(line_pass(c, !col, LINE_HALF, LINE_NONE, 0));
+}
+
+// The fused imaginary-time schedule on a complex128 state: the same sequence of passes as run_steps,
+// with the fp64 instantiations of the kernels (16 or 8 points per lane, no prefetch).
+static sgpe_status run_steps_c128(sgpe_ctx* c, int64_t n) {
+  const double npts = double(c->p.nx) * double(c->p.ny);
+  hipStream_t s = c->stream;
+  sgpe::RowArgsT<double> ra = row_args_t<double>(c, 0.0);
+  // a pending imaginary-time tail continues as in run_steps; a real-time one completes first
+  if (c->tail_pending == 1) {
+    const sgpe_status st = flush_tail(c);
+    if (st != SGPE_OK) return st;
+  }
+  const bool cont = c->tail_pending == 2;
   c->tail_pending = 0;
   hipError_t e;
   if (cont) {
-    e = sgpe::launch_col(col_args_t<double>(c, imag, false), imag ? sgpe::NORM_DOT : sgpe::NORM_NONE, c->col_points,
-                         s);
+    e = sgpe::launch_col(col_args_t<double>(c, true, false), sgpe::NORM_DOT, c->col_points, s);
   } else {
     e = sgpe::launch_row(ra, sgpe::ROW_FWD, false, false, c->row_points, s);
-    if (e == hipSuccess) e = sgpe::launch_col(col_args_t<double>(c, imag, true), sgpe::NORM_NONE, c->col_points, s);
+    if (e == hipSuccess) e = sgpe::launch_col(col_args_t<double>(c, true, true), sgpe::NORM_NONE, c->col_points, s);
   }
   const bool defer = c->own_psi;
   for (int64_t i = 1; i <= n && e == hipSuccess; ++i) {
     sgpe::RowArgsT<double> r = ra;
     r.scale = 1.0 / npts;
-    if (imag && (i > 1 || cont)) {
+    if (i > 1 || cont) {
       r.partials = c->partials;
       r.n_partials = col_groups(c);
     }
-    e = sgpe::launch_row(r, sgpe::ROW_STEP, imag, c->full2x2, c->row_points, s);
+    e = sgpe::launch_row(r, sgpe::ROW_STEP, true, c->full2x2, c->row_points, s);
     const bool last = (i == n);
     if (last && defer) break;   // the last K(dt/2) and the inverse x-transform wait (flush_tail)
-    const int nm = imag ? (last ? sgpe::NORM_SQ : sgpe::NORM_DOT) : sgpe::NORM_NONE;
-    if (e == hipSuccess) e = sgpe::launch_col(col_args_t<double>(c, imag, last), nm, c->col_points, s);
+    if (e == hipSuccess)
+      e = sgpe::launch_col(col_args_t<double>(c, true, last), last ? sgpe::NORM_SQ : sgpe::NORM_DOT, c->col_points, s);
   }
   if (e == hipSuccess && defer) {
-    c->tail_pending = kind;
+    c->tail_pending = 2;
     return SGPE_OK;
   }
   if (e == hipSuccess) {
     sgpe::RowArgsT<double> r = ra;
     r.scale = 1.0 / npts;
-    if (imag) {
-      r.partials = c->partials;
-      r.n_partials = col_groups(c);
-    }
+    r.partials = c->partials;
+    r.n_partials = col_groups(c);
     e = sgpe::launch_row(r, sgpe::ROW_INV, false, false, c->row_points, s);
   }
   return status_of(e);
 }
 
-// The fused schedule of n steps: K(dt/2) [R K(dt)]^(n-1) R K(dt/2), with the normalisation of
-// step i applied (as a scale) at the start of the next row pass.
+// The fused imaginary-time schedule of n steps: K(dt/2) [R K(dt)]^(n-1) R K(dt/2), with the
+// normalisation of step i applied (as a scale) at the start of the next row pass.
 static sgpe_status run_steps_variant(sgpe_ctx* c, int64_t n, bool imag);
 
 sgpe_status run_steps(sgpe_ctx* c, int64_t n, bool imag, std::vector<hipEvent_t>* ev) {
   if (n == 0) return SGPE_OK;
-  const bool variant = c->split_order != SGPE_SPLIT_KRK || c->split_rs != SGPE_RSPLIT_FROZEN;
-  // K-R-K with R = N L N differs from the default only inside the row pass's R: on a complex64
-  // state it runs the fused schedule below with that row pass (and continues across calls)
-  const bool krk_nln = c->split_order == SGPE_SPLIT_KRK && c->split_rs == SGPE_RSPLIT_NLN && c->prec != SGPE_C128;
-  if (variant && !krk_nln) {
-    // the variants complete every call; a tail of the default schedule completes first
+  const bool rkr = c->split_order != SGPE_SPLIT_KRK;
+  const bool nln = c->split_rs != SGPE_RSPLIT_FROZEN;
+  if (ev && (rkr || nln || c->prec == SGPE_C128)) return SGPE_ESTATE;
+  if (rkr) {
+    // R-K-R completes every call; a tail of K-R-K completes first
     const sgpe_status st = flush_tail(c);
     if (st != SGPE_OK) return st;
+    return run_steps_variant(c, n, imag);
   }
-  if (c->prec == SGPE_C128) {
-    if (ev) return SGPE_ESTATE;
-    return run_steps_c128(c, n, imag);
-  }
-  if (variant) {
-    if (ev) return SGPE_ESTATE;
-    if (!krk_nln) return run_steps_variant(c, n, imag);
-  }
-  const int step_mode = krk_nln ? sgpe::ROW_STEP_NLN : sgpe::ROW_STEP;
+  if (!imag) return run_steps_real(c, n, ev);
+  if (c->prec == SGPE_C128) return run_steps_c128(c, n);
+  // K-R-K with R = N L N differs from the default only inside the row pass's R
+  const int step_mode = nln ? sgpe::ROW_STEP_NLN : sgpe::ROW_STEP;
   const double npts = double(c->p.nx) * double(c->p.ny);
   const float inv_n = float(1.0 / npts);  // exact: a power of two
   hipStream_t s = c->stream;
   hipError_t e;
   RowArgs ra = row_args(c);
-  // A tail of the other kind (or any tail before a timed profile) completes first.  A tail of this
-  // kind continues: the merged K(dt) below completes the previous call's last step and begins this
-  // call's first, exactly as inside one call (in imaginary time its NORM_DOT partials give the
-  // norm at that step boundary, and the first row pass rescales by it).
-  const int kind = imag ? 2 : 1;
-  if (c->tail_pending != 0 && (c->tail_pending != kind || ev)) {
+  // A real-time tail (or any tail before a timed profile) completes first.  An imaginary-time one
+  // continues: the merged K(dt) below completes the previous call's last step and begins this
+  // call's first, exactly as inside one call (its NORM_DOT partials give the norm at that step
+  // boundary, and the first row pass rescales by it).
+  if (c->tail_pending != 0 && (c->tail_pending != 2 || ev)) {
     const sgpe_status st = flush_tail(c);
     if (st != SGPE_OK) return st;
   }
-  const bool cont = c->tail_pending == kind;
+  const bool cont = c->tail_pending == 2;
   c->tail_pending = 0;
   if (cont) {
-    e = sgpe::launch_col(col_args(c, imag, false), imag ? sgpe::NORM_DOT : sgpe::NORM_NONE, c->col_iters,
-                         c->col_points, s);
+    e = sgpe::launch_col(col_args(c, true, false), sgpe::NORM_DOT, c->col_iters, c->col_points, s);
   } else {
     e = sgpe::launch_row(ra, sgpe::ROW_FWD, false, false, c->row_iters, c->row_points, s);
     if (e == hipSuccess)
-      e = sgpe::launch_col(col_args(c, imag, true), sgpe::NORM_NONE, c->col_iters, c->col_points, s);
+      e = sgpe::launch_col(col_args(c, true, true), sgpe::NORM_NONE, c->col_iters, c->col_points, s);
   }
   if (e != hipSuccess) return status_of(e);
   // a context on a caller's state buffer, and a timed profile, complete every call
@@ -438,80 +515,89 @@ sgpe_status run_steps(sgpe_ctx* c, int64_t n, bool imag, std::vector<hipEvent_t>
   for (int64_t i = 1; i <= n; ++i) {
     RowArgs r = ra;
     r.scale = inv_n;
-    if (imag && (i > 1 || cont)) {
+    if (i > 1 || cont) {
       r.partials = c->partials;
       r.n_partials = col_groups(c);
     }
     if (ev) (void)hipEventRecord((*ev)[evi++], s);
-    e = sgpe::launch_row(r, step_mode, imag, c->full2x2, c->row_iters, c->row_points, s);
+    e = sgpe::launch_row(r, step_mode, true, c->full2x2, c->row_iters, c->row_points, s);
     if (e != hipSuccess) return status_of(e);
     if (ev) (void)hipEventRecord((*ev)[evi++], s);
     const bool last = (i == n);
     if (last && defer) break;   // the last K(dt/2) and the inverse x-transform wait (flush_tail)
-    const int nm = imag ? (last ? sgpe::NORM_SQ : sgpe::NORM_DOT) : sgpe::NORM_NONE;
-    e = sgpe::launch_col(col_args(c, imag, last), nm, c->col_iters, c->col_points, s);
+    e = sgpe::launch_col(col_args(c, true, last), last ? sgpe::NORM_SQ : sgpe::NORM_DOT, c->col_iters, c->col_points, s);
     if (e != hipSuccess) return status_of(e);
     if (ev) (void)hipEventRecord((*ev)[evi++], s);
   }
   if (defer) {
-    c->tail_pending = kind;
+    c->tail_pending = 2;
     return SGPE_OK;
   }
   RowArgs r = ra;
   r.scale = inv_n;
-  if (imag) {
-    r.partials = c->partials;
-    r.n_partials = col_groups(c);
-  }
+  r.partials = c->partials;
+  r.n_partials = col_groups(c);
   e = sgpe::launch_row(r, sgpe::ROW_INV, false, false, c->row_iters, c->row_points, s);
   return status_of(e);
 }
 
-// The tail a step call of the default schedule left (either precision): the last step's K(dt/2)
-// (with the imaginary-time norm partials of the finished step) and the inverse x-transform (with
-// its rescaling), exactly as the call would have ended.
+// The tail a K-R-K step call left (either precision): in real time the last step's K(dt/2), the pending
+// axis first; in imaginary time its K(dt/2) (with the norm partials of the finished step) and the
+// inverse x-transform (with its rescaling), exactly as the call would have ended.
 sgpe_status flush_tail(sgpe_ctx* c) {
   if (c->tail_pending == 0) return SGPE_OK;
   const bool imag = c->tail_pending == 2;
   c->tail_pending = 0;
-  const int nm = imag ? sgpe::NORM_SQ : sgpe::NORM_NONE;
+  if (!imag) {
+    hipError_t e = line_pass(c, c->tail_col, LINE_HALF, LINE_NONE, 0);
+    if (e == hipSuccess) e = line_pass(c, !c->tail_col, LINE_HALF, LINE_NONE, 0);
+    return status_of(e);
+  }
   if (c->prec == SGPE_C128) {
-    hipError_t e = sgpe::launch_col(col_args_t<double>(c, imag, true), nm, c->col_points, c->stream);
+    hipError_t e = sgpe::launch_col(col_args_t<double>(c, true, true), sgpe::NORM_SQ, c->col_points, c->stream);
     if (e != hipSuccess) return status_of(e);
     sgpe::RowArgsT<double> r = row_args_t<double>(c, 0.0);
     r.scale = 1.0 / (double(c->p.nx) * double(c->p.ny));
-    if (imag) {
-      r.partials = c->partials;
-      r.n_partials = col_groups(c);
-    }
+    r.partials = c->partials;
+    r.n_partials = col_groups(c);
     return status_of(sgpe::launch_row(r, sgpe::ROW_INV, false, false, c->row_points, c->stream));
   }
-  hipError_t e = sgpe::launch_col(col_args(c, imag, true), nm, c->col_iters, c->col_points, c->stream);
+  hipError_t e = sgpe::launch_col(col_args(c, true, true), sgpe::NORM_SQ, c->col_iters, c->col_points, c->stream);
   if (e != hipSuccess) return status_of(e);
   RowArgs r = row_args(c);
   r.scale = float(1.0 / (double(c->p.nx) * double(c->p.ny)));
-  if (imag) {
-    r.partials = c->partials;
-    r.n_partials = col_groups(c);
-  }
+  r.partials = c->partials;
+  r.n_partials = col_groups(c);
   e = sgpe::launch_row(r, sgpe::ROW_INV, false, false, c->row_iters, c->row_points, c->stream);
   return status_of(e);
 }
 
-// The R-K-R splitting variants (sgpe_set_splitting), built from the general row pass (K-R-K with
-// R as N L N is the fused schedule of run_steps with the ROW_STEP_NLN row pass):
-//   R-K-R, real time:       row (R(dt/2), fwd-x); n x [col K(dt); row (inv-x, R(dt/2), R(dt/2), fwd-x)],
-//                           the last row pass (inv-x, R(dt/2)) only;
-//   R-K-R, imaginary time:  the norm falls between the two R halves, so each step's row work takes
-//                           two passes: (inv-x, R(dt/2), norm partials) that stores nothing, then
-//                           (inv-x, R(dt/2), scale, R(dt/2), fwd-x).  The second recomputes the
-//                           first's R(dt/2) from the same input with the same code, so the partials
-//                           belong to exactly the state it rescales, and no intermediate state is
-//                           stored (one complex64 rounding fewer per step, and 48 instead of 64 bytes
-//                           per point of row traffic).
+// R-K-R (sgpe_set_splitting):
+//   real time:       line passes; K(dt) = X Y lies between two R halves, so with the axes' order
+//                    alternating: R(dt/2) X(dt) | Y(dt) R(dt/2) R(dt/2) Y(dt) | X(dt) R R X(dt) | ... |
+//                    Z(dt) R(dt/2), n + 1 sweeps, the densities refreshed between the two halves;
+//   imaginary time:  built from the general row pass.  The norm falls between the two R halves, so
+//                    each step takes a column pass and two row passes: (inv-x, R(dt/2), norm partials)
+//                    that stores nothing, then (inv-x, R(dt/2), scale, R(dt/2), fwd-x).  The second
+//                    recomputes the first's R(dt/2) from the same input with the same code, so the
+//                    partials belong to exactly the state it rescales, and no intermediate state is
+//                    stored (one complex64 rounding fewer per step, and 48 instead of 64 bytes per point
+//                    of row traffic).
 static sgpe_status run_steps_variant(sgpe_ctx* c, int64_t n, bool imag) {
   if (n == 0) return SGPE_OK;
   const sgpe_params& p = c->p;
+  hipError_t e = hipSuccess;
+  const double h = 0.5 * p.dt;
+  if (!imag) {
+    bool col = false;
+    e = line_pass(c, col, LINE_NONE, LINE_FULL, 1, h);
+    for (int64_t i = 1; i <= n && e == hipSuccess; ++i) {
+      col = !col;
+      const bool last = i == n;
+      e = line_pass(c, col, LINE_FULL, last ? LINE_NONE : LINE_FULL, last ? 1 : 2, h);
+    }
+    return status_of(e);
+  }
   const double npts = double(p.nx) * double(p.ny);
   const float inv_n = float(1.0 / npts);
   const int rs = c->split_rs;
@@ -519,8 +605,7 @@ static sgpe_status run_steps_variant(sgpe_ctx* c, int64_t n, bool imag) {
   const int var_rows = std::min(c->rows, sgpe::row_rows_per_block(p.nx, p.ny, c->row_points, c->max_lds));
   const int row_groups = p.ny / var_rows;
   hipStream_t s = c->stream;
-  hipError_t e = hipSuccess;
-  auto row = [&](double h, int flags, int nr, const double* parts, int nparts, bool real_space_parts) {
+  auto row = [&](int flags, int nr, const double* parts, int nparts) {
     RowArgs r = row_args(c, h);
     r.rows_per_block = var_rows;
     r.var_flags = flags;
@@ -529,29 +614,20 @@ static sgpe_status run_steps_variant(sgpe_ctx* c, int64_t n, bool imag) {
     r.scale = (flags & sgpe::VAR_INV) ? inv_n : 1.0f;   // with VAR_MID_SCALE: the inverse's 1/N only
     r.partials = parts;
     r.n_partials = nparts;
-    if (real_space_parts) {
+    if (parts) {   // of the real-space state
       r.parseval_w = (2.0 * p.xmax / p.nx) * (2.0 * p.ymax / p.ny);
       r.inv_npts = 1.0;
     }
     r.partials_out = c->partials;
-    if (e == hipSuccess) e = sgpe::launch_row(r, sgpe::ROW_VAR, imag, c->full2x2, 1, c->row_points, s);
+    if (e == hipSuccess) e = sgpe::launch_row(r, sgpe::ROW_VAR, true, c->full2x2, 1, c->row_points, s);
   };
-  auto col = [&](bool half, int norm_mode) {
-    if (e == hipSuccess) e = sgpe::launch_col(col_args(c, imag, half), norm_mode, c->col_iters, c->col_points, s);
-  };
-  // R-K-R
-  const double h = 0.5 * p.dt;
-  row(h, sgpe::VAR_FWD, 1, nullptr, 0, false);
+  row(sgpe::VAR_FWD, 1, nullptr, 0);
   for (int64_t i = 1; i <= n; ++i) {
-    col(false, sgpe::NORM_NONE);
     const bool last = (i == n);
-    if (!imag) {
-      row(h, last ? sgpe::VAR_INV : (sgpe::VAR_INV | sgpe::VAR_FWD), last ? 1 : 2, nullptr, 0, false);
-    } else {
-      row(h, sgpe::VAR_INV | sgpe::VAR_NORM_OUT | sgpe::VAR_NO_STORE, 1, nullptr, 0, false);
-      row(h, sgpe::VAR_INV | sgpe::VAR_MID_SCALE | (last ? 0 : sgpe::VAR_FWD), last ? 1 : 2, c->partials, row_groups,
-          true);
-    }
+    if (e == hipSuccess)
+      e = sgpe::launch_col(col_args(c, true, false), sgpe::NORM_NONE, c->col_iters, c->col_points, s);
+    row(sgpe::VAR_INV | sgpe::VAR_NORM_OUT | sgpe::VAR_NO_STORE, 1, nullptr, 0);
+    row(sgpe::VAR_INV | sgpe::VAR_MID_SCALE | (last ? 0 : sgpe::VAR_FWD), last ? 1 : 2, c->partials, row_groups);
   }
   return status_of(e);
 }
@@ -1113,7 +1189,9 @@ sgpe_status sgpe_profile_steps(sgpe_ctx* c, int32_t imag, int64_t n, double* row
   if (!c->has_state || c->split_order != SGPE_SPLIT_KRK || c->split_rs != SGPE_RSPLIT_FROZEN ||
       c->prec == SGPE_C128)
     return SGPE_ESTATE;
-  std::vector<hipEvent_t> ev(3 * size_t(n));
+  // imaginary time: three events per step (row pass, column pass); real time: a pair around the
+  // leading row pass and around each step's one pass (columns first, then alternating)
+  std::vector<hipEvent_t> ev(imag ? 3 * size_t(n) : 2 * size_t(n) + 2);
   for (auto& x : ev) {
     if (hipEventCreate(&x) != hipSuccess) {
       (void)hipGetLastError();
@@ -1124,18 +1202,26 @@ sgpe_status sgpe_profile_steps(sgpe_ctx* c, int32_t imag, int64_t n, double* row
   if (st == SGPE_OK) st = sync_and_latch(c);
   double tr = 0.0, tc = 0.0;
   if (st == SGPE_OK) {
-    for (int64_t i = 0; i < n; ++i) {
-      float a = 0.f, b = 0.f;
-      (void)hipEventElapsedTime(&a, ev[3 * i], ev[3 * i + 1]);
-      (void)hipEventElapsedTime(&b, ev[3 * i + 1], ev[3 * i + 2]);
-      tr += a;
-      tc += b;
+    auto ms = [&](size_t i) {
+      float t = 0.f;
+      (void)hipEventElapsedTime(&t, ev[i], ev[i + 1]);
+      return double(t);
+    };
+    if (imag) {
+      for (int64_t i = 0; i < n; ++i) {
+        tr += ms(3 * i) / double(n);
+        tc += ms(3 * i + 1) / double(n);
+      }
+    } else {
+      const int64_t ncol = (n + 1) / 2, nrow = n / 2;
+      for (int64_t i = 1; i <= n; ++i) (i % 2 ? tc : tr) += ms(2 * size_t(i)) / double(i % 2 ? ncol : nrow);
+      if (nrow == 0) tr = ms(0);   // one step has no row pass with R: the leading one
     }
   }
   for (auto& x : ev) (void)hipEventDestroy(x);
   if (st != SGPE_OK) return st;
-  if (row_ms) *row_ms = tr / double(n);
-  if (col_ms) *col_ms = tc / double(n);
+  if (row_ms) *row_ms = tr;
+  if (col_ms) *col_ms = tc;
   return SGPE_OK;
 }
 
@@ -1160,24 +1246,26 @@ sgpe_status sgpe_profile_kernels(sgpe_ctx* c, int32_t imag, int64_t n, double* r
   }
   hipStream_t s = c->stream;
   hipError_t e = made == 4 ? hipSuccess : hipErrorOutOfMemory;
-  // keep the state; enter the mixed representation with valid norm partials
+  // keep the state; in imaginary time enter the mixed representation with valid norm partials
   if (e == hipSuccess) e = hipMemcpyAsync(c->scratch, c->psi, bytes, hipMemcpyDeviceToDevice, s);
-  RowArgs ra = row_args(c);
-  if (e == hipSuccess) e = sgpe::launch_row(ra, sgpe::ROW_FWD, false, false, c->row_iters, c->row_points, s);
-  const int steady_norm = imag ? sgpe::NORM_DOT : sgpe::NORM_NONE;
-  if (e == hipSuccess) e = sgpe::launch_col(col_args(c, imag != 0, true), sgpe::NORM_DOT, c->col_iters, c->col_points, s);
-  RowArgs r = ra;
-  r.scale = float(1.0 / (double(p.nx) * double(p.ny)));
+  RowArgs r = row_args(c);
   if (imag) {
+    if (e == hipSuccess) e = sgpe::launch_row(r, sgpe::ROW_FWD, false, false, c->row_iters, c->row_points, s);
+    if (e == hipSuccess) e = sgpe::launch_col(col_args(c, true, true), sgpe::NORM_DOT, c->col_iters, c->col_points, s);
+    r.scale = float(1.0 / (double(p.nx) * double(p.ny)));
     r.partials = c->partials;
     r.n_partials = col_groups(c);
   }
-  const ColArgs ca = col_args(c, imag != 0, false);
+  const ColArgs ca = col_args(c, true, false);
   if (e == hipSuccess) e = hipEventRecord(ev[0], s);
-  for (int64_t i = 0; i < n && e == hipSuccess; ++i) e = sgpe::launch_row(r, sgpe::ROW_STEP, imag != 0, c->full2x2, c->row_iters, c->row_points, s);
+  for (int64_t i = 0; i < n && e == hipSuccess; ++i)
+    e = imag ? sgpe::launch_row(r, sgpe::ROW_STEP, true, c->full2x2, c->row_iters, c->row_points, s)
+             : line_pass(c, false, LINE_FULL, LINE_FULL, 1);
   if (e == hipSuccess) e = hipEventRecord(ev[1], s);
   if (e == hipSuccess) e = hipEventRecord(ev[2], s);
-  for (int64_t i = 0; i < n && e == hipSuccess; ++i) e = sgpe::launch_col(ca, steady_norm, c->col_iters, c->col_points, s);
+  for (int64_t i = 0; i < n && e == hipSuccess; ++i)
+    e = imag ? sgpe::launch_col(ca, sgpe::NORM_DOT, c->col_iters, c->col_points, s)
+             : line_pass(c, true, LINE_FULL, LINE_FULL, 1);
   if (e == hipSuccess) e = hipEventRecord(ev[3], s);
   if (e == hipSuccess) e = hipMemcpyAsync(c->psi, c->scratch, bytes, hipMemcpyDeviceToDevice, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);

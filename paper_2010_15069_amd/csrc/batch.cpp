@@ -27,6 +27,7 @@
 #include "sgpe_internal.hpp"
 
 using sgpe::ColArgs;
+using sgpe::LineArgs;
 using sgpe::RowArgs;
 using namespace sgpe_host;
 
@@ -34,8 +35,12 @@ namespace {
 
 // Argument table layout of a class with `count` members.
 enum RowVariant { ROWTAB_FWD = 0, ROWTAB_SCALE = 1, ROWTAB_PARTIALS = 2, ROWTAB_N = 3 };
-// column variants: index 2 * imag + half (half: the K(dt/2) of a call's first and last step)
-constexpr int COLTAB_N = 4;
+// column variants (imaginary time): K(dt), and the K(dt/2) of a call's first and last step
+enum ColVariant { COLTAB_FULL = 0, COLTAB_HALF = 1, COLTAB_N = 2 };
+// line variants (real time), index 2 * variant + (along columns): the ops before and after R, or
+// K(dt/2)'s op alone
+enum LineVariant { LINETAB_FIRST = 0, LINETAB_MID = 1, LINETAB_LAST = 2, LINETAB_ONLY = 3, LINETAB_HALF = 4 };
+constexpr int LINETAB_N = 10;
 
 struct BatchClass {
   int nx = 0, ny = 0;
@@ -43,6 +48,7 @@ struct BatchClass {
   std::vector<int> members;
   RowArgs* row_tab = nullptr;   // device, [ROWTAB_N][count]
   ColArgs* col_tab = nullptr;   // device, [COLTAB_N][count]
+  LineArgs* line_tab = nullptr; // device, [LINETAB_N][count]
   sgpe::EnergyArgs* e_tab = nullptr;   // device, [count]: the members' energy arguments
   hipStream_t stream = nullptr;
   hipEvent_t done = nullptr;
@@ -68,7 +74,8 @@ struct sgpe_batch {
   bool persist_graph_ok = true;     // cleared if capturing the cooperative launch fails
   RowArgs* p_row_first = nullptr;   // device, [instances]
   RowArgs* p_row_imag = nullptr;    // device, [instances]: scale from the norm partials
-  ColArgs* p_col[2] = {nullptr, nullptr};   // device, [instances]: K(dt), real / imaginary time
+  ColArgs* p_col = nullptr;         // device, [instances]: K(dt), imaginary time
+  LineArgs* p_line[2] = {nullptr, nullptr};   // device, [instances]: rows / columns, real time
   int4* p_row_items = nullptr;
   int4* p_col_items = nullptr;
   sgpe::PersistClass* p_cls_dev = nullptr;   // [kPersistGroups][kPersistClasses]
@@ -100,6 +107,7 @@ sgpe_status build_tables(BatchClass& k, const std::vector<sgpe_ctx*>& inst) {
   const size_t n = k.members.size();
   std::vector<RowArgs> rows(ROWTAB_N * n);
   std::vector<ColArgs> cols(COLTAB_N * n);
+  std::vector<LineArgs> lines(LINETAB_N * n);
   for (size_t j = 0; j < n; ++j) {
     const sgpe_ctx* c = inst[k.members[j]];
     const RowArgs a = row_args(c);
@@ -111,68 +119,107 @@ sgpe_status build_tables(BatchClass& k, const std::vector<sgpe_ctx*>& inst) {
     rows[ROWTAB_FWD * n + j] = a;
     rows[ROWTAB_SCALE * n + j] = sc;
     rows[ROWTAB_PARTIALS * n + j] = pa;
-    for (int imag = 0; imag < 2; ++imag)
-      for (int half = 0; half < 2; ++half) cols[(2 * imag + half) * n + j] = col_args(c, imag != 0, half != 0);
+    cols[COLTAB_FULL * n + j] = col_args(c, true, false);
+    cols[COLTAB_HALF * n + j] = col_args(c, true, true);
+    for (int col = 0; col < 2; ++col) {
+      lines[(2 * LINETAB_FIRST + col) * n + j] = line_args(c, col, LINE_HALF, LINE_FULL, 1);
+      lines[(2 * LINETAB_MID + col) * n + j] = line_args(c, col, LINE_FULL, LINE_FULL, 1);
+      lines[(2 * LINETAB_LAST + col) * n + j] = line_args(c, col, LINE_FULL, LINE_HALF, 1);
+      lines[(2 * LINETAB_ONLY + col) * n + j] = line_args(c, col, LINE_HALF, LINE_HALF, 1);
+      lines[(2 * LINETAB_HALF + col) * n + j] = line_args(c, col, LINE_HALF, LINE_NONE, 0);
+    }
   }
   if (hipMemcpy(k.row_tab, rows.data(), rows.size() * sizeof(RowArgs), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(k.col_tab, cols.data(), cols.size() * sizeof(ColArgs), hipMemcpyHostToDevice) != hipSuccess) {
+      hipMemcpy(k.col_tab, cols.data(), cols.size() * sizeof(ColArgs), hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(k.line_tab, lines.data(), lines.size() * sizeof(LineArgs), hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipGetLastError();
     return SGPE_EDEVICE;
   }
   return SGPE_OK;
 }
 
-// The fused schedule of n steps for every member of a class, on stream s (the same launch
-// sequence as a single context's).
-hipError_t enqueue_class(const sgpe_batch* b, const BatchClass& k, int64_t n, bool imag, hipStream_t s) {
+// One line pass of a class.
+hipError_t class_line(const sgpe_batch* b, const BatchClass& k, LineVariant variant, bool col, hipStream_t s) {
+  const int cnt = int(k.members.size());
+  const sgpe_ctx* c0 = b->inst[k.members[0]];
+  return sgpe::launch_line_batch(line_args(c0, col, LINE_NONE, LINE_NONE, 0), k.line_tab + (2 * variant + int(col)) * cnt,
+                                 cnt, col ? k.ny : k.nx, col ? k.nx : k.ny, col, k.full2x2,
+                                 col ? c0->col_points : c0->row_points, s);
+}
+
+// The pass of step i of n real-time steps (along columns for odd i), of a call that completes itself.
+LineVariant line_variant(int64_t i, int64_t n) {
+  return n == 1 ? LINETAB_ONLY : i == 1 ? LINETAB_FIRST : i == n ? LINETAB_LAST : LINETAB_MID;
+}
+
+// n real-time steps of every member of a class, on stream s (a single context's launches).
+hipError_t enqueue_class_real(const sgpe_batch* b, const BatchClass& k, int64_t n, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  hipError_t e = class_line(b, k, LINETAB_HALF, false, s);
+  for (int64_t i = 1; i <= n && e == hipSuccess; ++i) e = class_line(b, k, line_variant(i, n), i % 2 != 0, s);
+  if (e == hipSuccess) e = class_line(b, k, LINETAB_HALF, n % 2 == 0, s);
+  return e;
+}
+
+// The fused imaginary-time schedule of n steps for every member of a class, on stream s (the same
+// launch sequence as a single context's).  renormalise = false keeps the fixed scale throughout (for
+// timing on states whose norm means nothing).
+hipError_t enqueue_class_imag(const sgpe_batch* b, const BatchClass& k, int64_t n, hipStream_t s,
+                              bool renormalise = true) {
   if (n == 0) return hipSuccess;
   const int cnt = int(k.members.size());
   const sgpe_ctx* c0 = b->inst[k.members[0]];
   const RowArgs shape_r = row_args(c0);
-  const ColArgs shape_c = col_args(c0, imag, false);
+  const ColArgs shape_c = col_args(c0, true, false);
   const int rp = c0->row_points, cp = c0->col_points;
   const RowArgs* t_fwd = k.row_tab + ROWTAB_FWD * cnt;
   const RowArgs* t_sc = k.row_tab + ROWTAB_SCALE * cnt;
-  const RowArgs* t_pa = k.row_tab + ROWTAB_PARTIALS * cnt;
-  auto ctab = [&](bool half) { return k.col_tab + (2 * int(imag) + int(half)) * cnt; };
+  const RowArgs* t_pa = renormalise ? k.row_tab + ROWTAB_PARTIALS * cnt : t_sc;
+  auto ctab = [&](bool half) { return k.col_tab + int(half ? COLTAB_HALF : COLTAB_FULL) * cnt; };
   hipError_t e = sgpe::launch_row_batch(shape_r, t_fwd, cnt, sgpe::ROW_FWD, false, false, rp, s);
   if (e == hipSuccess) e = sgpe::launch_col_batch(shape_c, ctab(true), cnt, sgpe::NORM_NONE, cp, s);
   for (int64_t i = 1; i <= n && e == hipSuccess; ++i) {
-    e = sgpe::launch_row_batch(shape_r, (imag && i > 1) ? t_pa : t_sc, cnt, sgpe::ROW_STEP, imag, k.full2x2, rp, s);
+    e = sgpe::launch_row_batch(shape_r, i > 1 ? t_pa : t_sc, cnt, sgpe::ROW_STEP, true, k.full2x2, rp, s);
     const bool last = (i == n);
-    const int nm = imag ? (last ? sgpe::NORM_SQ : sgpe::NORM_DOT) : sgpe::NORM_NONE;
-    if (e == hipSuccess) e = sgpe::launch_col_batch(shape_c, ctab(last), cnt, nm, cp, s);
+    if (e == hipSuccess)
+      e = sgpe::launch_col_batch(shape_c, ctab(last), cnt, last ? sgpe::NORM_SQ : sgpe::NORM_DOT, cp, s);
   }
-  if (e == hipSuccess) e = sgpe::launch_row_batch(shape_r, imag ? t_pa : t_sc, cnt, sgpe::ROW_INV, false, false, rp, s);
+  if (e == hipSuccess) e = sgpe::launch_row_batch(shape_r, t_pa, cnt, sgpe::ROW_INV, false, false, rp, s);
   return e;
 }
 
-// Persistent mode: per class the call's first x transform and half K, then one cooperative launch
-// for steps 1..n-1 of every instance, then per class the last step (its row pass, the half K with
-// the final norm) and the last inverse x transform.  The same passes, in the same order per
+// Persistent mode: one cooperative launch for every instance's steady-state passes, the others as
+// per-class launches -- imaginary time: the first x transform and half K, the last step (its row pass,
+// the half K with the final norm) and the last inverse x transform; real time: the leading half op, the
+// first and the last step's pass and the closing half op.  The same passes, in the same order per
 // instance, as the per-class launches.
 hipError_t enqueue_persistent(sgpe_batch* b, int64_t n, bool imag, hipStream_t s) {
   hipError_t e = hipSuccess;
   for (const auto& k : b->cls) {
     const int cnt = int(k.members.size());
     const sgpe_ctx* c0 = b->inst[k.members[0]];
-    const RowArgs shape_r = row_args(c0);
-    const ColArgs shape_c = col_args(c0, imag, false);
-    if (e == hipSuccess)
-      e = sgpe::launch_row_batch(shape_r, k.row_tab + ROWTAB_FWD * cnt, cnt, sgpe::ROW_FWD, false, false, 8, s);
-    if (e == hipSuccess)
-      e = sgpe::launch_col_batch(shape_c, k.col_tab + (2 * int(imag) + 1) * cnt, cnt, sgpe::NORM_NONE, 8, s);
+    if (imag) {
+      if (e == hipSuccess)
+        e = sgpe::launch_row_batch(row_args(c0), k.row_tab + ROWTAB_FWD * cnt, cnt, sgpe::ROW_FWD, false, false, 8, s);
+      if (e == hipSuccess)
+        e = sgpe::launch_col_batch(col_args(c0, true, false), k.col_tab + COLTAB_HALF * cnt, cnt, sgpe::NORM_NONE, 8, s);
+    } else {
+      if (e == hipSuccess) e = class_line(b, k, LINETAB_HALF, false, s);
+      if (e == hipSuccess) e = class_line(b, k, line_variant(1, n), true, s);
+    }
   }
-  if (e == hipSuccess && n > 1) {
+  const int64_t steps = imag ? n - 1 : n - 2;
+  if (e == hipSuccess && steps > 0) {
     sgpe::PersistArgs a{};
     a.row_first = b->p_row_first;
-    a.row_step = imag ? b->p_row_imag : b->p_row_first;
-    a.col = b->p_col[imag ? 1 : 0];
+    a.row_step = b->p_row_imag;
+    a.col = b->p_col;
+    a.line_row = b->p_line[0];
+    a.line_col = b->p_line[1];
     a.row_items = b->p_row_items;
     a.col_items = b->p_col_items;
     a.cls = b->p_cls_dev;
-    a.steps = int(n - 1);
-    a.first_is_first = 1;
+    a.steps = int(steps);
     a.barrier = b->p_words;
     a.abort_host = b->p_abort_host_dev;
     a.spin_limit = b->p_spin_limit;
@@ -181,17 +228,19 @@ hipError_t enqueue_persistent(sgpe_batch* b, int64_t n, bool imag, hipStream_t s
   for (const auto& k : b->cls) {
     const int cnt = int(k.members.size());
     const sgpe_ctx* c0 = b->inst[k.members[0]];
-    const RowArgs shape_r = row_args(c0);
-    const ColArgs shape_c = col_args(c0, imag, false);
-    const RowArgs* t_sc = k.row_tab + ROWTAB_SCALE * cnt;
-    const RowArgs* t_pa = k.row_tab + ROWTAB_PARTIALS * cnt;
-    if (e == hipSuccess)
-      e = sgpe::launch_row_batch(shape_r, (imag && n > 1) ? t_pa : t_sc, cnt, sgpe::ROW_STEP, imag, false, 8, s);
-    if (e == hipSuccess)
-      e = sgpe::launch_col_batch(shape_c, k.col_tab + (2 * int(imag) + 1) * cnt, cnt,
-                                 imag ? sgpe::NORM_SQ : sgpe::NORM_NONE, 8, s);
-    if (e == hipSuccess)
-      e = sgpe::launch_row_batch(shape_r, imag ? t_pa : t_sc, cnt, sgpe::ROW_INV, false, false, 8, s);
+    if (imag) {
+      const RowArgs shape_r = row_args(c0);
+      const RowArgs* t_sc = k.row_tab + ROWTAB_SCALE * cnt;
+      const RowArgs* t_pa = k.row_tab + ROWTAB_PARTIALS * cnt;
+      if (e == hipSuccess)
+        e = sgpe::launch_row_batch(shape_r, n > 1 ? t_pa : t_sc, cnt, sgpe::ROW_STEP, true, false, 8, s);
+      if (e == hipSuccess)
+        e = sgpe::launch_col_batch(col_args(c0, true, false), k.col_tab + COLTAB_HALF * cnt, cnt, sgpe::NORM_SQ, 8, s);
+      if (e == hipSuccess) e = sgpe::launch_row_batch(shape_r, t_pa, cnt, sgpe::ROW_INV, false, false, 8, s);
+    } else {
+      if (e == hipSuccess && n > 1) e = class_line(b, k, LINETAB_LAST, n % 2 != 0, s);
+      if (e == hipSuccess) e = class_line(b, k, LINETAB_HALF, n % 2 == 0, s);
+    }
   }
   return e;
 }
@@ -202,7 +251,7 @@ hipError_t enqueue_all(sgpe_batch* b, int64_t n, bool imag, hipStream_t origin) 
   hipError_t e = hipEventRecord(b->fork, origin);
   for (auto& k : b->cls) {
     if (e == hipSuccess) e = hipStreamWaitEvent(k.stream, b->fork, 0);
-    if (e == hipSuccess) e = enqueue_class(b, k, n, imag, k.stream);
+    if (e == hipSuccess) e = imag ? enqueue_class_imag(b, k, n, k.stream) : enqueue_class_real(b, k, n, k.stream);
     if (e == hipSuccess) e = hipEventRecord(k.done, k.stream);
   }
   for (auto& k : b->cls)
@@ -333,7 +382,8 @@ sgpe_status sgpe_batch_create(const sgpe_params* params, int32_t count, void* hi
     if (hipStreamCreateWithFlags(&k.stream, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&k.done, hipEventDisableTiming) != hipSuccess ||
         hipMalloc(reinterpret_cast<void**>(&k.row_tab), ROWTAB_N * n * sizeof(RowArgs)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&k.col_tab), COLTAB_N * n * sizeof(ColArgs)) != hipSuccess) {
+        hipMalloc(reinterpret_cast<void**>(&k.col_tab), COLTAB_N * n * sizeof(ColArgs)) != hipSuccess ||
+        hipMalloc(reinterpret_cast<void**>(&k.line_tab), LINETAB_N * n * sizeof(LineArgs)) != hipSuccess) {
       (void)hipGetLastError();
       return fail(SGPE_EDEVICE);
     }
@@ -353,6 +403,7 @@ void sgpe_batch_destroy(sgpe_batch* b) {
     if (k.stream) (void)hipStreamSynchronize(k.stream);
     if (k.row_tab) (void)hipFree(k.row_tab);
     if (k.col_tab) (void)hipFree(k.col_tab);
+    if (k.line_tab) (void)hipFree(k.line_tab);
     if (k.e_tab) (void)hipFree(k.e_tab);
     if (k.done) (void)hipEventDestroy(k.done);
     if (k.stream) (void)hipStreamDestroy(k.stream);
@@ -362,7 +413,7 @@ void sgpe_batch_destroy(sgpe_batch* b) {
     (void)hipStreamDestroy(b->graph_stream);
   }
   for (void* ptr : {static_cast<void*>(b->p_row_first), static_cast<void*>(b->p_row_imag),
-                    static_cast<void*>(b->p_col[0]), static_cast<void*>(b->p_col[1]),
+                    static_cast<void*>(b->p_col), static_cast<void*>(b->p_line[0]), static_cast<void*>(b->p_line[1]),
                     static_cast<void*>(b->p_row_items), static_cast<void*>(b->p_col_items),
                     static_cast<void*>(b->p_words), static_cast<void*>(b->p_cls_dev)})
     if (ptr) (void)hipFree(ptr);
@@ -532,7 +583,8 @@ static sgpe_status enable_persistent(sgpe_batch* b) {
   }
   const size_t n = b->inst.size();
   std::vector<RowArgs> first(n), imag(n);
-  std::vector<ColArgs> col_r(n), col_i(n);
+  std::vector<ColArgs> col(n);
+  std::vector<LineArgs> line_r(n), line_c(n);
   for (size_t i = 0; i < n; ++i) {
     const sgpe_ctx* c = b->inst[i];
     RowArgs a = row_args(c);
@@ -541,16 +593,17 @@ static sgpe_status enable_persistent(sgpe_batch* b) {
     a.partials = c->partials;
     a.n_partials = col_groups(c);
     imag[i] = a;
-    col_r[i] = col_args(c, false, false);
-    col_i[i] = col_args(c, true, false);
+    col[i] = col_args(c, true, false);
+    line_r[i] = line_args(c, false, LINE_FULL, LINE_FULL, 1);
+    line_c[i] = line_args(c, true, LINE_FULL, LINE_FULL, 1);
   }
   auto up = [](auto** dst, const auto& v) {
     using T = std::remove_reference_t<decltype(v[0])>;
     if (!*dst && hipMalloc(reinterpret_cast<void**>(dst), v.size() * sizeof(T)) != hipSuccess) return false;
     return hipMemcpy(*dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice) == hipSuccess;
   };
-  if (!up(&b->p_row_first, first) || !up(&b->p_row_imag, imag) || !up(&b->p_col[0], col_r) ||
-      !up(&b->p_col[1], col_i)) {
+  if (!up(&b->p_row_first, first) || !up(&b->p_row_imag, imag) || !up(&b->p_col, col) ||
+      !up(&b->p_line[0], line_r) || !up(&b->p_line[1], line_c)) {
     (void)hipGetLastError();
     return SGPE_ENOMEM;
   }
@@ -744,7 +797,7 @@ sgpe_status sgpe_batch_autotune(sgpe_batch* b, int32_t steps, double* best_ms) {
     BatchClass& k = b->cls[ci];
     const sgpe_ctx* c0 = b->inst[k.members[0]];
     const size_t bytes = size_t(c0->p.nx) * size_t(c0->p.ny) * sizeof(float4);
-    // keep the members' states: tuning runs real steps on them
+    // keep the members' states: tuning steps them
     std::vector<void*> saved(k.members.size(), nullptr);
     for (size_t j = 0; j < k.members.size() && st == SGPE_OK; ++j) {
       if (hipMalloc(&saved[j], bytes) != hipSuccess ||
@@ -771,9 +824,12 @@ sgpe_status sgpe_batch_autotune(sgpe_batch* b, int32_t steps, double* best_ms) {
             break;
           }
           if (set_class_schedule(b, k, s) != SGPE_OK) continue;  // not valid for this shape
-          hipError_t e = enqueue_class(b, k, 2, false, b->stream);
+          // both kinds of step: their kernels differ, and a class has one schedule for both
+          hipError_t e = enqueue_class_real(b, k, 2, b->stream);
+          if (e == hipSuccess) e = enqueue_class_imag(b, k, 2, b->stream, false);
           if (e == hipSuccess) e = hipEventRecord(t0, b->stream);
-          if (e == hipSuccess) e = enqueue_class(b, k, steps, false, b->stream);
+          if (e == hipSuccess) e = enqueue_class_real(b, k, steps, b->stream);
+          if (e == hipSuccess) e = enqueue_class_imag(b, k, steps, b->stream, false);
           if (e == hipSuccess) e = hipEventRecord(t1, b->stream);
           if (e == hipSuccess) e = hipEventSynchronize(t1);
           float ms = 0.0f;
@@ -788,7 +844,7 @@ sgpe_status sgpe_batch_autotune(sgpe_batch* b, int32_t steps, double* best_ms) {
           }
         }
     if (st == SGPE_OK) st = set_class_schedule(b, k, best_t < 0.0f ? start : best);
-    if (best_ms && best_t >= 0.0f) best_ms[ci] = double(best_t) / double(steps);
+    if (best_ms && best_t >= 0.0f) best_ms[ci] = double(best_t) / (2.0 * double(steps));
     for (size_t j = 0; j < k.members.size(); ++j) {
       if (saved[j]) {
         if (st == SGPE_OK &&

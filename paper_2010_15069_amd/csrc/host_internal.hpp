@@ -62,11 +62,13 @@ struct sgpe_ctx {
   std::vector<void*> allocations;
   double* host_part = nullptr;   // pinned host copy of reduction partials, grown on demand
   size_t host_part_n = 0;
-  // A step call of the default schedule (either precision) on a state the context owns leaves its last
-  // step's K(dt/2) and the inverse x-transform pending (1: real time, 2: imaginary time, 0: none);
-  // the next step call of the same kind merges them with its own first K(dt/2), and every other
-  // entry point completes them first (flush_tail, from check_ctx).
+  // A K-R-K step call (either precision) on a state the context owns leaves its last step's K(dt/2)
+  // pending (1: real time, with its last R along columns if tail_col, else along rows; 2: imaginary
+  // time, with the inverse x-transform pending too; 0: none); the next step call of the same kind
+  // merges it with its own first K(dt/2), and every other entry point completes it first
+  // (flush_tail, from check_ctx).
   int tail_pending = 0;
+  bool tail_col = false;
   // sgpe_relax_imag's ring of energy checks in flight (allocated on its first call): the energies
   // on the device, their pinned host copies, and an event after each copy
   double* relax_dev = nullptr;
@@ -95,6 +97,9 @@ sgpe_schedule get_schedule(const sgpe_ctx* c);
 // Row-pass arguments with the real-space coefficients of a sub-step h (h <= 0: h = dt).
 sgpe::RowArgs row_args(const sgpe_ctx* c, double h = 0.0);
 sgpe::ColArgs col_args(const sgpe_ctx* c, bool imag, bool half);
+// Real-time line passes: an op of K(dt/2) or K(dt) along the line, or none.
+enum LineOp { LINE_NONE, LINE_HALF, LINE_FULL };
+sgpe::LineArgs line_args(const sgpe_ctx* c, bool col, LineOp pre, LineOp post, int n_r, double h_sub = 0.0);
 // Validates the context and makes its device current, then completes a pending step tail, so
 // that the state is in its documented layout: every entry point but the step calls uses this one.
 sgpe_status check_ctx(sgpe_ctx* c);

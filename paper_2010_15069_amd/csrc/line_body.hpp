@@ -1,0 +1,128 @@
+// Device body of the line pass, the one sweep of a real-time step (see line_launch.hpp for the
+// kernels and for why one sweep is enough).
+#pragma once
+
+#include "col_body.hpp"
+#include "row_body.hpp"
+
+namespace sgpe {
+
+extern __shared__ __align__(16) unsigned char line_lds[];
+
+// Lines of length N along the rows (COL = false) or the columns of the state.  P points per lane;
+// lanes 2j and 2j+1 hold the two components of the same points, as in the row and column passes,
+// whose memory and LDS layouts these are.
+//
+// Both ops run through one loop body, so an op is the same instructions whether it shares a pass with R
+// or has one of its own: a call that leaves its last ops to a later pass gives the bits of one that
+// does not.  The 1/N of each inverse transform waits for the store (R takes it through its couplings);
+// all of it is a power of two.
+template <int N, bool COL, bool FULL, bool NLN, int P, bool WT, class R>
+__device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngroups) {
+  using C = cplx_t<R>;
+  using Q = point_t<R>;
+  C* const lds_raw = reinterpret_cast<C*>(line_lds);
+  constexpr int T = N / P;
+  constexpr int SLOTS = N + N / 16;
+  constexpr uint32_t PB = sizeof(Q), CB = sizeof(C);   // bytes per point / component
+  const int tid = threadIdx.x;
+  const int comp = tid & 1;
+  const int pair = tid >> 1;
+  int line, t;
+  LdsView<C> lds;
+  uint32_t off, mstride;
+  if constexpr (COL) {
+    const int sh = __builtin_ctz(a.lines);
+    const int cc = pair & (a.lines - 1);
+    t = pair >> sh;
+    line = (col_group(wg, ngroups) << sh) + cc;
+    lds = LdsView<C>{lds_raw + 2 * cc + comp, 1 + sh};
+    const uint32_t rstride = PB * static_cast<uint32_t>(a.nx);
+    off = static_cast<uint32_t>(t) * rstride + PB * static_cast<uint32_t>(line) + CB * comp;
+    mstride = static_cast<uint32_t>(T) * rstride;
+  } else {
+    const int rloc = pair / T;
+    t = pair - rloc * T;
+    line = wg * a.lines + rloc;
+    lds = LdsView<C>{lds_raw + rloc * 2 * SLOTS + comp, 1};
+    off = static_cast<uint32_t>(line) * (PB * N) + static_cast<uint32_t>(t) * PB + CB * comp;
+    mstride = PB * T;
+  }
+  const char* __restrict__ base = reinterpret_cast<const char*>(a.psi);
+  char* __restrict__ out = reinterpret_cast<char*>(a.psi);
+  C v[P];
+#pragma unroll
+  for (int m = 0; m < P; ++m) v[m] = *reinterpret_cast<const C*>(base + (off + mstride * m));
+  TwPlain<N, P, R> tr;
+  load_twiddles<N>(tr, t, a.tw);
+  R hb_line[P], hb_cross = R(0);
+  if constexpr (FULL) {
+#pragma unroll
+    for (int m = 0; m < P; ++m) hb_line[m] = a.hbx[t + T * m] * a.hfrac;
+    hb_cross = a.hby[line] * a.hfrac;
+  }
+  // An op's table values of the lane's points are loaded before the forward transform, so that their
+  // latency hides behind it, at 8 or 4 points per lane (complex128 at 64^2: 7.3 us per step, against 7.6
+  // loaded where used); at 16 points the transform needs the registers (254 VGPRs without a spill at 1024
+  // points; with the values held, 53 spilled and a step took 26.1 us at 1024^2 instead of 19.3), and
+  // they are loaded where used.
+  R s = R(1);
+#pragma unroll 1
+  for (int stage = 0; stage < 2; ++stage) {
+    const void* const op = stage == 0 ? a.op_pre : a.op_post;
+    if (op != nullptr) {
+      if constexpr (COL) {
+        const C* __restrict__ tab = static_cast<const C*>(op);   // P(k_y) - 1
+        constexpr bool EARLY = P < 16;
+        C q[EARLY ? P : 1];
+        if constexpr (EARLY) {
+#pragma unroll
+          for (int m = 0; m < P; ++m) q[m] = tab[t + T * m];
+        }
+        fwd_pass<N>(v, lds, t, tr);
+#pragma unroll
+        for (int m = 0; m < P; ++m) {
+          C e;
+          if constexpr (EARLY) e = q[m];
+          else e = tab[t + T * m];
+          const C w = v[m];
+          v[m] = mk2(w.x + fma_(-e.y, w.y, e.x * w.x), w.y + fma_(e.y, w.x, e.x * w.y));
+        }
+      } else {
+        // this component's row of M'(k_x) - 1, {own, other}
+        const Q* __restrict__ tab = static_cast<const Q*>(op);
+        constexpr bool EARLY = P < 16;
+        Q d[EARLY ? P : 1];
+        if constexpr (EARLY) {
+#pragma unroll
+          for (int m = 0; m < P; ++m) d[m] = tab[2 * (t + T * m) + comp];
+        }
+        fwd_pass<N>(v, lds, t, tr);
+#pragma unroll
+        for (int m = 0; m < P; ++m) {
+          Q e;
+          if constexpr (EARLY) e = d[m];
+          else e = tab[2 * (t + T * m) + comp];
+          const C w = v[m];
+          const C o = pair_swap(w);
+          const R cr = fma_(-e.w, o.y, fma_(e.z, o.x, fma_(-e.y, w.y, e.x * w.x)));
+          const R ci = fma_(e.w, o.x, fma_(e.z, o.y, fma_(e.y, w.x, e.x * w.y)));
+          v[m] = mk2(w.x + cr, w.y + ci);
+        }
+      }
+      inv_pass<N>(v, lds, t, tr);
+      s *= R(1) / R(N);
+    }
+    if (stage == 0) {
+#pragma unroll 1
+      for (int r = 0; r < a.n_r; ++r) {
+        if constexpr (NLN) row_apply_r_nln<N, false, FULL>(v, a, line, t, comp == 0, hb_line, hb_cross, s * s);
+        else row_apply_r<N, false, FULL>(v, a, line, t, comp == 0, hb_line, hb_cross, s * s);
+      }
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < P; ++m) store_state<WT>(reinterpret_cast<C*>(out + (off + mstride * m)), vscale(v[m], s));
+}
+
+}  // namespace sgpe

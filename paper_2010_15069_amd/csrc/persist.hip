@@ -6,10 +6,11 @@
 // one instance, a column item 1024 / ny columns.  Each item runs in a 256-thread workgroup at 8 points
 // per lane, with the same device bodies (row_body, col_body) and the same per-instance arguments
 // as the single-instance and per-class launches, so every instance computes exactly what a single
-// context with that schedule computes.  The steps of the split step (Sec. 3.2's K(dt/2) R(dt) K(dt/2)
-// with the adjacent K halves merged) alternate a row phase (inverse x-FFT, scale, R(dt), forward
+// context with that schedule computes.  Imaginary-time steps of the split step (Sec. 3.2's
+// K(dt/2) R(dt) K(dt/2) with the adjacent K halves merged) alternate a row phase (inverse x-FFT, scale, R(dt), forward
 // x-FFT for every row item) and a column phase (forward y-FFT, K(dt) and the imaginary-time norm
-// partials, inverse y-FFT for every column item), with a barrier after each phase.
+// partials, inverse y-FFT for every column item), with a barrier after each phase.  A real-time step is
+// one phase of line passes (line_launch.hpp), along rows and columns in turn.
 //
 // The workgroups stay resident for the whole launch.  They form eight groups by blockIdx.x mod 8:
 // the dispatcher deals a launch's workgroups to the eight XCDs in turn, so a group is the
@@ -26,8 +27,7 @@
 // polls, records the failure in host-visible memory and returns; every workgroup then leaves at its
 // next barrier, and the host reports SGPE_EDEVICE.  A small kernel zeroes the counters and the abort
 // word before each launch (graph-replay safe).
-#include "col_body.hpp"
-#include "row_body.hpp"
+#include "line_body.hpp"
 
 namespace sgpe {
 
@@ -71,25 +71,43 @@ __device__ __forceinline__ bool persist_barrier(const PersistArgs& a, unsigned n
 // One class's workgroups (in one group) run all the launch's steps of that class's instances in the
 // group with the body of its grid size, so only that body's per-lane constants are live in them;
 // every workgroup of the group meets at every barrier (one beyond its class's share takes no items).
+// Imaginary time: a row and a column phase per step, the launch's first row phase with the fixed scale.
+// Real time: one phase of line passes per step, rows first, the axes alternating.
 template <int N, bool IMAG>
 __device__ __forceinline__ void persist_class(const PersistArgs& a, const PersistClass& k, int local) {
-  constexpr int NORM = IMAG ? NORM_DOT : NORM_NONE;
   const int first = local < k.wg_count ? local : k.n_row + k.n_col;   // past every item: idle
   unsigned nb = 0;
   for (int s = 0; s < a.steps; ++s) {
-    const RowArgs* rows = (s == 0 && a.first_is_first) ? a.row_first : a.row_step;
-    for (int i = first; i < k.n_row; i += k.wg_count) {
-      const int4 it = a.row_items[k.row_begin + i];
-      row_body<N, ROW_STEP, IMAG, false, 1, 8, true>(rows[it.x], it.y);
-      __syncthreads();
+    if constexpr (IMAG) {
+      const RowArgs* rows = s == 0 ? a.row_first : a.row_step;
+      for (int i = first; i < k.n_row; i += k.wg_count) {
+        const int4 it = a.row_items[k.row_begin + i];
+        row_body<N, ROW_STEP, true, false, 1, 8, true>(rows[it.x], it.y);
+        __syncthreads();
+      }
+      if (!persist_barrier(a, ++nb)) return;
+      for (int i = first; i < k.n_col; i += k.wg_count) {
+        const int4 it = a.col_items[k.col_begin + i];
+        col_body<N, NORM_DOT, 1, 8, true>(a.col[it.x], it.y, it.w);
+        __syncthreads();
+      }
+      if (!persist_barrier(a, ++nb)) return;
+    } else {
+      if (s % 2 == 0) {
+        for (int i = first; i < k.n_row; i += k.wg_count) {
+          const int4 it = a.row_items[k.row_begin + i];
+          line_body<N, false, false, false, 8, true>(a.line_row[it.x], it.y, it.w);
+          __syncthreads();
+        }
+      } else {
+        for (int i = first; i < k.n_col; i += k.wg_count) {
+          const int4 it = a.col_items[k.col_begin + i];
+          line_body<N, true, false, false, 8, true>(a.line_col[it.x], it.y, it.w);
+          __syncthreads();
+        }
+      }
+      if (!persist_barrier(a, ++nb)) return;
     }
-    if (!persist_barrier(a, ++nb)) return;
-    for (int i = first; i < k.n_col; i += k.wg_count) {
-      const int4 it = a.col_items[k.col_begin + i];
-      col_body<N, NORM, 1, 8, true>(a.col[it.x], it.y, it.w);
-      __syncthreads();
-    }
-    if (!persist_barrier(a, ++nb)) return;
   }
 }
 

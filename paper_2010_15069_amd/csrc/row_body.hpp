@@ -171,19 +171,27 @@ __device__ __forceinline__ C apply_r_full(C w, C o, const RFull<T>& f, T hbx, T 
 // when every lane's angles allow it (the common case), else the general one -- a wave-uniform
 // branch, so a wave never runs both.
 // hbx_r: this lane's h Omega_x / 2 at its P positions, hb_row: h Omega_y / 2 of the row (full
-// 2x2 variant only; loaded by the caller ahead of the transforms).
-template <int N, bool IMAG, bool FULL, int P, class C, class R>
-__device__ __forceinline__ void row_apply_r(C (&v)[P], const RowArgsT<R>& a, int row, int t, bool up,
-                                            const R (&hbx_r)[P], R hb_row) {
-  constexpr int T = N / P;
+// 2x2 variant only; loaded by the caller ahead of the transforms).  A: any argument struct with the
+// real-space fields of RowArgsT (x along the line the lane holds, y across).  gs: the square of the
+// scale that v still lacks (a power of two, so folding it into the couplings is exact).
+template <class R, class A>
+__device__ __forceinline__ RCoef<R> r_coefs(const A& a, bool up, R gs) {
   RCoef<R> c;
   c.sgn = up ? R(1) : R(-1);
   c.hd_own = up ? a.hdelta2 : -a.hdelta2;
-  c.hg_own = up ? a.hg_uu : a.hg_dd;
-  c.hg_ud = a.hg_ud;
-  c.hg_uu = a.hg_uu;
-  c.hg_dd = a.hg_dd;
+  c.hg_uu = a.hg_uu * gs;
+  c.hg_dd = a.hg_dd * gs;
+  c.hg_ud = a.hg_ud * gs;
+  c.hg_own = up ? c.hg_uu : c.hg_dd;
   c.hdelta2 = a.hdelta2;
+  return c;
+}
+
+template <int N, bool IMAG, bool FULL, int P, class C, class R, class A>
+__device__ __forceinline__ void row_apply_r(C (&v)[P], const A& a, int row, int t, bool up,
+                                            const R (&hbx_r)[P], R hb_row, R gs = R(1)) {
+  constexpr int T = N / P;
+  const RCoef<R> c = r_coefs(a, up, gs);
   const R y = fma_(static_cast<R>(row), a.dy, a.y0);
   const R hvy = a.hvy * y * y;
 #pragma unroll
@@ -211,25 +219,11 @@ __device__ __forceinline__ void row_apply_r(C (&v)[P], const RowArgsT<R>& a, int
 // R(h) split to second order as N(h/2) L(h) N(h/2): the mean-field phase with the densities of
 // its input, the exponential of the linear real-space terms (trap, detuning, spatial coupling),
 // the mean-field phase again with the updated densities.  Coefficients as in row_apply_r.
-template <int N, bool IMAG, bool FULL, int P, class C, class R>
-__device__ __forceinline__ void row_apply_r_nln(C (&v)[P], const RowArgsT<R>& a, int row, int t, bool up,
-                                                const R (&hbx_r)[P], R hb_row) {
-  if constexpr (!FULL && !IMAG) {
-    // Real time with a diagonal linear part: the three factors are phases, which commute and leave
-    // both densities as they are, so their product is the one phase of the frozen form with the
-    // input's densities -- the same exponent, evaluated once instead of three times.
-    row_apply_r<N, IMAG, FULL>(v, a, row, t, up, hbx_r, hb_row);
-    return;
-  }
+template <int N, bool IMAG, bool FULL, int P, class C, class R, class A>
+__device__ __forceinline__ void row_apply_r_nln(C (&v)[P], const A& a, int row, int t, bool up,
+                                                const R (&hbx_r)[P], R hb_row, R gs = R(1)) {
   constexpr int T = N / P;
-  RCoef<R> c;
-  c.sgn = up ? R(1) : R(-1);
-  c.hd_own = up ? a.hdelta2 : -a.hdelta2;
-  c.hg_own = up ? a.hg_uu : a.hg_dd;
-  c.hg_ud = a.hg_ud;
-  c.hg_uu = a.hg_uu;
-  c.hg_dd = a.hg_dd;
-  c.hdelta2 = a.hdelta2;
+  const RCoef<R> c = r_coefs(a, up, gs);
   const R y = fma_(static_cast<R>(row), a.dy, a.y0);
   const R hvy = a.hvy * y * y;
   auto half_n = [&](C w) {

@@ -1,7 +1,7 @@
 // HIP kernels of the split-step solver for gfx950: the row pass.
 //
-// One Strang step K(dt/2) R(dt) K(dt/2) (Sec. 3.2) is computed by two fused sweeps over the
-// state, which lives in HBM as [ny][nx] float4 {re_up, im_up, re_dn, im_dn}:
+// One imaginary-time Strang step K(dt/2) R(dt) K(dt/2) (Sec. 3.2) is computed by two fused sweeps over
+// the state (a real-time step takes one, see line_launch.hpp), which lives in HBM as [ny][nx] float4 {re_up, im_up, re_dn, im_dn}:
 //
 //   row pass    -- per row: inverse x-FFT, scale, real-space 2x2 exponential R (trap, detuning,
 //                  mean field, spatial Raman coupling; Eqs. (H2)-(H4)), forward x-FFT;
@@ -99,22 +99,19 @@ static hipError_t row_launch_n(const RowArgs& a, const RowArgs* tab, int count, 
   switch (mode) {
     case ROW_FWD: return row_launch_t<N, ROW_FWD, false, false>(a, tab, count, iters, points, s);
     case ROW_INV: return row_launch_t<N, ROW_INV, false, false>(a, tab, count, iters, points, s);
+    // real-time steps take the line pass (line_launch.hpp)
     case ROW_STEP:
-      if (imag) return full ? row_launch_t<N, ROW_STEP, true, true>(a, tab, count, iters, points, s)
-                            : row_launch_t<N, ROW_STEP, true, false>(a, tab, count, iters, points, s);
-      return full ? row_launch_t<N, ROW_STEP, false, true>(a, tab, count, iters, points, s)
-                  : row_launch_t<N, ROW_STEP, false, false>(a, tab, count, iters, points, s);
+      if (!imag) return hipErrorInvalidValue;
+      return full ? row_launch_t<N, ROW_STEP, true, true>(a, tab, count, iters, points, s)
+                  : row_launch_t<N, ROW_STEP, true, false>(a, tab, count, iters, points, s);
     case ROW_STEP_NLN:
-      // real time with a diagonal linear part: N L N is exactly the frozen form's one phase
-      if (imag) return full ? row_launch_t<N, ROW_STEP_NLN, true, true>(a, tab, count, iters, points, s)
-                            : row_launch_t<N, ROW_STEP_NLN, true, false>(a, tab, count, iters, points, s);
-      return full ? row_launch_t<N, ROW_STEP_NLN, false, true>(a, tab, count, iters, points, s)
-                  : row_launch_t<N, ROW_STEP, false, false>(a, tab, count, iters, points, s);
+      if (!imag) return hipErrorInvalidValue;
+      return full ? row_launch_t<N, ROW_STEP_NLN, true, true>(a, tab, count, iters, points, s)
+                  : row_launch_t<N, ROW_STEP_NLN, true, false>(a, tab, count, iters, points, s);
     case ROW_VAR:
-      if (imag) return full ? row_launch_t<N, ROW_VAR, true, true>(a, tab, count, iters, points, s)
-                            : row_launch_t<N, ROW_VAR, true, false>(a, tab, count, iters, points, s);
-      return full ? row_launch_t<N, ROW_VAR, false, true>(a, tab, count, iters, points, s)
-                  : row_launch_t<N, ROW_VAR, false, false>(a, tab, count, iters, points, s);
+      if (!imag) return hipErrorInvalidValue;
+      return full ? row_launch_t<N, ROW_VAR, true, true>(a, tab, count, iters, points, s)
+                  : row_launch_t<N, ROW_VAR, true, false>(a, tab, count, iters, points, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -159,10 +156,9 @@ static hipError_t row_launch_c128_n(const RowArgsT<double>& a, int mode, bool im
     case ROW_FWD: return row_launch_c128<N, ROW_FWD, false, false>(a, points, s);
     case ROW_INV: return row_launch_c128<N, ROW_INV, false, false>(a, points, s);
     case ROW_STEP:
-      if (imag) return full ? row_launch_c128<N, ROW_STEP, true, true>(a, points, s)
-                            : row_launch_c128<N, ROW_STEP, true, false>(a, points, s);
-      return full ? row_launch_c128<N, ROW_STEP, false, true>(a, points, s)
-                  : row_launch_c128<N, ROW_STEP, false, false>(a, points, s);
+      if (!imag) return hipErrorInvalidValue;
+      return full ? row_launch_c128<N, ROW_STEP, true, true>(a, points, s)
+                  : row_launch_c128<N, ROW_STEP, true, false>(a, points, s);
     default: return hipErrorInvalidValue;
   }
 }

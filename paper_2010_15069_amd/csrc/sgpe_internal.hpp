@@ -89,6 +89,30 @@ struct ColArgsT {
 };
 using ColArgs = ColArgsT<float>;
 
+// Line pass (real time): in place on real-space data, per line along one axis:
+//   [op_pre]  n_r x R(h)  [op_post]
+// where an op is F^-1 U F along the line, U the factor of the k-space propagator that belongs to
+// the axis (rows: M'(k_x), columns: P(k_y)).  The real-space fields have RowArgsT's names with x the
+// axis along the line and y the one across it, whichever the grid's axes are.
+template <class T>
+struct LineArgsT {
+  point_t<T>* psi;           // [ny][nx] state, in place
+  int nx;                    // row length of the state in memory
+  int lines;                 // lines (rows or columns) per workgroup
+  const point_t<T>* tw;      // roots of the line's length
+  const void* op_pre;        // M' - 1 as in ColArgsT::kx_tab (rows) or P - 1 as in ky_tab (columns);
+  const void* op_post;       //   NULL: that op is not applied
+  int n_r;                   // real-space sub-steps R(h) in turn (0, 1 or 2)
+  T x0, dx, y0, dy;
+  T hvx, hvy;
+  T hdelta2;
+  T hg_uu, hg_dd, hg_ud;
+  const T* hbx;              // h Omega / 2 along the line and across it (full 2x2 variant only),
+  const T* hby;              //   built for h = dt and scaled by
+  T hfrac;                   //   h / dt
+};
+using LineArgs = LineArgsT<float>;
+
 constexpr int kEnergyRowParts = 3;
 
 struct EnergyArgs {
@@ -142,6 +166,15 @@ hipError_t launch_row_batch(const RowArgs& shape, const RowArgs* tab, int count,
                             int points, hipStream_t s);
 hipError_t launch_col_batch(const ColArgs& shape, const ColArgs* tab, int count, int norm_mode, int points,
                             hipStream_t s);
+// Line passes along rows (col = false) or columns: `lines` lines per workgroup at `points` points
+// per lane; nln: each R(h) as N(h/2) L(h) N(h/2).  A batched launch takes its instances' arguments from
+// tab (device), as the row and column passes do; n_lines is the number of lines across the grid.
+hipError_t launch_line(const LineArgs& a, int n, int n_lines, bool col, bool full2x2, bool nln, int points,
+                       hipStream_t s);
+hipError_t launch_line(const LineArgsT<double>& a, int n, int n_lines, bool col, bool full2x2, int points,
+                       hipStream_t s);
+hipError_t launch_line_batch(const LineArgs& shape, const LineArgs* tab, int count, int n, int n_lines, bool col,
+                             bool full2x2, int points, hipStream_t s);
 hipError_t launch_energy(const EnergyArgs& a, hipStream_t s);
 // The energy per particle from the partials launch_energy wrote (a's buffers), combined on the
 // device in a fixed order and written to out (one double, device memory).
@@ -191,13 +224,14 @@ struct PersistClass {
 };
 struct PersistArgs {
   const RowArgs* row_first;   // per instance: the row pass of a call's first step (fixed scale)
-  const RowArgs* row_step;    // per instance: later steps (imaginary time: scale from the partials)
-  const ColArgs* col;         // per instance: K(dt), norm partials in imaginary time
+  const RowArgs* row_step;    // per instance: later steps (scale from the partials)
+  const ColArgs* col;         // per instance: K(dt) with norm partials
+  const LineArgs* line_row;   // per instance, real time: a steady-state step along rows
+  const LineArgs* line_col;   //   and along columns
   const int4* row_items;
   const int4* col_items;
   const PersistClass* cls;    // [kPersistGroups][kPersistClasses], device memory
   int steps;                  // steady-state steps in this launch
-  int first_is_first;         // 1: the launch's first step is the call's first (row_first)
   unsigned* barrier;          // device words of the group barriers, kPersistWords (zeroed per launch)
   unsigned* abort_host;       // host-visible: a barrier wait gave up
   unsigned spin_limit;        // polls before a barrier wait gives up
