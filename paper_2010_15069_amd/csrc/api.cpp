@@ -110,21 +110,15 @@ sgpe_status raman_tables(sgpe_ctx* c, const double* om_x, const double* om_y) {
   return SGPE_OK;
 }
 
-// Forward roots exp(-2 pi i j / n), j < n / 2, in fp64 (energy kernels).
-// Roots exp(-2 pi i j / n) rounded once to fp32 as {cos, sin, eta, 0}, where
-// 1 + eta = 1 / (cos^2 + sin^2) of the rounded pair (evaluated in fp64): the step kernels'
-// forward transform multiplies by the rounded root, their exact inverse by conj(root)(1 + eta),
-// whose low part conj(root) eta they form from cos, sin and eta.
-// fp64 (complex128 kernels): the roots rounded to fp64 with eta = 0 -- their modulus error, ~1e-16,
-// needs no correction at that precision.
+// Root table of a transform of length n: (tan(phi / 2), sin(phi)) of phi = 2 pi j / n at entry j + n/4,
+// |j| <= n/4 -- the shears of a rotation by phi (see "Step-kernel transforms" in fft_device.hpp), each
+// rounded once to T.
 template <class T = float>
-std::vector<sgpe::point_t<T>> twiddles_plain(int n) {
-  std::vector<sgpe::point_t<T>> t(n);
-  for (int j = 0; j < n; ++j) {
+std::vector<sgpe::cplx_t<T>> root_table(int n) {
+  std::vector<sgpe::cplx_t<T>> t(n / 2 + 1);
+  for (int j = -n / 4; j <= n / 4; ++j) {
     const double a = 2.0 * M_PI * double(j) / double(n);
-    const T c = T(std::cos(a)), s = T(std::sin(a));
-    const double eta = std::is_same<T, float>::value ? 1.0 / (double(c) * double(c) + double(s) * double(s)) - 1.0 : 0.0;
-    t[j] = mk4(c, s, eta, 0.0, T());
+    t[j + n / 4] = mk2h(std::tan(0.5 * a), std::sin(a), T());
   }
   return t;
 }
@@ -882,11 +876,11 @@ sgpe_status sgpe_create_ex(const sgpe_params* p, int32_t precision, void* hip_st
   }
   if (c128) c->psi64 = static_cast<double4*>(state);
   else c->psi = static_cast<float4*>(state);
-  if ((st = upload(c, &c->twp64_x, twiddles_plain<double>(p->nx))) != SGPE_OK) return fail(st);
-  if ((st = upload(c, &c->twp64_y, twiddles_plain<double>(p->ny))) != SGPE_OK) return fail(st);
+  if ((st = upload(c, &c->twp64_x, root_table<double>(p->nx))) != SGPE_OK) return fail(st);
+  if ((st = upload(c, &c->twp64_y, root_table<double>(p->ny))) != SGPE_OK) return fail(st);
   if (!c128) {
-    if ((st = upload(c, &c->twp_x, twiddles_plain(p->nx))) != SGPE_OK) return fail(st);
-    if ((st = upload(c, &c->twp_y, twiddles_plain(p->ny))) != SGPE_OK) return fail(st);
+    if ((st = upload(c, &c->twp_x, root_table(p->nx))) != SGPE_OK) return fail(st);
+    if ((st = upload(c, &c->twp_y, root_table(p->ny))) != SGPE_OK) return fail(st);
   }
   for (int imag = 0; imag < 2; ++imag) {
     for (int half = 0; half < 2; ++half) {

@@ -42,9 +42,14 @@ __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngrou
   const char* __restrict__ base = reinterpret_cast<const char*>(a.psi);
   char* __restrict__ out = reinterpret_cast<char*>(a.psi);
   const uint32_t rstride = PB * static_cast<uint32_t>(a.nx);
-  const uint32_t mstride = static_cast<uint32_t>(T) * rstride;
   const uint32_t tile_stride = PB * static_cast<uint32_t>(C);
-  uint32_t off = static_cast<uint32_t>(t) * rstride + PB * static_cast<uint32_t>(x0) + CB * comp;
+  const LanePos<T> rp = real_pos<N, P>(t), sp = spec_pos<N, P>(t);
+  uint32_t row_off[P];   // of the lane's rows
+#pragma unroll
+  for (int m = 0; m < P; ++m)
+    row_off[m] = m == 0 ? static_cast<uint32_t>(rp.p0) * rstride
+                        : static_cast<uint32_t>(rp.b) * rstride + static_cast<uint32_t>(T * m) * rstride;
+  uint32_t off = PB * static_cast<uint32_t>(x0) + CB * comp;
 
   // The k_y operator values of the lane's P rows.  With 16 points per lane the row is staged in
   // LDS (loaded per point after the forward transform, its latency would sit in the middle of the
@@ -67,11 +72,11 @@ __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngrou
       if (k * nth < N) kyv[k] = a.ky_tab[min(tid + k * nth, N - 1)];
   } else {
 #pragma unroll
-    for (int m = 0; m < P; ++m) kyr[m] = a.ky_tab[t + T * m];
+    for (int m = 0; m < P; ++m) kyr[m] = a.ky_tab[sp.at(m)];
   }
   CX v[P], nxt[P];
 #pragma unroll
-  for (int m = 0; m < P; ++m) v[m] = *reinterpret_cast<const CX*>(base + (off + mstride * m));
+  for (int m = 0; m < P; ++m) v[m] = *reinterpret_cast<const CX*>(base + (off + row_off[m]));
   // this component's row of M' - 1 at k_x: {d_own, d_other}
   point_t<R> d = a.kx_tab[2 * x0 + comp], dn = d;
   TwPlain<N, P, R> tr;
@@ -89,7 +94,7 @@ __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngrou
     if (it + 1 < ITERS) {
 #pragma unroll
       for (int m = 0; m < P; ++m)
-        nxt[m] = *reinterpret_cast<const CX*>(base + (off + tile_stride + mstride * m));
+        nxt[m] = *reinterpret_cast<const CX*>(base + (off + tile_stride + row_off[m]));
       dn = a.kx_tab[2 * (x0 + (it + 1) * C) + comp];
     }
     fwd_pass<N>(v, lds, t, tr);
@@ -100,8 +105,8 @@ __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngrou
       const CX w = v[m];
       const CX o = pair_swap(w);
       CX q;
-      if constexpr (KY_GLOBAL) q = a.ky_tab[t + T * m];
-      else if constexpr (KY_LDS) q = kyl[t + T * m];
+      if constexpr (KY_GLOBAL) q = a.ky_tab[sp.at(m)];
+      else if constexpr (KY_LDS) q = kyl[sp.at(m)];
       else q = kyr[m];
       const R c1r = fma_(-d.w, o.y, fma_(d.z, o.x, fma_(-d.y, w.y, d.x * w.x)));
       const R c1i = fma_(d.w, o.x, fma_(d.z, o.y, fma_(d.y, w.x, d.x * w.y)));
@@ -119,7 +124,7 @@ __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngrou
     inv_pass<N>(v, lds, t, tr);
 
 #pragma unroll
-    for (int m = 0; m < P; ++m) store_state<WT>(reinterpret_cast<CX*>(out + (off + mstride * m)), v[m]);
+    for (int m = 0; m < P; ++m) store_state<WT>(reinterpret_cast<CX*>(out + (off + row_off[m])), v[m]);
     if (it + 1 < ITERS) {
 #pragma unroll
       for (int m = 0; m < P; ++m) v[m] = nxt[m];

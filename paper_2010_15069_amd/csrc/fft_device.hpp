@@ -3,14 +3,15 @@
 // exchange and fp64 reductions.
 //
 // FFT organisation (transform length N, P points per lane, P in {4, 8, 16}): T = N/P lanes own one
-// transform, lane t holding the P positions t + T*m (m = 0..P-1); in the step kernels each lane
-// owns one spinor component and the neighbouring lane the other component of the same positions.
-// Each Stockham stage of radix R (P, then a smaller remainder) performs P/R butterflies per lane on
-// registers; the outputs of every stage but the last go through LDS, and the last stage's outputs
-// land back in the lane's own registers in natural order.  So the first stage reads and the last
-// stage writes the positions t + T*m, which are contiguous across lanes: global loads and stores
-// are coalesced and no digit-reversal pass exists.  Roots are rounded once to fp32; the inverse
-// transform is the exact inverse of the forward one (see "Step-kernel transforms" below).
+// transform, lane t holding the P positions = t mod T; in the step kernels each lane owns one spinor
+// component and the neighbouring lane the other component of the same positions.  Each Stockham stage
+// of radix R (P, then a smaller remainder) performs P/R butterflies per lane on registers; the outputs
+// of every stage but the last go through LDS, and the last stage's outputs land back in the lane's own
+// registers.  So the first stage reads and the last stage writes positions that are contiguous across
+// lanes: global loads and stores are coalesced and no digit-reversal pass exists.  Which register holds
+// which of its positions a lane learns from real_pos (before the forward transform, after the inverse)
+// and spec_pos (between them).  The inverse transform is the exact inverse of the forward one (see
+// "Step-kernel transforms" below).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -103,6 +104,16 @@ __device__ __forceinline__ int2 batch_item() {
 }
 
 // ---------------------------------------------------------------------------------------------
+// Positions of a lane's registers: m T + t, or -- where a stage works with signed digits (below) --
+// that sequence rotated by one register, (m - 1) T + t with register 0 wrapping to the end.
+// ---------------------------------------------------------------------------------------------
+template <int STEP>
+struct LanePos {
+  int b, p0;   // register m > 0 holds b + STEP m (b may be negative), register 0 holds p0
+  __device__ __forceinline__ int at(int m) const { return m == 0 ? p0 : b + STEP * m; }
+};
+
+// ---------------------------------------------------------------------------------------------
 // LDS addressing: a transform's N positions occupy N + N/16 slots (one pad slot per 16
 // positions) and `stride` transforms are interleaved slot by slot, so that lanes which own
 // neighbouring transforms touch neighbouring slots.
@@ -111,72 +122,88 @@ template <class V>
 struct LdsView {
   V* base;     // slot 0 of this thread's transform
   int shift;   // log2 of the number of interleaved transforms (a power of two)
-  __device__ __forceinline__ V& at(int pos) const { return base[(pos + (pos >> 4)) << shift]; }
+  static __device__ __forceinline__ int slot(int pos) { return pos + (pos >> 4); }
+  __device__ __forceinline__ V& at(int pos) const { return base[slot(pos) << shift]; }
+  // position pos.at(m); steps of a multiple of 16 positions are steps of a fixed number of slots, so
+  // the lane's one base serves every m > 0
+  template <int STEP>
+  __device__ __forceinline__ V& at(const LanePos<STEP>& pos, int m) const {
+    if constexpr (STEP % 16 == 0) {
+      return m == 0 ? at(pos.p0) : (base + (slot(pos.b) << shift))[(STEP / 16 * 17 * m) << shift];
+    } else {
+      return at(pos.at(m));
+    }
+  }
 };
 
 // ---------------------------------------------------------------------------------------------
-// Step-kernel transforms: a forward transform with roots rounded once to fp32, and its exact
-// inverse.
+// Step-kernel transforms: a forward transform with rounded roots, and its exact inverse.
 //
-// A forward transform with fp32-rounded roots w~ is a slightly perturbed DFT.  Followed by the
-// textbook inverse (conjugate roots), the round trip is not the identity: |w~| != 1 scales every
-// butterfly path and that same map is re-applied every step (a coherent drift).  Here the inverse
-// instead undoes the forward stage by stage in reverse order: each small DFT by its conjugate
-// structure and each rounded root by v = conj(w~) / |w~|^2.  v is held as conj(w~) plus a low part
-// conj(w~) eta (eta = 1/|w~|^2 - 1, about 1e-8) that enters the fma chain of the product before
-// the large terms, so every result is rounded once from the exact product.  (Scaling a rounded
-// product by 1 + eta afterwards does not work: eta is below half an ulp and the rounding drops
-// it, the same way every step.)  The pair is then an exact inverse in exact arithmetic, the round
-// trip carries only unbiased rounding, and the rounded roots enter the split step only through
-// commutators with the step's operators, O(dt eps) per step.  The forward costs 4 instructions
-// per complex product instead of 8 for a compensated one; the inverse costs 8.
+// A transform with rounded roots is a slightly perturbed DFT.  Followed by the textbook inverse
+// (conjugate roots), the round trip is not the identity: rounded roots have |w| != 1, and that same
+// map is re-applied every step (a coherent drift).  Here every rotation by an angle phi is three
+// shears (lifting steps)
+//     x += p y,  y -= u x,  x += p y,     p = tan(phi / 2), u = sin(phi),
+// and its inverse the same shears with the signs turned, which undoes them exactly in exact arithmetic
+// whatever p and u were rounded to.  The inverse transform undoes the forward one stage by stage, so
+// the pair is an exact inverse, the round trip carries only unbiased rounding, and the rounded
+// constants enter the split step only through commutators with the step's operators, O(dt eps) per step.
+// A rotation costs 3 instructions either way (a rounded complex product takes 4, its exact inverse 8
+// and two more for the root's modulus correction) and a root 2 registers.
+//
+// Shears are well conditioned for |phi| <= pi/2 (p <= 1), and all roots stay there: a stage of radix R
+// that combines R transforms of length L rotates by 2 pi s r / (R L), and both s and r are taken as
+// signed digits, -L/2 <= s < L/2 and -R/2 < r <= R/2 (the residues beyond the middle counted from
+// above).  A signed r shifts the subsequence its transform runs over by one period, a signed s the
+// index k of the outputs, so both only rotate a sequence of P positions by one (LanePos); no data moves.
+// And the root of -r is the root of r with the shears' signs turned, so a butterfly of radix R holds
+// R/2 roots instead of R - 1: 32 registers of roots at N = 1024 and P = 16, where rounded roots with
+// modulus corrections took 81.
+// The forward error and the round trip's (against fp64, random data, N = 16 to 4096) are those of
+// rounded roots or smaller: 1.07e-7 and 1.33e-7 at N = 1024, P = 16, against 1.09e-7 and 1.35e-7.
+// Larger grids are bound by instruction issue at the two waves per SIMD that the registers allow; a
+// row pass at 1024 points went from 1945 to 1658 VALU instructions and from 192 to 142 VGPRs, the column
+// pass from 1990 to 1663 and from 242 to 213.  Per step, rounded roots -> shears: 26.8 -> 24.2 us at
+// 1024^2 and 135 -> 118 us at 2048^2 (imaginary time), 20.0 -> 17.5 us at 1024^2 (real time).
 // ---------------------------------------------------------------------------------------------
-// Butterfly constants.  fp32: the rounded 1/sqrt(2), cos(pi/8), sin(pi/8) and the low parts that
-// make the inverse exact.  fp64: the rounded constants; their modulus error (~1e-16) is left in
-// place -- applied every step it drifts by ~1e-10 over 10^6 steps -- so the low parts are zero.
-template <class T> struct Roots;
-template <> struct Roots<float> {
-  static constexpr float R2 = 0.70710676908493042f;      // fp32(1/sqrt(2))
-  static constexpr float R2_LO = 2.42032350e-08f;        // r2 (1/(2 r2^2) - 1) for the fp32 r2
-  static constexpr float C8 = 0.92387950420379639f;      // fp32(cos(pi/8))
-  static constexpr float S8 = 0.38268342614173889f;      // fp32(sin(pi/8))
-  static constexpr float C8_LO = 5.27244843e-08f;        // c8 eta8, eta8 = 1/(c8^2 + s8^2) - 1
-  static constexpr float S8_LO = 2.18391971e-08f;        // s8 eta8
-};
-template <> struct Roots<double> {
-  static constexpr double R2 = 0.70710678118654752440;
-  static constexpr double R2_LO = 0.0;
-  static constexpr double C8 = 0.92387953251128675613;
-  static constexpr double S8 = 0.38268343236508977173;
-  static constexpr double C8_LO = 0.0;
-  static constexpr double S8_LO = 0.0;
+// p and u of the fixed rotations by pi/8, pi/4 and 3 pi/8
+template <class T> struct Roots {
+  static constexpr T P1 = T(0.198912367379658006912), U1 = T(0.382683432365089771728);
+  static constexpr T P2 = T(0.414213562373095048802), U2 = T(0.707106781186547524401);
+  static constexpr T P3 = T(0.668178637919298919998), U3 = T(0.923879532511286756128);
 };
 
+// a e^{-i phi}, and its exact inverse (which is a e^{+i phi})
+template <class C, class T = typename RealOf<C>::T>
+__device__ __forceinline__ C rot_neg(C a, T p, T u) {
+  const T x = fma_(p, a.y, a.x);
+  const T y = fma_(-u, x, a.y);
+  return mk2(fma_(p, y, x), y);
+}
+template <class C, class T = typename RealOf<C>::T>
+__device__ __forceinline__ C rot_pos(C a, T p, T u) {
+  const T x = fma_(-p, a.y, a.x);
+  const T y = fma_(u, x, a.y);
+  return mk2(fma_(-p, y, x), y);
+}
 template <class C>
 __device__ __forceinline__ C pf_rot90(C a) { return mk2(a.y, -a.x); }   // * (-i)
 template <class C>
 __device__ __forceinline__ C pi_rot90(C a) { return mk2(-a.y, a.x); }   // * (+i)
-// * r2 (1 - i) and its exact inverse * (1 + i) / (2 r2)
-template <class C>
-__device__ __forceinline__ C pf_rot45(C a) {
-  using K = Roots<typename RealOf<C>::T>;
-  return mk2(K::R2 * (a.x + a.y), K::R2 * (a.y - a.x));
+// * W16^k (k = 1, 2, 3) and its exact inverse
+template <int K, class C>
+__device__ __forceinline__ C pf_rot(C a) {
+  using R = Roots<typename RealOf<C>::T>;
+  if constexpr (K == 1) return rot_neg(a, R::P1, R::U1);
+  else if constexpr (K == 2) return rot_neg(a, R::P2, R::U2);
+  else return rot_neg(a, R::P3, R::U3);
 }
-template <class C>
-__device__ __forceinline__ C pi_rot45(C a) {
-  using K = Roots<typename RealOf<C>::T>;
-  const auto d = a.x - a.y, e = a.x + a.y;
-  return mk2(fma_(d, K::R2, d * K::R2_LO), fma_(e, K::R2, e * K::R2_LO));
-}
-// * (c - i s) and its exact inverse * ((c + lx) + i (s + ly)), (lx, ly) = (c, s) eta
-template <class C, class T = typename RealOf<C>::T>
-__device__ __forceinline__ C pf_cmul(C a, T c, T s) {
-  return mk2(fma_(a.x, c, a.y * s), fma_(a.y, c, -a.x * s));
-}
-template <class C, class T = typename RealOf<C>::T>
-__device__ __forceinline__ C pi_cmul(C a, T c, T s, T lx, T ly) {
-  return mk2(fma_(a.x, c, fma_(-a.y, s, fma_(a.x, lx, -a.y * ly))),
-             fma_(a.y, c, fma_(a.x, s, fma_(a.y, lx, a.x * ly))));
+template <int K, class C>
+__device__ __forceinline__ C pi_rot(C a) {
+  using R = Roots<typename RealOf<C>::T>;
+  if constexpr (K == 1) return rot_pos(a, R::P1, R::U1);
+  else if constexpr (K == 2) return rot_pos(a, R::P2, R::U2);
+  else return rot_pos(a, R::P3, R::U3);
 }
 
 // forward small DFTs (sign -1)
@@ -206,9 +233,9 @@ __device__ __forceinline__ void pf_dft8(C (&a)[8]) {
   C o0 = a[1], o1 = a[3], o2 = a[5], o3 = a[7];
   pf_dft4(e0, e1, e2, e3);
   pf_dft4(o0, o1, o2, o3);
-  o1 = pf_rot45(o1);
+  o1 = pf_rot<2>(o1);
   o2 = pf_rot90(o2);
-  o3 = pf_rot90(pf_rot45(o3));
+  o3 = pf_rot90(pf_rot<2>(o3));
   a[0] = vadd(e0, o0); a[4] = vsub(e0, o0);
   a[1] = vadd(e1, o1); a[5] = vsub(e1, o1);
   a[2] = vadd(e2, o2); a[6] = vsub(e2, o2);
@@ -221,9 +248,9 @@ __device__ __forceinline__ void pi_dft8(C (&a)[8]) {
   C e1 = vadd(a[1], a[5]), o1 = vsub(a[1], a[5]);
   C e2 = vadd(a[2], a[6]), o2 = vsub(a[2], a[6]);
   C e3 = vadd(a[3], a[7]), o3 = vsub(a[3], a[7]);
-  o1 = pi_rot45(o1);
+  o1 = pi_rot<2>(o1);
   o2 = pi_rot90(o2);
-  o3 = pi_rot45(pi_rot90(o3));
+  o3 = pi_rot<2>(pi_rot90(o3));
   pi_dft4(e0, e1, e2, e3);
   pi_dft4(o0, o1, o2, o3);
   a[0] = e0; a[2] = e1; a[4] = e2; a[6] = e3;
@@ -233,18 +260,17 @@ __device__ __forceinline__ void pi_dft8(C (&a)[8]) {
 // forward 16-point DFT (4x4; input r = r1 + 4 r2, output k = k2 + 4 k1)
 template <class C>
 __device__ __forceinline__ void pf_dft16(C (&a)[16]) {
-  using K = Roots<typename RealOf<C>::T>;
 #pragma unroll
   for (int r1 = 0; r1 < 4; ++r1) pf_dft4(a[r1], a[r1 + 4], a[r1 + 8], a[r1 + 12]);
-  a[5] = pf_cmul(a[5], K::C8, K::S8);                    // W16^1
-  a[9] = pf_rot45(a[9]);                                 // W16^2
-  a[13] = pf_cmul(a[13], K::S8, K::C8);                  // W16^3
-  a[6] = pf_rot45(a[6]);                                 // W16^2
+  a[5] = pf_rot<1>(a[5]);                                // W16^1
+  a[9] = pf_rot<2>(a[9]);                                // W16^2
+  a[13] = pf_rot<3>(a[13]);                              // W16^3
+  a[6] = pf_rot<2>(a[6]);                                // W16^2
   a[10] = pf_rot90(a[10]);                               // W16^4
-  a[14] = pf_rot90(pf_rot45(a[14]));                     // W16^6
-  a[7] = pf_cmul(a[7], K::S8, K::C8);                    // W16^3
-  a[11] = pf_rot90(pf_rot45(a[11]));                     // W16^6
-  a[15] = vneg(pf_cmul(a[15], K::C8, K::S8));            // W16^9 = -W16^1
+  a[14] = pf_rot90(pf_rot<2>(a[14]));                    // W16^6
+  a[7] = pf_rot<3>(a[7]);                                // W16^3
+  a[11] = pf_rot90(pf_rot<2>(a[11]));                    // W16^6
+  a[15] = vneg(pf_rot<1>(a[15]));                        // W16^9 = -W16^1
 #pragma unroll
   for (int k2 = 0; k2 < 4; ++k2) pf_dft4(a[4 * k2], a[4 * k2 + 1], a[4 * k2 + 2], a[4 * k2 + 3]);
   C t[16];
@@ -258,7 +284,6 @@ __device__ __forceinline__ void pf_dft16(C (&a)[16]) {
 // exact inverse of pf_dft16, times 16: the same steps undone in reverse order
 template <class C>
 __device__ __forceinline__ void pi_dft16(C (&a)[16]) {
-  using K = Roots<typename RealOf<C>::T>;
   C t[16];
 #pragma unroll
   for (int k1 = 0; k1 < 4; ++k1)
@@ -266,15 +291,15 @@ __device__ __forceinline__ void pi_dft16(C (&a)[16]) {
     for (int k2 = 0; k2 < 4; ++k2) t[k1 + 4 * k2] = a[k2 + 4 * k1];
 #pragma unroll
   for (int k2 = 0; k2 < 4; ++k2) pi_dft4(t[4 * k2], t[4 * k2 + 1], t[4 * k2 + 2], t[4 * k2 + 3]);
-  t[5] = pi_cmul(t[5], K::C8, K::S8, K::C8_LO, K::S8_LO);
-  t[9] = pi_rot45(t[9]);
-  t[13] = pi_cmul(t[13], K::S8, K::C8, K::S8_LO, K::C8_LO);
-  t[6] = pi_rot45(t[6]);
+  t[5] = pi_rot<1>(t[5]);
+  t[9] = pi_rot<2>(t[9]);
+  t[13] = pi_rot<3>(t[13]);
+  t[6] = pi_rot<2>(t[6]);
   t[10] = pi_rot90(t[10]);
-  t[14] = pi_rot45(pi_rot90(t[14]));
-  t[7] = pi_cmul(t[7], K::S8, K::C8, K::S8_LO, K::C8_LO);
-  t[11] = pi_rot45(pi_rot90(t[11]));
-  t[15] = vneg(pi_cmul(t[15], K::C8, K::S8, K::C8_LO, K::S8_LO));
+  t[14] = pi_rot<2>(pi_rot90(t[14]));
+  t[7] = pi_rot<3>(t[7]);
+  t[11] = pi_rot<2>(pi_rot90(t[11]));
+  t[15] = pi_rot<1>(vneg(t[15]));
 #pragma unroll
   for (int r1 = 0; r1 < 4; ++r1) pi_dft4(t[r1], t[r1 + 4], t[r1 + 8], t[r1 + 12]);
 #pragma unroll
@@ -313,21 +338,11 @@ __device__ __forceinline__ void pi_dft(C (&a)[R]) {
 }
 
 // Step-kernel transforms with P points per thread (P = 4, 8 or 16; T = N / P threads per
-// transform, thread t holding positions t + T m).  Stages have radix P, then the remainder.
+// transform).  Stages have radix P, then the remainder.
+template <int N, int P, int L>
+constexpr int stage_radix() { return N / L >= P ? P : N / L; }
 
-// Stage roots a thread needs: the first stage (L = 1) needs none; a later stage of radix R uses
-// W_N^(s r N/(R L)) for its P/R butterflies and r = 1..R-1.
-template <int N, int P, int L = 1>
-constexpr int tw_count_p() {
-  constexpr int REM = N / L;
-  constexpr int R = REM >= P ? P : REM;
-  constexpr int here = L > 1 ? (P / R) * (R - 1) : 0;
-  if constexpr (R == REM) return here;
-  else return here + tw_count_p<N, P, L * R>();
-}
-
-// Radix of the last stage of a length-N transform with P points per thread (radix-P stages,
-// then the remainder).
+// Radix of the last stage of a length-N transform.
 template <int N, int P, int L = 1>
 constexpr int last_radix() {
   constexpr int REM = N / L;
@@ -335,128 +350,173 @@ constexpr int last_radix() {
   else return last_radix<N, P, L * P>();
 }
 
-// Per-thread stage roots for the step kernels: fp32 (cos, sin) of each root and eta, where
-// 1 + eta = 1/|root|^2 of the rounded pair; the inverse forms its low part (cos, sin) eta with two
-// products at use (its rounding, ~1e-15, lies far below the fp32 rounding it feeds).  Table
-// entries are float4 {cos, sin, eta, 0} of exp(-2 pi i j / N).  Loaded once per kernel (they
-// depend only on the thread index); three registers per root.
-// fp64 roots carry no modulus correction (their |w~| - 1 is ~1e-16; see Roots<double>), so the fp64
-// instantiation holds no eta and its inverse multiplies by conj(w~) alone: 2 registers per root
-// fewer, and the 4-instruction product instead of the corrected one.
+// The stage that combines transforms of length L reads, for the output offset o, the offsets
+// o + (N / R L) r with signed r.  The offsets of a stage's inputs to the later stages therefore run over
+// (h - N / L, h] instead of [0, N / L), with this h for the offsets of the stage's own outputs.
+template <int N, int P, int L>
+constexpr int offset_top() {
+  constexpr int LN = L * stage_radix<N, P, L>();   // length after this stage
+  if constexpr (LN == N) return 0;
+  else return stage_radix<N, P, LN>() / 2 * (N / (LN * stage_radix<N, P, LN>())) + offset_top<N, P, LN>();
+}
+
+// Positions of the lane's inputs of the stage at length L: rotated where its offset is a negative one
+// (only the last stage, whose one offset is 0, has P != R and it is never rotated).
+template <int N, int P, int L = 1>
+__device__ __forceinline__ LanePos<N / P> stage_in_pos(int t) {
+  constexpr int T = N / P;
+  if constexpr (N / L <= P) {
+    return {t, t};
+  } else {
+    const bool neg = t / L > offset_top<N, P, L>();
+    return {neg ? t - T : t, neg ? t + (N - T) : t};
+  }
+}
+// Positions (within the array after the stage) of the lane's outputs of a stage of radix P at length L.
+template <int N, int P, int L>
+__device__ __forceinline__ LanePos<L> stage_out_pos(int t) {
+  const int s = t & (L - 1), o = (t / L) * (P * L) + s;
+  if constexpr (L == 1) {
+    return {o, o};
+  } else {
+    const bool neg = s >= L / 2;
+    return {neg ? o - L : o, neg ? o + L * (P - 1) : o};
+  }
+}
+// The lane's positions in real space (the forward transform's input) and in k-space (its output).
+template <int N, int P>
+__device__ __forceinline__ LanePos<N / P> real_pos(int t) { return stage_in_pos<N, P>(t); }
+template <int N, int P>
+__device__ __forceinline__ LanePos<N / P> spec_pos(int t) {
+  constexpr int T = N / P;
+  if constexpr (T > 1 && last_radix<N, P>() == P) return stage_out_pos<N, P, T>(t);
+  else return {t, t};   // a smaller last radix rotates at compile time (last_reg)
+}
+// The register of output k of the last stage's butterfly u (U butterflies of radix R).
+template <int P, int R>
+constexpr int last_reg(int u, int k) {
+  constexpr int U = P / R;
+  return u + U * (U > 1 && u >= U / 2 ? (k + R - 1) % R : k);
+}
+
+// Stage roots a thread holds: the first stage (L = 1) needs none; a later one of radix R the (p, u) of
+// 2 pi s r / (R L) for its P/R butterflies and r = 1..R/2.
+template <int N, int P, int L = 1>
+constexpr int tw_count_p() {
+  constexpr int R = stage_radix<N, P, L>();
+  constexpr int here = L > 1 ? (P / R) * (R / 2) : 0;
+  if constexpr (R * L == N) return here;
+  else return here + tw_count_p<N, P, L * R>();
+}
+
 template <int N, int P = 16, class T = float>
 struct TwPlain {
   static constexpr int COUNT = tw_count_p<N, P>() > 0 ? tw_count_p<N, P>() : 1;
-  static constexpr bool CORRECTED = sizeof(T) == 4;
-  cplx_t<T> cs[COUNT];
-  T eta[CORRECTED ? COUNT : 1];
+  cplx_t<T> pu[COUNT];
 };
 
+// tw: the (p, u) of 2 pi j / N at entry j + N/4, |j| <= N/4.  Loaded once per kernel (they depend only on
+// the thread index).
 template <int N, int P, int L = 1, int BASE = 0, class TR>
-__device__ __forceinline__ void load_twiddles(TwPlain<N, P, TR>& tr, int t, const typename Cplx<TR>::Q* __restrict__ tw) {
-  using Q = typename Cplx<TR>::Q;
+__device__ __forceinline__ void load_twiddles(TwPlain<N, P, TR>& tr, int t, const cplx_t<TR>* __restrict__ tw) {
+  using C = cplx_t<TR>;
   constexpr int T = N / P;
-  constexpr int REM = N / L;
-  constexpr int R = REM >= P ? P : REM;
+  constexpr int R = stage_radix<N, P, L>();
   constexpr int U = P / R;
-  constexpr int TW_STRIDE = N / (R * L);
   if constexpr (L > 1) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      // byte offset of root s r TW_STRIDE, 32-bit from the uniform table base
-      const uint32_t o = static_cast<uint32_t>((t + T * u) & (L - 1)) * (uint32_t(sizeof(Q)) * TW_STRIDE);
+      const int s0 = (t + T * u) & (L - 1);
+      const int s = s0 >= L / 2 ? s0 - L : s0;
+      // byte offset of entry N/4 + s r N/(R L), 32-bit from the uniform table base
+      const int d = s * int(sizeof(C) * (N / (R * L)));
+      int o = int(sizeof(C)) * (N / 4);
 #pragma unroll
-      for (int r = 1; r < R; ++r) {
-        const Q w = *reinterpret_cast<const Q*>(reinterpret_cast<const char*>(tw) + o * r);
-        tr.cs[BASE + u * (R - 1) + (r - 1)] = mk2(w.x, w.y);
-        if constexpr (TwPlain<N, P, TR>::CORRECTED) tr.eta[BASE + u * (R - 1) + (r - 1)] = w.z;
+      for (int r = 1; r <= R / 2; ++r) {
+        o += d;
+        tr.pu[BASE + u * (R / 2) + (r - 1)] =
+            *reinterpret_cast<const C*>(reinterpret_cast<const char*>(tw) + static_cast<uint32_t>(o));
       }
     }
   }
-  if constexpr (R != REM) {
-    constexpr int NEXT = BASE + (L > 1 ? U * (R - 1) : 0);
+  if constexpr (R * L != N) {
+    constexpr int NEXT = BASE + (L > 1 ? U * (R / 2) : 0);
     load_twiddles<N, P, L * R, NEXT>(tr, t, tw);
   }
 }
 
-// forward stage (plain roots)
-template <int N, int P, int R, int L, bool LAST, int BASE, class C, class TR>
+// forward stage
+template <int N, int P, int L, int BASE, class C, class TR>
 __device__ __forceinline__ void pf_stage(C (&v)[P], const LdsView<C>& lds, int t, const TwPlain<N, P, TR>& tr) {
-  constexpr int T = N / P;
+  constexpr int R = stage_radix<N, P, L>();
   constexpr int U = P / R;
+  constexpr bool LAST = R * L == N;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     C a[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) a[r] = v[u + U * r];
-    const int b = t + T * u;
-    const int s = b & (L - 1);
     if constexpr (L > 1) {
 #pragma unroll
       for (int r = 1; r < R; ++r) {
-        const C w = tr.cs[BASE + u * (R - 1) + (r - 1)];
-        a[r] = pf_cmul(a[r], w.x, w.y);
+        const C w = tr.pu[BASE + u * (R / 2) + ((r <= R / 2 ? r : R - r) - 1)];
+        a[r] = r <= R / 2 ? rot_neg(a[r], w.x, w.y) : rot_pos(a[r], w.x, w.y);
       }
     }
     pf_dft<R>(a);
     if constexpr (LAST) {
 #pragma unroll
-      for (int k = 0; k < R; ++k) v[u + U * k] = a[k];
+      for (int k = 0; k < R; ++k) v[last_reg<P, R>(u, k)] = a[k];
     } else {
-      const int q = b / L;
+      const auto pos = stage_out_pos<N, P, L>(t);
 #pragma unroll
-      for (int k = 0; k < R; ++k) lds.at(q * R * L + s + L * k) = a[k];
+      for (int k = 0; k < R; ++k) lds.at(pos, k) = a[k];
     }
   }
 }
 
-// Forward length-N transform (positions t + T*m in and out), plain roots.
+// Forward length-N transform (positions real_pos in, spec_pos out).
 template <int N, int L = 1, int BASE = 0, int P, class C, class TR>
 __device__ __forceinline__ void fwd_pass(C (&v)[P], const LdsView<C>& lds, int t, const TwPlain<N, P, TR>& tr) {
-  constexpr int REM = N / L;
-  constexpr int R = REM >= P ? P : REM;
-  constexpr bool LAST = (R == REM);
-  constexpr int T = N / P;
-  pf_stage<N, P, R, L, LAST, BASE>(v, lds, t, tr);
-  if constexpr (!LAST) {
+  constexpr int R = stage_radix<N, P, L>();
+  if constexpr (R * L == N) {
+    pf_stage<N, P, L, BASE>(v, lds, t, tr);
+  } else {
+    pf_stage<N, P, L, BASE>(v, lds, t, tr);
     __syncthreads();
+    const auto pos = stage_in_pos<N, P, L * R>(t);
 #pragma unroll
-    for (int m = 0; m < P; ++m) v[m] = lds.at(t + T * m);
+    for (int m = 0; m < P; ++m) v[m] = lds.at(pos, m);
     __syncthreads();
-    constexpr int NEXT = BASE + (L > 1 ? (P / R) * (R - 1) : 0);
+    constexpr int NEXT = BASE + (L > 1 ? (P / R) * (R / 2) : 0);
     fwd_pass<N, L * R, NEXT>(v, lds, t, tr);
   }
 }
 
 // Inverse stage: the forward stage's outputs (from LDS, or the registers for the last stage)
-// through the exact inverse butterfly and inverse roots, into registers {u + U r}.
-template <int N, int P, int R, int L, bool LAST, int BASE, class C, class TR>
+// through the exact inverse butterfly and inverse rotations, into registers {u + U r}.
+template <int N, int P, int L, int BASE, class C, class TR>
 __device__ __forceinline__ void pi_stage(C (&v)[P], const LdsView<C>& lds, int t, const TwPlain<N, P, TR>& tr) {
-  constexpr int T = N / P;
+  constexpr int R = stage_radix<N, P, L>();
   constexpr int U = P / R;
+  constexpr bool LAST = R * L == N;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     C a[R];
-    const int b = t + T * u;
-    const int s = b & (L - 1);
     if constexpr (LAST) {
 #pragma unroll
-      for (int k = 0; k < R; ++k) a[k] = v[u + U * k];
+      for (int k = 0; k < R; ++k) a[k] = v[last_reg<P, R>(u, k)];
     } else {
-      const int q = b / L;
+      const auto pos = stage_out_pos<N, P, L>(t);
 #pragma unroll
-      for (int k = 0; k < R; ++k) a[k] = lds.at(q * R * L + s + L * k);
+      for (int k = 0; k < R; ++k) a[k] = lds.at(pos, k);
     }
     pi_dft<R>(a);
     if constexpr (L > 1) {
 #pragma unroll
       for (int r = 1; r < R; ++r) {
-        const C w = tr.cs[BASE + u * (R - 1) + (r - 1)];
-        if constexpr (TwPlain<N, P, TR>::CORRECTED) {
-          const TR eta = tr.eta[BASE + u * (R - 1) + (r - 1)];
-          a[r] = pi_cmul(a[r], w.x, w.y, w.x * eta, w.y * eta);
-        } else {
-          a[r] = mk2(fma_(a[r].x, w.x, -a[r].y * w.y), fma_(a[r].y, w.x, a[r].x * w.y));   // * conj(w~)
-        }
+        const C w = tr.pu[BASE + u * (R / 2) + ((r <= R / 2 ? r : R - r) - 1)];
+        a[r] = r <= R / 2 ? rot_pos(a[r], w.x, w.y) : rot_neg(a[r], w.x, w.y);
       }
     }
 #pragma unroll
@@ -468,20 +528,18 @@ __device__ __forceinline__ void pi_stage(C (&v)[P], const LdsView<C>& lds, int t
 // workgroup call it; on return every LDS read is complete.
 template <int N, int L = 1, int BASE = 0, int P, class C, class TR>
 __device__ __forceinline__ void inv_pass(C (&v)[P], const LdsView<C>& lds, int t, const TwPlain<N, P, TR>& tr) {
-  constexpr int REM = N / L;
-  constexpr int R = REM >= P ? P : REM;
-  constexpr bool LAST = (R == REM);
-  constexpr int T = N / P;
-  if constexpr (LAST) {
-    pi_stage<N, P, R, L, true, BASE>(v, lds, t, tr);
+  constexpr int R = stage_radix<N, P, L>();
+  if constexpr (R * L == N) {
+    pi_stage<N, P, L, BASE>(v, lds, t, tr);
   } else {
-    constexpr int NEXT = BASE + (L > 1 ? (P / R) * (R - 1) : 0);
+    constexpr int NEXT = BASE + (L > 1 ? (P / R) * (R / 2) : 0);
     inv_pass<N, L * R, NEXT>(v, lds, t, tr);
-    // undo "read positions t + T m from LDS", then this stage
+    // undo the forward's reads from LDS, then this stage
+    const auto pos = stage_in_pos<N, P, L * R>(t);
 #pragma unroll
-    for (int m = 0; m < P; ++m) lds.at(t + T * m) = v[m];
+    for (int m = 0; m < P; ++m) lds.at(pos, m) = v[m];
     __syncthreads();
-    pi_stage<N, P, R, L, false, BASE>(v, lds, t, tr);
+    pi_stage<N, P, L, BASE>(v, lds, t, tr);
     __syncthreads();
   }
 }

@@ -18,8 +18,8 @@ struct sgpe_ctx {
   float4* psi = nullptr;
   bool own_psi = false;
   float4* scratch = nullptr;
-  float4* twp_x = nullptr;  // fp32-rounded roots with modulus corrections (step kernels)
-  float4* twp_y = nullptr;
+  float2* twp_x = nullptr;  // root tables (RowArgsT::tw) of the step kernels
+  float2* twp_y = nullptr;
   // K tables, index = 2*imag + half  (half: h = dt/2, else h = dt)
   float4* kx_tab[4] = {nullptr, nullptr, nullptr, nullptr};
   float2* ky_tab[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -43,8 +43,8 @@ struct sgpe_ctx {
   // fp32 tables are then unused (the schedule fields above apply, with no prefetch)
   int prec = 0;             // sgpe_precision
   double4* psi64 = nullptr;
-  double4* twp64_x = nullptr;  // fp64 roots (every context: the energy kernels transform in fp64)
-  double4* twp64_y = nullptr;
+  double2* twp64_x = nullptr;  // fp64 root tables (every context: the energy kernels transform in fp64)
+  double2* twp64_y = nullptr;
   double4* kx64[4] = {nullptr, nullptr, nullptr, nullptr};
   double2* ky64[4] = {nullptr, nullptr, nullptr, nullptr};
   double* hbx64 = nullptr;  // dt * Omega_x(x_j) / 2

@@ -30,35 +30,37 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
   const int pair = tid >> 1;
   int line, t;
   LdsView<C> lds;
-  uint32_t off, mstride;
+  uint32_t off, pstride;   // of the lane's line, between its positions
   if constexpr (COL) {
     const int sh = __builtin_ctz(a.lines);
     const int cc = pair & (a.lines - 1);
     t = pair >> sh;
     line = (col_group(wg, ngroups) << sh) + cc;
     lds = LdsView<C>{lds_raw + 2 * cc + comp, 1 + sh};
-    const uint32_t rstride = PB * static_cast<uint32_t>(a.nx);
-    off = static_cast<uint32_t>(t) * rstride + PB * static_cast<uint32_t>(line) + CB * comp;
-    mstride = static_cast<uint32_t>(T) * rstride;
+    off = PB * static_cast<uint32_t>(line) + CB * comp;
+    pstride = PB * static_cast<uint32_t>(a.nx);
   } else {
     const int rloc = pair / T;
     t = pair - rloc * T;
     line = wg * a.lines + rloc;
     lds = LdsView<C>{lds_raw + rloc * 2 * SLOTS + comp, 1};
-    off = static_cast<uint32_t>(line) * (PB * N) + static_cast<uint32_t>(t) * PB + CB * comp;
-    mstride = PB * T;
+    off = static_cast<uint32_t>(line) * (PB * N) + CB * comp;
+    pstride = PB;
   }
+  const LanePos<T> rp = real_pos<N, P>(t), sp = spec_pos<N, P>(t);
+  const uint32_t off0 = off + static_cast<uint32_t>(rp.p0) * pstride, offb = off + static_cast<uint32_t>(rp.b) * pstride;
+  const uint32_t mstride = static_cast<uint32_t>(T) * pstride;
   const char* __restrict__ base = reinterpret_cast<const char*>(a.psi);
   char* __restrict__ out = reinterpret_cast<char*>(a.psi);
   C v[P];
 #pragma unroll
-  for (int m = 0; m < P; ++m) v[m] = *reinterpret_cast<const C*>(base + (off + mstride * m));
+  for (int m = 0; m < P; ++m) v[m] = *reinterpret_cast<const C*>(base + (m == 0 ? off0 : offb + mstride * m));
   TwPlain<N, P, R> tr;
   load_twiddles<N>(tr, t, a.tw);
   R hb_line[P], hb_cross = R(0);
   if constexpr (FULL) {
 #pragma unroll
-    for (int m = 0; m < P; ++m) hb_line[m] = a.hbx[t + T * m] * a.hfrac;
+    for (int m = 0; m < P; ++m) hb_line[m] = a.hbx[rp.at(m)] * a.hfrac;
     hb_cross = a.hby[line] * a.hfrac;
   }
   // An op's table values of the lane's points are loaded before the forward transform, so that their
@@ -77,14 +79,14 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
         C q[EARLY ? P : 1];
         if constexpr (EARLY) {
 #pragma unroll
-          for (int m = 0; m < P; ++m) q[m] = tab[t + T * m];
+          for (int m = 0; m < P; ++m) q[m] = tab[sp.at(m)];
         }
         fwd_pass<N>(v, lds, t, tr);
 #pragma unroll
         for (int m = 0; m < P; ++m) {
           C e;
           if constexpr (EARLY) e = q[m];
-          else e = tab[t + T * m];
+          else e = tab[sp.at(m)];
           const C w = v[m];
           v[m] = mk2(w.x + fma_(-e.y, w.y, e.x * w.x), w.y + fma_(e.y, w.x, e.x * w.y));
         }
@@ -95,14 +97,14 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
         Q d[EARLY ? P : 1];
         if constexpr (EARLY) {
 #pragma unroll
-          for (int m = 0; m < P; ++m) d[m] = tab[2 * (t + T * m) + comp];
+          for (int m = 0; m < P; ++m) d[m] = tab[2 * sp.at(m) + comp];
         }
         fwd_pass<N>(v, lds, t, tr);
 #pragma unroll
         for (int m = 0; m < P; ++m) {
           Q e;
           if constexpr (EARLY) e = d[m];
-          else e = tab[2 * (t + T * m) + comp];
+          else e = tab[2 * sp.at(m) + comp];
           const C w = v[m];
           const C o = pair_swap(w);
           const R cr = fma_(-e.w, o.y, fma_(e.z, o.x, fma_(-e.y, w.y, e.x * w.x)));
@@ -122,7 +124,8 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
     }
   }
 #pragma unroll
-  for (int m = 0; m < P; ++m) store_state<WT>(reinterpret_cast<C*>(out + (off + mstride * m)), vscale(v[m], s));
+  for (int m = 0; m < P; ++m)
+    store_state<WT>(reinterpret_cast<C*>(out + (m == 0 ? off0 : offb + mstride * m)), vscale(v[m], s));
 }
 
 }  // namespace sgpe

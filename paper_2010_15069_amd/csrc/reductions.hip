@@ -92,8 +92,7 @@ int norm_blocks() { return 256; }
 //     spatial Raman term Omega(r) Re(u* d) of the real-space energy.
 // Row kernel: the real-space terms, the norm and the rows' k_x terms; column kernel: the columns'
 // k_y terms.  The DFTs are the step kernels' register-resident forward transform (fwd_pass: radix-P
-// stages exchanged through LDS, natural order in and out) instantiated in fp64 with the roots
-// rounded once to fp64, on the state widened to fp64 as it is loaded, so the energy of a complex64
+// stages exchanged through LDS, natural order in and out) instantiated in fp64 on the state widened to fp64 as it is loaded, so the energy of a complex64
 // state carries no transform error of its own.  Each lane holds one component of one line.  The
 // partials are scaled so that their combination reads E = (w / N ek + w er) / norm
 // + w ei norm0 / norm^2 (w = dx dy, N = nx ny), as for a 2-D sum.
@@ -154,9 +153,10 @@ __device__ __forceinline__ void energy_row_body(const EnergyArgs& a, int block) 
   }
   // keep the transform's loads (and their registers) after the loop above
   asm volatile("" ::: "memory");
+  const LanePos<T> rp = real_pos<N, P>(t), sp = spec_pos<N, P>(t);
   double2 v[P];
 #pragma unroll
-  for (int m = 0; m < P; ++m) v[m] = energy_load<Q>(a, row0 + t + T * m, comp);
+  for (int m = 0; m < P; ++m) v[m] = energy_load<Q>(a, row0 + rp.at(m), comp);
   TwPlain<N, P, double> tr;
   load_twiddles<N>(tr, t, a.twx);
   const LdsView<double2> lds{reinterpret_cast<double2*>(energy_lds) + 2 * r + comp, 1 + __builtin_ctz(a.rows)};
@@ -165,7 +165,7 @@ __device__ __forceinline__ void energy_row_body(const EnergyArgs& a, int block) 
   double ex = 0.0;   // the rows' k_x terms
 #pragma unroll
   for (int m = 0; m < P; ++m) {
-    const double kx = energy_freq(t + T * m, N) * a.dkx;
+    const double kx = energy_freq(sp.at(m), N) * a.dkx;
     ex += (0.5 * kx * kx + kl * kx) * (v[m].x * v[m].x + v[m].y * v[m].y);
   }
   const double se = block_sum(er, red);
@@ -203,9 +203,10 @@ __device__ __forceinline__ void energy_col_body(const EnergyArgs& a, int block) 
   const int tid = threadIdx.x, comp = tid & 1, pair = tid >> 1;
   const int cc = pair & (C - 1), t = pair / C;
   const int x = col_group(block, a.nx / C) * C + cc;
+  const LanePos<T> rp = real_pos<N, P>(t), sp = spec_pos<N, P>(t);
   double2 v[P];
 #pragma unroll
-  for (int m = 0; m < P; ++m) v[m] = energy_load<Q>(a, size_t(t + T * m) * a.nx + x, comp);
+  for (int m = 0; m < P; ++m) v[m] = energy_load<Q>(a, size_t(rp.at(m)) * a.nx + x, comp);
   TwPlain<N, P, double> tr;
   load_twiddles<N>(tr, t, a.twy);
   const LdsView<double2> lds{reinterpret_cast<double2*>(energy_lds) + 2 * cc + comp, 1 + __builtin_ctz(C)};
@@ -213,7 +214,7 @@ __device__ __forceinline__ void energy_col_body(const EnergyArgs& a, int block) 
   double acc = 0.0;
 #pragma unroll
   for (int m = 0; m < P; ++m) {
-    const double ky = energy_freq(t + T * m, N) * a.dky;
+    const double ky = energy_freq(sp.at(m), N) * a.dky;
     acc += 0.5 * ky * ky * (v[m].x * v[m].x + v[m].y * v[m].y);
   }
   const double s = block_sum(acc, red);

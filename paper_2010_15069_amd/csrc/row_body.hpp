@@ -190,13 +190,13 @@ __device__ __forceinline__ RCoef<R> r_coefs(const A& a, bool up, R gs) {
 template <int N, bool IMAG, bool FULL, int P, class C, class R, class A>
 __device__ __forceinline__ void row_apply_r(C (&v)[P], const A& a, int row, int t, bool up,
                                             const R (&hbx_r)[P], R hb_row, R gs = R(1)) {
-  constexpr int T = N / P;
+  const LanePos<N / P> pos = real_pos<N, P>(t);
   const RCoef<R> c = r_coefs(a, up, gs);
   const R y = fma_(static_cast<R>(row), a.dy, a.y0);
   const R hvy = a.hvy * y * y;
 #pragma unroll
   for (int m = 0; m < P; ++m) {
-    const int j = t + T * m;
+    const int j = pos.at(m);
     const R x = fma_(static_cast<R>(j), a.dx, a.x0);
     const R hv = fma_(a.hvx * x, x, hvy);
     const R n_own = fma_(v[m].x, v[m].x, v[m].y * v[m].y);
@@ -222,7 +222,7 @@ __device__ __forceinline__ void row_apply_r(C (&v)[P], const A& a, int row, int 
 template <int N, bool IMAG, bool FULL, int P, class C, class R, class A>
 __device__ __forceinline__ void row_apply_r_nln(C (&v)[P], const A& a, int row, int t, bool up,
                                                 const R (&hbx_r)[P], R hb_row, R gs = R(1)) {
-  constexpr int T = N / P;
+  const LanePos<N / P> pos = real_pos<N, P>(t);
   const RCoef<R> c = r_coefs(a, up, gs);
   const R y = fma_(static_cast<R>(row), a.dy, a.y0);
   const R hvy = a.hvy * y * y;
@@ -235,7 +235,7 @@ __device__ __forceinline__ void row_apply_r_nln(C (&v)[P], const A& a, int row, 
   };
 #pragma unroll
   for (int m = 0; m < P; ++m) {
-    const int j = t + T * m;
+    const int j = pos.at(m);
     const R x = fma_(static_cast<R>(j), a.dx, a.x0);
     const R hv = fma_(a.hvx * x, x, hvy);
     C w = half_n(v[m]);
@@ -278,17 +278,19 @@ __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
   const int row0 = wg * ITERS * a.rows_per_block + rloc;
   constexpr bool STEP = MODE == ROW_STEP || MODE == ROW_STEP_NLN;
   const LdsView<C> lds{lds_raw + rloc * 2 * SLOTS + comp, 1};
-  // element `pos` of this lane's component is at byte offset PB pos from the row start; 32-bit
-  // offsets from a wave-uniform base
+  // element j of this lane's component is at byte offset PB j from the row start; 32-bit offsets from
+  // a wave-uniform base.  The pass reads k-space positions and writes them back, except at the ends
+  // of a call (ROW_FWD reads and ROW_INV writes real space).
   const char* __restrict__ base = reinterpret_cast<const char*>(a.psi);
   char* __restrict__ out = reinterpret_cast<char*>(a.psi);
-  const uint32_t lane_off = static_cast<uint32_t>(t) * PB + CB * comp;
+  const LanePos<T> rp = real_pos<N, P>(t), sp = spec_pos<N, P>(t);
+  const LanePos<T> in = MODE == ROW_FWD ? rp : sp, to = MODE == ROW_INV ? rp : sp;
   const uint32_t group_stride = static_cast<uint32_t>(a.rows_per_block) * (PB * N);
 
   double pv[prefetch_per_lane<R, N>()];
   if constexpr (MODE != ROW_FWD) prefetch_partials(a, pv);
   C v[P], nxt[P];
-  uint32_t off = static_cast<uint32_t>(row0) * (PB * N) + lane_off;
+  uint32_t off = static_cast<uint32_t>(row0) * (PB * N) + CB * comp;
   // Load order: the inverse transform starts with the last forward stage, whose butterfly u
   // takes positions u + U k; issuing those loads together lets it start before the rest land.
   constexpr int RL = MODE == ROW_FWD ? P : last_radix<N, P>();
@@ -296,7 +298,7 @@ __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
 #pragma unroll
   for (int i = 0; i < P; ++i) {
     const int m = i / RL + UL * (i % RL);
-    v[m] = *reinterpret_cast<const C*>(base + (off + PB * T * m));
+    v[m] = *reinterpret_cast<const C*>(base + (off + PB * in.at(m)));
   }
   TwPlain<N, P, R> tr;
   load_twiddles<N>(tr, t, a.tw);
@@ -304,7 +306,7 @@ __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
   R hbx_r[P], hby_r[ITERS];
   if constexpr (FULL && STEP) {
 #pragma unroll
-    for (int m = 0; m < P; ++m) hbx_r[m] = a.hbx[t + T * m];
+    for (int m = 0; m < P; ++m) hbx_r[m] = a.hbx[rp.at(m)];
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) hby_r[it] = a.hby[row0 + it * a.rows_per_block];
   }
@@ -316,7 +318,7 @@ __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
 #pragma unroll
       for (int i = 0; i < P; ++i) {
         const int m = i / RL + UL * (i % RL);
-        nxt[m] = *reinterpret_cast<const C*>(base + (off + group_stride + PB * T * m));
+        nxt[m] = *reinterpret_cast<const C*>(base + (off + group_stride + PB * in.at(m)));
       }
     }
     if constexpr (MODE == ROW_FWD) {
@@ -340,7 +342,7 @@ __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
       }
     }
 #pragma unroll
-    for (int m = 0; m < P; ++m) store_state<WT>(reinterpret_cast<C*>(out + (off + PB * T * m)), v[m]);
+    for (int m = 0; m < P; ++m) store_state<WT>(reinterpret_cast<C*>(out + (off + PB * to.at(m))), v[m]);
     if (it + 1 < ITERS) {
 #pragma unroll
       for (int m = 0; m < P; ++m) v[m] = nxt[m];
@@ -365,20 +367,23 @@ __device__ __forceinline__ void row_var_body(const RowArgs& a, int wg) {
   const LdsView<float2> lds{lds_raw + rloc * 2 * SLOTS + comp, 1};
   const char* __restrict__ base = reinterpret_cast<const char*>(a.psi);
   char* __restrict__ out = reinterpret_cast<char*>(a.psi);
-  const uint32_t off = static_cast<uint32_t>(row) * (16u * N) + static_cast<uint32_t>(t) * 16u + 8u * comp;
+  const uint32_t off = static_cast<uint32_t>(row) * (16u * N) + 8u * comp;
   const int flags = a.var_flags;
+  // k-space positions on entry after a column pass, on return after a forward transform
+  const LanePos<T> rp = real_pos<N, P>(t), sp = spec_pos<N, P>(t);
+  const LanePos<T> in = (flags & VAR_INV) ? sp : rp, to = (flags & VAR_FWD) ? sp : rp;
 
   double pv[prefetch_per_lane<float, N>()];
   prefetch_partials(a, pv);
   float2 v[P];
 #pragma unroll
-  for (int m = 0; m < P; ++m) v[m] = *reinterpret_cast<const float2*>(base + (off + 16u * T * m));
+  for (int m = 0; m < P; ++m) v[m] = *reinterpret_cast<const float2*>(base + (off + 16u * in.at(m)));
   TwPlain<N, P> tr;
   load_twiddles<N>(tr, t, a.tw);
   float hbx_r[P], hb_row = 0.0f;
   if constexpr (FULL) {
 #pragma unroll
-    for (int m = 0; m < P; ++m) hbx_r[m] = a.hbx[t + T * m] * a.hfrac;
+    for (int m = 0; m < P; ++m) hbx_r[m] = a.hbx[rp.at(m)] * a.hfrac;
     hb_row = a.hby[row] * a.hfrac;
   }
   const bool mid = (flags & VAR_MID_SCALE) != 0;
@@ -409,7 +414,7 @@ __device__ __forceinline__ void row_var_body(const RowArgs& a, int wg) {
   if (flags & VAR_FWD) fwd_pass<N>(v, lds, t, tr);
   if (!(flags & VAR_NO_STORE)) {
 #pragma unroll
-    for (int m = 0; m < P; ++m) store_state<true>(reinterpret_cast<float2*>(out + (off + 16u * T * m)), v[m]);
+    for (int m = 0; m < P; ++m) store_state<true>(reinterpret_cast<float2*>(out + (off + 16u * to.at(m))), v[m]);
   }
 }
 

@@ -49,7 +49,7 @@ struct RowArgsT {
   point_t<T>* psi;       // [ny][nx] state, in place
   int nx, ny;
   int rows_per_block;
-  const point_t<T>* tw;  // roots exp(-2 pi i j / nx) as {cos, sin, eta, 0} (rounded to T, see fwd_pass)
+  const cplx_t<T>* tw;   // (tan(phi/2), sin(phi)) of phi = 2 pi j / nx at entry j + nx/4, |j| <= nx/4
   // scale applied after the inverse transform: either `scale`, or computed from partials
   T scale;
   const double* partials;  // NULL => use `scale`
@@ -82,7 +82,7 @@ struct ColArgsT {
   point_t<T>* psi;
   int nx, ny;
   int cols;                  // columns per workgroup
-  const point_t<T>* tw;      // roots exp(-2 pi i j / ny) as {cos, sin, eta, 0}
+  const cplx_t<T>* tw;       // the same for ny
   const point_t<T>* kx_tab;  // per k_x: {d11, d12} {d21, d22} as complex (M'(k_x) - 1)
   const cplx_t<T>* ky_tab;   // per k_y: P(k_y) - 1
   double* partials;          // one double per workgroup (norm modes)
@@ -99,7 +99,7 @@ struct LineArgsT {
   point_t<T>* psi;           // [ny][nx] state, in place
   int nx;                    // row length of the state in memory
   int lines;                 // lines (rows or columns) per workgroup
-  const point_t<T>* tw;      // roots of the line's length
+  const cplx_t<T>* tw;       // RowArgsT::tw for the line's length
   const void* op_pre;        // M' - 1 as in ColArgsT::kx_tab (rows) or P - 1 as in ky_tab (columns);
   const void* op_post;       //   NULL: that op is not applied
   int n_r;                   // real-space sub-steps R(h) in turn (0, 1 or 2)
@@ -121,8 +121,8 @@ struct EnergyArgs {
   int nx, ny;
   int rows;                  // rows per row-kernel workgroup (energy_rows_per_block)
   int cols;                  // columns per column-kernel workgroup (energy_cols_per_block)
-  const double4* twx;        // the fp64 step-kernel roots of length nx ({cos, sin, 0, 0} of 2 pi j / nx)
-  const double4* twy;        // the same for ny
+  const double2* twx;        // the fp64 step kernels' root table of length nx
+  const double2* twy;        // the same for ny
   double xmin, dx, ymin, dy;
   double wx2h, wy2h;         // wx^2/2, wy^2/2
   double delta, g_uu, g_dd, g_ud;
