@@ -24,7 +24,6 @@ extern __shared__ __align__(16) unsigned char col_lds[];
 template <int N, int NORM, int ITERS, int P, bool WT, class R>
 __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngroups) {
   using CX = cplx_t<R>;
-  CX* const lds_raw = reinterpret_cast<CX*>(col_lds);
   constexpr uint32_t PB = sizeof(point_t<R>), CB = sizeof(CX);   // bytes per point / component
   __shared__ double red[64];
   constexpr int T = N / P;
@@ -36,7 +35,7 @@ __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngrou
   const int t = pair / C;
   const int tile0 = col_group(wg, ngroups) * ITERS;
   const int x0 = tile0 * C + cc;
-  const LdsView<CX> lds{lds_raw + 2 * cc + comp, 1 + __builtin_ctz(C)};
+  const LdsView<CX> lds = lds_line<N, CX>(col_lds, cc, C, comp);
   // element (row y) of this lane's component is at byte offset PB (y nx + x) + CB comp; 32-bit
   // offsets from a wave-uniform base, the row stride a wave-uniform value
   const char* __restrict__ base = reinterpret_cast<const char*>(a.psi);
@@ -44,12 +43,11 @@ __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngrou
   const uint32_t rstride = PB * static_cast<uint32_t>(a.nx);
   const uint32_t tile_stride = PB * static_cast<uint32_t>(C);
   const LanePos<T> rp = real_pos<N, P>(t), sp = spec_pos<N, P>(t);
-  uint32_t row_off[P];   // of the lane's rows
-#pragma unroll
-  for (int m = 0; m < P; ++m)
-    row_off[m] = m == 0 ? static_cast<uint32_t>(rp.p0) * rstride
-                        : static_cast<uint32_t>(rp.b) * rstride + static_cast<uint32_t>(T * m) * rstride;
-  uint32_t off = PB * static_cast<uint32_t>(x0) + CB * comp;
+  const uint32_t mstride = static_cast<uint32_t>(T) * rstride;
+  uint32_t off = PB * static_cast<uint32_t>(x0) + CB * comp + static_cast<uint32_t>(rp.b) * rstride;
+  // register 0 holds row p0, the others rows b + T m
+  const uint32_t off0 = static_cast<uint32_t>(rp.p0 - rp.b) * rstride;
+  auto row_off = [&](int m) { return m == 0 ? off0 : mstride * static_cast<uint32_t>(m); };
 
   // The k_y operator values of the lane's P rows.  With 16 points per lane the row is staged in
   // LDS (loaded per point after the forward transform, its latency would sit in the middle of the
@@ -76,12 +74,12 @@ __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngrou
   }
   CX v[P], nxt[P];
 #pragma unroll
-  for (int m = 0; m < P; ++m) v[m] = *reinterpret_cast<const CX*>(base + (off + row_off[m]));
+  for (int m = 0; m < P; ++m) v[m] = *reinterpret_cast<const CX*>(base + (off + row_off(m)));
   // this component's row of M' - 1 at k_x: {d_own, d_other}
   point_t<R> d = a.kx_tab[2 * x0 + comp], dn = d;
   TwPlain<N, P, R> tr;
   load_twiddles<N>(tr, t, a.tw);
-  CX* __restrict__ kyl = lds_raw + 2 * C * (N + N / 16);
+  CX* __restrict__ kyl = reinterpret_cast<CX*>(col_lds + kLdsSkew) + 2 * C * (N + N / 16);
   if constexpr (KY_LDS) {
 #pragma unroll
     for (int k = 0; k < KY_MAX; ++k)
@@ -94,7 +92,7 @@ __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngrou
     if (it + 1 < ITERS) {
 #pragma unroll
       for (int m = 0; m < P; ++m)
-        nxt[m] = *reinterpret_cast<const CX*>(base + (off + tile_stride + row_off[m]));
+        nxt[m] = *reinterpret_cast<const CX*>(base + (off + tile_stride + row_off(m)));
       dn = a.kx_tab[2 * (x0 + (it + 1) * C) + comp];
     }
     fwd_pass<N>(v, lds, t, tr);
@@ -124,7 +122,7 @@ __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngrou
     inv_pass<N>(v, lds, t, tr);
 
 #pragma unroll
-    for (int m = 0; m < P; ++m) store_state<WT>(reinterpret_cast<CX*>(out + (off + row_off[m])), v[m]);
+    for (int m = 0; m < P; ++m) store_state<WT>(reinterpret_cast<CX*>(out + (off + row_off(m))), v[m]);
     if (it + 1 < ITERS) {
 #pragma unroll
       for (int m = 0; m < P; ++m) v[m] = nxt[m];

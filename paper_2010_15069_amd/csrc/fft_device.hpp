@@ -114,27 +114,59 @@ struct LanePos {
 };
 
 // ---------------------------------------------------------------------------------------------
-// LDS addressing: a transform's N positions occupy N + N/16 slots (one pad slot per 16
-// positions) and `stride` transforms are interleaved slot by slot, so that lanes which own
-// neighbouring transforms touch neighbouring slots.
+// LDS addressing: a transform's N positions occupy N + N/16 slots (one pad slot per 16 positions) of
+// two values, the components of a line interleaved.  The lines of a workgroup follow one another,
+// each kLdsSkew / lines bytes further than its slots: lanes that own neighbouring lines (column tiles)
+// would else meet in the same banks.  A lane's accesses of a stage are then one register and constants;
+// with the lines interleaved slot by slot, a stride only the launch knows, each took an address of its
+// own (the column pass at 1024 points: 213 VGPRs, now 147).  Skews of 0, 128 and 256 bytes: 28.8, 24.6 and
+// 25.7 us per step at 1024^2 (imaginary time, paired accesses).  Both changes: 24.3 -> 24.0 us per step
+// at 1024^2 in imaginary time and 17.7 -> 16.6 in real time, 7.8 -> 7.4 at 64^2, the 24-instance sweep
+// 17.0 -> 16.3 ms.
 // ---------------------------------------------------------------------------------------------
+// A value in one 8-byte access.  Volatile keeps the compiler from pairing accesses into the two-address
+// forms: ds_read2_b64 took 4.4 LDS cycles per value and wave in these exchanges, two single reads 3.7.
+// (complex128 values are 16 bytes and have no such form.)
+using LdsWord = volatile __attribute__((address_space(3))) unsigned long long;
+__device__ __forceinline__ float2 lds_get(const float2* p) {
+  const unsigned long long b = *(const LdsWord*)(p);
+  float2 v;
+  __builtin_memcpy(&v, &b, sizeof v);
+  return v;
+}
+__device__ __forceinline__ void lds_put(float2* p, float2 v) {
+  unsigned long long b;
+  __builtin_memcpy(&b, &v, sizeof b);
+  *(LdsWord*)(p) = b;
+}
+__device__ __forceinline__ double2 lds_get(const double2* p) { return *p; }
+__device__ __forceinline__ void lds_put(double2* p, double2 v) { *p = v; }
+
 template <class V>
 struct LdsView {
-  V* base;     // slot 0 of this thread's transform
-  int shift;   // log2 of the number of interleaved transforms (a power of two)
+  V* base;     // slot 0 of this lane's line and component
   static __device__ __forceinline__ int slot(int pos) { return pos + (pos >> 4); }
-  __device__ __forceinline__ V& at(int pos) const { return base[slot(pos) << shift]; }
-  // position pos.at(m); steps of a multiple of 16 positions are steps of a fixed number of slots, so
-  // the lane's one base serves every m > 0
+  // the address of position pos.at(m); steps of a multiple of 16 positions are steps of a fixed number
+  // of slots, so the lane's one base serves every m > 0
   template <int STEP>
-  __device__ __forceinline__ V& at(const LanePos<STEP>& pos, int m) const {
+  __device__ __forceinline__ V* at(const LanePos<STEP>& pos, int m) const {
     if constexpr (STEP % 16 == 0) {
-      return m == 0 ? at(pos.p0) : (base + (slot(pos.b) << shift))[(STEP / 16 * 17 * m) << shift];
+      return m == 0 ? base + 2 * slot(pos.p0) : (base + 2 * slot(pos.b)) + 2 * (STEP / 16 * 17) * m;
     } else {
-      return at(pos.at(m));
+      return base + 2 * slot(pos.at(m));
     }
   }
+  template <int STEP>
+  __device__ __forceinline__ V get(const LanePos<STEP>& pos, int m) const { return lds_get(at(pos, m)); }
+  template <int STEP>
+  __device__ __forceinline__ void put(const LanePos<STEP>& pos, int m, V v) const { lds_put(at(pos, m), v); }
 };
+// The view of line `line` of `lines` (a power of two) of length N.
+template <int N, class V>
+__device__ __forceinline__ LdsView<V> lds_line(unsigned char* lds, int line, int lines, int comp) {
+  const int skew = ((line * kLdsSkew) >> __builtin_ctz(lines)) & -int(sizeof(V));
+  return {reinterpret_cast<V*>(lds + line * (2 * (N + N / 16) * int(sizeof(V))) + skew) + comp};
+}
 
 // ---------------------------------------------------------------------------------------------
 // Step-kernel transforms: a forward transform with rounded roots, and its exact inverse.
@@ -470,7 +502,7 @@ __device__ __forceinline__ void pf_stage(C (&v)[P], const LdsView<C>& lds, int t
     } else {
       const auto pos = stage_out_pos<N, P, L>(t);
 #pragma unroll
-      for (int k = 0; k < R; ++k) lds.at(pos, k) = a[k];
+      for (int k = 0; k < R; ++k) lds.put(pos, k, a[k]);
     }
   }
 }
@@ -486,7 +518,7 @@ __device__ __forceinline__ void fwd_pass(C (&v)[P], const LdsView<C>& lds, int t
     __syncthreads();
     const auto pos = stage_in_pos<N, P, L * R>(t);
 #pragma unroll
-    for (int m = 0; m < P; ++m) v[m] = lds.at(pos, m);
+    for (int m = 0; m < P; ++m) v[m] = lds.get(pos, m);
     __syncthreads();
     constexpr int NEXT = BASE + (L > 1 ? (P / R) * (R / 2) : 0);
     fwd_pass<N, L * R, NEXT>(v, lds, t, tr);
@@ -509,7 +541,7 @@ __device__ __forceinline__ void pi_stage(C (&v)[P], const LdsView<C>& lds, int t
     } else {
       const auto pos = stage_out_pos<N, P, L>(t);
 #pragma unroll
-      for (int k = 0; k < R; ++k) a[k] = lds.at(pos, k);
+      for (int k = 0; k < R; ++k) a[k] = lds.get(pos, k);
     }
     pi_dft<R>(a);
     if constexpr (L > 1) {
@@ -537,7 +569,7 @@ __device__ __forceinline__ void inv_pass(C (&v)[P], const LdsView<C>& lds, int t
     // undo the forward's reads from LDS, then this stage
     const auto pos = stage_in_pos<N, P, L * R>(t);
 #pragma unroll
-    for (int m = 0; m < P; ++m) lds.at(pos, m) = v[m];
+    for (int m = 0; m < P; ++m) lds.put(pos, m, v[m]);
     __syncthreads();
     pi_stage<N, P, L, BASE>(v, lds, t, tr);
     __syncthreads();

@@ -21,32 +21,30 @@ template <int N, bool COL, bool FULL, bool NLN, int P, bool WT, class R>
 __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngroups) {
   using C = cplx_t<R>;
   using Q = point_t<R>;
-  C* const lds_raw = reinterpret_cast<C*>(line_lds);
   constexpr int T = N / P;
-  constexpr int SLOTS = N + N / 16;
   constexpr uint32_t PB = sizeof(Q), CB = sizeof(C);   // bytes per point / component
   const int tid = threadIdx.x;
   const int comp = tid & 1;
   const int pair = tid >> 1;
-  int line, t;
-  LdsView<C> lds;
+  int line, t, lane_line;
   uint32_t off, pstride;   // of the lane's line, between its positions
   if constexpr (COL) {
     const int sh = __builtin_ctz(a.lines);
     const int cc = pair & (a.lines - 1);
     t = pair >> sh;
     line = (col_group(wg, ngroups) << sh) + cc;
-    lds = LdsView<C>{lds_raw + 2 * cc + comp, 1 + sh};
+    lane_line = cc;
     off = PB * static_cast<uint32_t>(line) + CB * comp;
     pstride = PB * static_cast<uint32_t>(a.nx);
   } else {
     const int rloc = pair / T;
     t = pair - rloc * T;
     line = wg * a.lines + rloc;
-    lds = LdsView<C>{lds_raw + rloc * 2 * SLOTS + comp, 1};
+    lane_line = rloc;
     off = static_cast<uint32_t>(line) * (PB * N) + CB * comp;
     pstride = PB;
   }
+  const LdsView<C> lds = lds_line<N, C>(line_lds, lane_line, a.lines, comp);
   const LanePos<T> rp = real_pos<N, P>(t), sp = spec_pos<N, P>(t);
   const uint32_t off0 = off + static_cast<uint32_t>(rp.p0) * pstride, offb = off + static_cast<uint32_t>(rp.b) * pstride;
   const uint32_t mstride = static_cast<uint32_t>(T) * pstride;

@@ -12,16 +12,16 @@ namespace sgpe {
 // Geometry
 // -------------------------------------------------------------------------------------------
 // Step kernels: lane pairs (two components) x T = n/points lanes per line; a slot of the LDS
-// exchange holds both components (16 bytes).
-size_t row_lds_bytes(int nx, int rows) { return size_t(rows) * size_t(nx + nx / 16) * 16; }
+// exchange holds both components (16 bytes); lds_line places the lines.
+size_t row_lds_bytes(int nx, int rows) { return size_t(rows) * size_t(nx + nx / 16) * 16 + kLdsSkew; }
 
 // column pass: the transforms' exchange slots, then the k_y operator row (one float2 per k_y)
-size_t col_lds_bytes(int ny, int cols) { return size_t(cols) * size_t(ny + ny / 16) * 16 + size_t(ny) * 8; }
+size_t col_lds_bytes(int ny, int cols) { return row_lds_bytes(ny, cols) + size_t(ny) * 8; }
 
 // complex128 column pass: double2 slots, and the k_y row (one double2 per k_y) where the kernel
 // stages it in LDS (16 points per lane, below 4096 points)
 size_t col_lds_bytes_c128(int ny, int cols, int points) {
-  return size_t(cols) * size_t(ny + ny / 16) * 32 + (points != 16 || ny >= 4096 ? 0 : size_t(ny) * 16);
+  return 2 * row_lds_bytes(ny, cols) + (points != 16 || ny >= 4096 ? 0 : size_t(ny) * 16);
 }
 
 int row_rows_per_block(int nx, int ny, int points, size_t max_lds) {
@@ -54,11 +54,10 @@ int col_default_cols(int nx, int ny, int points, size_t max_lds) {
 // from there; T = N / points lanes per component of a line, two components per lane pair.  Lines per
 // workgroup: up to 128 / T (a workgroup of at most 256 threads, 512 at 4096 points), but no more
 // than keeps ~256 workgroups on the grid (small grids are latency-bound: more workgroups, each
-// shorter).  Both kernels interleave their transforms in LDS slot by slot, N + N/16 double2 slots
-// each.
+// shorter).
 __host__ __device__ constexpr int energy_points(int n) { return n >= 1024 ? 16 : 8; }
 
-size_t energy_lds_bytes(int n, int lines) { return size_t(2) * lines * size_t(n + n / 16) * 16; }
+size_t energy_lds_bytes(int n, int lines) { return 2 * row_lds_bytes(n, lines); }
 
 static int energy_lines_per_block(int n, int count) {
   const int t = n / energy_points(n);
@@ -159,7 +158,7 @@ __device__ __forceinline__ void energy_row_body(const EnergyArgs& a, int block) 
   for (int m = 0; m < P; ++m) v[m] = energy_load<Q>(a, row0 + rp.at(m), comp);
   TwPlain<N, P, double> tr;
   load_twiddles<N>(tr, t, a.twx);
-  const LdsView<double2> lds{reinterpret_cast<double2*>(energy_lds) + 2 * r + comp, 1 + __builtin_ctz(a.rows)};
+  const LdsView<double2> lds = lds_line<N, double2>(energy_lds, r, a.rows, comp);
   fwd_pass<N>(v, lds, t, tr);
   const double kl = comp == 0 ? a.k_l : -a.k_l;
   double ex = 0.0;   // the rows' k_x terms
@@ -209,7 +208,7 @@ __device__ __forceinline__ void energy_col_body(const EnergyArgs& a, int block) 
   for (int m = 0; m < P; ++m) v[m] = energy_load<Q>(a, size_t(rp.at(m)) * a.nx + x, comp);
   TwPlain<N, P, double> tr;
   load_twiddles<N>(tr, t, a.twy);
-  const LdsView<double2> lds{reinterpret_cast<double2*>(energy_lds) + 2 * cc + comp, 1 + __builtin_ctz(C)};
+  const LdsView<double2> lds = lds_line<N, double2>(energy_lds, cc, C, comp);
   fwd_pass<N>(v, lds, t, tr);
   double acc = 0.0;
 #pragma unroll

@@ -266,9 +266,7 @@ extern __shared__ __align__(16) unsigned char row_lds[];
 template <int N, int MODE, bool IMAG, bool FULL, int ITERS, int P, bool WT, class R>
 __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
   using C = cplx_t<R>;
-  C* const lds_raw = reinterpret_cast<C*>(row_lds);
   constexpr int T = N / P;
-  constexpr int SLOTS = N + N / 16;
   constexpr uint32_t PB = sizeof(point_t<R>), CB = sizeof(C);   // bytes per point / component
   const int tid = threadIdx.x;
   const int comp = tid & 1;
@@ -277,7 +275,7 @@ __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
   const int t = pair - rloc * T;
   const int row0 = wg * ITERS * a.rows_per_block + rloc;
   constexpr bool STEP = MODE == ROW_STEP || MODE == ROW_STEP_NLN;
-  const LdsView<C> lds{lds_raw + rloc * 2 * SLOTS + comp, 1};
+  const LdsView<C> lds = lds_line<N, C>(row_lds, rloc, a.rows_per_block, comp);
   // element j of this lane's component is at byte offset PB j from the row start; 32-bit offsets from
   // a wave-uniform base.  The pass reads k-space positions and writes them back, except at the ends
   // of a call (ROW_FWD reads and ROW_INV writes real space).
@@ -354,17 +352,15 @@ __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
 // The general row pass of the splitting variants (one row group per workgroup); see RowVarFlags.
 template <int N, bool IMAG, bool FULL, int P>
 __device__ __forceinline__ void row_var_body(const RowArgs& a, int wg) {
-  float2* const lds_raw = reinterpret_cast<float2*>(row_lds);
   __shared__ double red[64];
   constexpr int T = N / P;
-  constexpr int SLOTS = N + N / 16;
   const int tid = threadIdx.x;
   const int comp = tid & 1;
   const int pair = tid >> 1;
   const int rloc = pair / T;
   const int t = pair - rloc * T;
   const int row = wg * a.rows_per_block + rloc;
-  const LdsView<float2> lds{lds_raw + rloc * 2 * SLOTS + comp, 1};
+  const LdsView<float2> lds = lds_line<N, float2>(row_lds, rloc, a.rows_per_block, comp);
   const char* __restrict__ base = reinterpret_cast<const char*>(a.psi);
   char* __restrict__ out = reinterpret_cast<char*>(a.psi);
   const uint32_t off = static_cast<uint32_t>(row) * (16u * N) + 8u * comp;

@@ -270,6 +270,7 @@ bool col_cols_supported(int nx, int ny, int cols, int iters, int points, size_t 
 bool energy_fits(int nx, int ny, size_t max_lds);
 int energy_rows_per_block(int nx, int ny);
 int energy_cols_per_block(int nx, int ny, size_t max_lds);
+constexpr int kLdsSkew = 128;   // bytes, shared out among a workgroup's lines (lds_line)
 size_t energy_lds_bytes(int n, int lines);
 size_t row_lds_bytes(int nx, int rows);
 size_t col_lds_bytes(int ny, int cols);
