@@ -132,10 +132,11 @@ double kval(int j, int n, double d) {
 // k-space 2x2 propagator factored as P(k_y) M'(k_x) with
 //   M'(k_x) = e^{-h kx^2/2 (i)} [ c 1 - s (b . sigma) ],  b = (omega/2, k_l k_x),
 //   P(k_y)  = e^{-h ky^2/2 (i)};
-// stored as M' - 1 (four complex entries) and P - 1, to fp32 relative accuracy.
+// stored as M' - 1 (per component its row, {own, other}) and P - 1, to relative accuracy.  Real time:
+// complex entries.
 template <class T = float>
-void k_tables(const sgpe_params& p, bool imag, double h, std::vector<sgpe::point_t<T>>& kx_out,
-              std::vector<sgpe::cplx_t<T>>& ky_out) {
+void k_tables_real(const sgpe_params& p, double h, std::vector<sgpe::point_t<T>>& kx_out,
+                   std::vector<sgpe::cplx_t<T>>& ky_out) {
   const double dx = 2.0 * p.xmax / p.nx, dy = 2.0 * p.ymax / p.ny;
   kx_out.assign(2 * size_t(p.nx), mk4(0, 0, 0, 0, T()));
   ky_out.assign(size_t(p.ny), mk2h(0, 0, T()));
@@ -144,23 +145,13 @@ void k_tables(const sgpe_params& p, bool imag, double h, std::vector<sgpe::point
     const double bx = 0.5 * p.omega, bz = p.k_l * kx;
     const double bm = std::hypot(bx, bz);
     const double al = 0.5 * h * kx * kx;
-    double m11r, m11i, m12r, m12i, m22r, m22i;
-    if (!imag) {
-      const double c = std::cos(h * bm);
-      const double s = bm > 0.0 ? std::sin(h * bm) / bm : h;
-      const double pr = std::cos(al), pi = -std::sin(al);
-      // pref * (c - i s bz), pref * (-i s bx), pref * (c + i s bz)
-      m11r = pr * c + pi * s * bz;  m11i = pi * c - pr * s * bz;
-      m12r = pi * s * bx;           m12i = -pr * s * bx;
-      m22r = pr * c - pi * s * bz;  m22i = pi * c + pr * s * bz;
-    } else {
-      const double ch = std::cosh(h * bm);
-      const double sh = bm > 0.0 ? std::sinh(h * bm) / bm : h;
-      const double pr = std::exp(-al);
-      m11r = pr * (ch - sh * bz);  m11i = 0.0;
-      m12r = -pr * sh * bx;        m12i = 0.0;
-      m22r = pr * (ch + sh * bz);  m22i = 0.0;
-    }
+    const double c = std::cos(h * bm);
+    const double s = bm > 0.0 ? std::sin(h * bm) / bm : h;
+    const double pr = std::cos(al), pi = -std::sin(al);
+    // pref * (c - i s bz), pref * (-i s bx), pref * (c + i s bz)
+    const double m11r = pr * c + pi * s * bz, m11i = pi * c - pr * s * bz;
+    const double m12r = pi * s * bx, m12i = -pr * s * bx;
+    const double m22r = pr * c - pi * s * bz, m22i = pi * c + pr * s * bz;
     // per component: {d_own, d_other} of its row of M' - 1 (up: d11, d12; down: d22, d21)
     kx_out[2 * size_t(j)] = mk4(m11r - 1.0, m11i, m12r, m12i, T());
     kx_out[2 * size_t(j) + 1] = mk4(m22r - 1.0, m22i, m12r, m12i, T());
@@ -168,12 +159,30 @@ void k_tables(const sgpe_params& p, bool imag, double h, std::vector<sgpe::point
   for (int i = 0; i < p.ny; ++i) {
     const double ky = kval(i, p.ny, dy);
     const double be = 0.5 * h * ky * ky;
-    if (!imag) {
-      const double sh = std::sin(0.5 * be);
-      ky_out[i] = mk2h(-2.0 * sh * sh, -std::sin(be), T());
-    } else {
-      ky_out[i] = mk2h(std::expm1(-be), 0.0, T());
-    }
+    const double sh = std::sin(0.5 * be);
+    ky_out[i] = mk2h(-2.0 * sh * sh, -std::sin(be), T());
+  }
+}
+
+// Imaginary time: the same with hyperbolic functions, all entries real.
+template <class T = float>
+void k_tables_imag(const sgpe_params& p, double h, std::vector<sgpe::cplx_t<T>>& kx_out, std::vector<T>& ky_out) {
+  const double dx = 2.0 * p.xmax / p.nx, dy = 2.0 * p.ymax / p.ny;
+  kx_out.assign(2 * size_t(p.nx), mk2h(0, 0, T()));
+  ky_out.assign(size_t(p.ny), T(0));
+  for (int j = 0; j < p.nx; ++j) {
+    const double kx = kval(j, p.nx, dx);
+    const double bx = 0.5 * p.omega, bz = p.k_l * kx;
+    const double bm = std::hypot(bx, bz);
+    const double ch = std::cosh(h * bm);
+    const double sh = bm > 0.0 ? std::sinh(h * bm) / bm : h;
+    const double pr = std::exp(-0.5 * h * kx * kx);
+    kx_out[2 * size_t(j)] = mk2h(pr * (ch - sh * bz) - 1.0, -pr * sh * bx, T());
+    kx_out[2 * size_t(j) + 1] = mk2h(pr * (ch + sh * bz) - 1.0, -pr * sh * bx, T());
+  }
+  for (int i = 0; i < p.ny; ++i) {
+    const double ky = kval(i, p.ny, dy);
+    ky_out[i] = T(std::expm1(-0.5 * h * ky * ky));
   }
 }
 
@@ -302,19 +311,18 @@ sgpe::RowArgsT<T> row_args_t(const sgpe_ctx* c, double h_sub) {
 RowArgs row_args(const sgpe_ctx* c, double h_sub) { return row_args_t<float>(c, h_sub); }
 
 template <class T>
-sgpe::ColArgsT<T> col_args_t(const sgpe_ctx* c, bool imag, bool half) {
+sgpe::ColArgsT<T> col_args_t(const sgpe_ctx* c, bool half) {
   sgpe::ColArgsT<T> a{};
-  const int idx = 2 * (imag ? 1 : 0) + (half ? 1 : 0);
   if constexpr (std::is_same<T, double>::value) {
     a.psi = c->psi64;
     a.tw = c->twp64_y;
-    a.kx_tab = c->kx64[idx];
-    a.ky_tab = c->ky64[idx];
+    a.kx_tab = c->kx64_imag[half];
+    a.ky_tab = c->ky64_imag[half];
   } else {
     a.psi = c->psi;
     a.tw = c->twp_y;
-    a.kx_tab = c->kx_tab[idx];
-    a.ky_tab = c->ky_tab[idx];
+    a.kx_tab = c->kx_imag[half];
+    a.ky_tab = c->ky_imag[half];
   }
   a.nx = c->p.nx;
   a.ny = c->p.ny;
@@ -323,7 +331,7 @@ sgpe::ColArgsT<T> col_args_t(const sgpe_ctx* c, bool imag, bool half) {
   return a;
 }
 
-ColArgs col_args(const sgpe_ctx* c, bool imag, bool half) { return col_args_t<float>(c, imag, half); }
+ColArgs col_args(const sgpe_ctx* c, bool half) { return col_args_t<float>(c, half); }
 
 // Line-pass arguments along columns (col) or rows with ops of K(pre), K(post) (LineOp) and n_r real-space
 // sub-steps R(h_sub) (h_sub <= 0: dt).  x is the axis along the line.
@@ -337,8 +345,11 @@ sgpe::LineArgsT<T> line_args_t(const sgpe_ctx* c, bool col, LineOp pre, LineOp p
   a.lines = col ? c->cols : c->rows;
   auto op = [&](LineOp o) -> const void* {
     if (o == LINE_NONE) return nullptr;
-    const sgpe::ColArgsT<T> k = col_args_t<T>(c, false, o == LINE_HALF);
-    return col ? static_cast<const void*>(k.ky_tab) : static_cast<const void*>(k.kx_tab);
+    const bool half = o == LINE_HALF;
+    if constexpr (std::is_same<T, double>::value)
+      return col ? static_cast<const void*>(c->ky64_real[half]) : static_cast<const void*>(c->kx64_real[half]);
+    else
+      return col ? static_cast<const void*>(c->ky_real[half]) : static_cast<const void*>(c->kx_real[half]);
   };
   a.op_pre = op(pre);
   a.op_post = op(post);
@@ -348,7 +359,7 @@ sgpe::LineArgsT<T> line_args_t(const sgpe_ctx* c, bool col, LineOp pre, LineOp p
   a.hg_uu = r.hg_uu;
   a.hg_dd = r.hg_dd;
   a.hg_ud = r.hg_ud;
-  a.tw = col ? col_args_t<T>(c, false, false).tw : r.tw;
+  a.tw = col ? col_args_t<T>(c, false).tw : r.tw;
   a.x0 = col ? r.y0 : r.x0;
   a.dx = col ? r.dy : r.dx;
   a.y0 = col ? r.x0 : r.y0;
@@ -428,10 +439,10 @@ static sgpe_status run_steps_c128(sgpe_ctx* c, int64_t n) {
   c->tail_pending = 0;
   hipError_t e;
   if (cont) {
-    e = sgpe::launch_col(col_args_t<double>(c, true, false), sgpe::NORM_DOT, c->col_points, s);
+    e = sgpe::launch_col(col_args_t<double>(c, false), sgpe::NORM_DOT, c->col_points, s);
   } else {
     e = sgpe::launch_row(ra, sgpe::ROW_FWD, false, false, c->row_points, s);
-    if (e == hipSuccess) e = sgpe::launch_col(col_args_t<double>(c, true, true), sgpe::NORM_NONE, c->col_points, s);
+    if (e == hipSuccess) e = sgpe::launch_col(col_args_t<double>(c, true), sgpe::NORM_NONE, c->col_points, s);
   }
   const bool defer = c->own_psi;
   for (int64_t i = 1; i <= n && e == hipSuccess; ++i) {
@@ -445,7 +456,7 @@ static sgpe_status run_steps_c128(sgpe_ctx* c, int64_t n) {
     const bool last = (i == n);
     if (last && defer) break;   // the last K(dt/2) and the inverse x-transform wait (flush_tail)
     if (e == hipSuccess)
-      e = sgpe::launch_col(col_args_t<double>(c, true, last), last ? sgpe::NORM_SQ : sgpe::NORM_DOT, c->col_points, s);
+      e = sgpe::launch_col(col_args_t<double>(c, last), last ? sgpe::NORM_SQ : sgpe::NORM_DOT, c->col_points, s);
   }
   if (e == hipSuccess && defer) {
     c->tail_pending = 2;
@@ -496,11 +507,11 @@ sgpe_status run_steps(sgpe_ctx* c, int64_t n, bool imag, std::vector<hipEvent_t>
   const bool cont = c->tail_pending == 2;
   c->tail_pending = 0;
   if (cont) {
-    e = sgpe::launch_col(col_args(c, true, false), sgpe::NORM_DOT, c->col_iters, c->col_points, s);
+    e = sgpe::launch_col(col_args(c, false), sgpe::NORM_DOT, c->col_iters, c->col_points, s);
   } else {
     e = sgpe::launch_row(ra, sgpe::ROW_FWD, false, false, c->row_iters, c->row_points, s);
     if (e == hipSuccess)
-      e = sgpe::launch_col(col_args(c, true, true), sgpe::NORM_NONE, c->col_iters, c->col_points, s);
+      e = sgpe::launch_col(col_args(c, true), sgpe::NORM_NONE, c->col_iters, c->col_points, s);
   }
   if (e != hipSuccess) return status_of(e);
   // a context on a caller's state buffer, and a timed profile, complete every call
@@ -519,7 +530,7 @@ sgpe_status run_steps(sgpe_ctx* c, int64_t n, bool imag, std::vector<hipEvent_t>
     if (ev) (void)hipEventRecord((*ev)[evi++], s);
     const bool last = (i == n);
     if (last && defer) break;   // the last K(dt/2) and the inverse x-transform wait (flush_tail)
-    e = sgpe::launch_col(col_args(c, true, last), last ? sgpe::NORM_SQ : sgpe::NORM_DOT, c->col_iters, c->col_points, s);
+    e = sgpe::launch_col(col_args(c, last), last ? sgpe::NORM_SQ : sgpe::NORM_DOT, c->col_iters, c->col_points, s);
     if (e != hipSuccess) return status_of(e);
     if (ev) (void)hipEventRecord((*ev)[evi++], s);
   }
@@ -548,7 +559,7 @@ sgpe_status flush_tail(sgpe_ctx* c) {
     return status_of(e);
   }
   if (c->prec == SGPE_C128) {
-    hipError_t e = sgpe::launch_col(col_args_t<double>(c, true, true), sgpe::NORM_SQ, c->col_points, c->stream);
+    hipError_t e = sgpe::launch_col(col_args_t<double>(c, true), sgpe::NORM_SQ, c->col_points, c->stream);
     if (e != hipSuccess) return status_of(e);
     sgpe::RowArgsT<double> r = row_args_t<double>(c, 0.0);
     r.scale = 1.0 / (double(c->p.nx) * double(c->p.ny));
@@ -556,7 +567,7 @@ sgpe_status flush_tail(sgpe_ctx* c) {
     r.n_partials = col_groups(c);
     return status_of(sgpe::launch_row(r, sgpe::ROW_INV, false, false, c->row_points, c->stream));
   }
-  hipError_t e = sgpe::launch_col(col_args(c, true, true), sgpe::NORM_SQ, c->col_iters, c->col_points, c->stream);
+  hipError_t e = sgpe::launch_col(col_args(c, true), sgpe::NORM_SQ, c->col_iters, c->col_points, c->stream);
   if (e != hipSuccess) return status_of(e);
   RowArgs r = row_args(c);
   r.scale = float(1.0 / (double(c->p.nx) * double(c->p.ny)));
@@ -619,7 +630,7 @@ static sgpe_status run_steps_variant(sgpe_ctx* c, int64_t n, bool imag) {
   for (int64_t i = 1; i <= n; ++i) {
     const bool last = (i == n);
     if (e == hipSuccess)
-      e = sgpe::launch_col(col_args(c, true, false), sgpe::NORM_NONE, c->col_iters, c->col_points, s);
+      e = sgpe::launch_col(col_args(c, false), sgpe::NORM_NONE, c->col_iters, c->col_points, s);
     row(sgpe::VAR_INV | sgpe::VAR_NORM_OUT | sgpe::VAR_NO_STORE, 1, nullptr, 0);
     row(sgpe::VAR_INV | sgpe::VAR_MID_SCALE | (last ? 0 : sgpe::VAR_FWD), last ? 1 : 2, c->partials, row_groups);
   }
@@ -882,25 +893,25 @@ sgpe_status sgpe_create_ex(const sgpe_params* p, int32_t precision, void* hip_st
     if ((st = upload(c, &c->twp_x, root_table(p->nx))) != SGPE_OK) return fail(st);
     if ((st = upload(c, &c->twp_y, root_table(p->ny))) != SGPE_OK) return fail(st);
   }
-  for (int imag = 0; imag < 2; ++imag) {
+  auto k_upload = [&](auto type, auto** kxr, auto** kyr, auto** kxi, auto** kyi) {
+    using T = decltype(type);
     for (int half = 0; half < 2; ++half) {
-      const int idx = 2 * imag + half;
       const double h = half ? 0.5 * p->dt : p->dt;
-      if (c128) {
-        std::vector<double4> kx;
-        std::vector<double2> ky;
-        k_tables<double>(*p, imag != 0, h, kx, ky);
-        if ((st = upload(c, &c->kx64[idx], kx)) != SGPE_OK) return fail(st);
-        if ((st = upload(c, &c->ky64[idx], ky)) != SGPE_OK) return fail(st);
-      } else {
-        std::vector<float4> kx;
-        std::vector<float2> ky;
-        k_tables(*p, imag != 0, h, kx, ky);
-        if ((st = upload(c, &c->kx_tab[idx], kx)) != SGPE_OK) return fail(st);
-        if ((st = upload(c, &c->ky_tab[idx], ky)) != SGPE_OK) return fail(st);
-      }
+      std::vector<sgpe::point_t<T>> kx;
+      std::vector<sgpe::cplx_t<T>> ky, kxm;
+      std::vector<T> kym;
+      k_tables_real<T>(*p, h, kx, ky);
+      k_tables_imag<T>(*p, h, kxm, kym);
+      sgpe_status u;
+      if ((u = upload(c, &kxr[half], kx)) != SGPE_OK || (u = upload(c, &kyr[half], ky)) != SGPE_OK ||
+          (u = upload(c, &kxi[half], kxm)) != SGPE_OK || (u = upload(c, &kyi[half], kym)) != SGPE_OK)
+        return u;
     }
-  }
+    return SGPE_OK;
+  };
+  st = c128 ? k_upload(double(), c->kx64_real, c->ky64_real, c->kx64_imag, c->ky64_imag)
+            : k_upload(float(), c->kx_real, c->ky_real, c->kx_imag, c->ky_imag);
+  if (st != SGPE_OK) return fail(st);
   if (c->full2x2) {
     std::vector<double> om(p->nx);
     const double dx = 2.0 * p->xmax / p->nx;
@@ -1245,12 +1256,12 @@ sgpe_status sgpe_profile_kernels(sgpe_ctx* c, int32_t imag, int64_t n, double* r
   RowArgs r = row_args(c);
   if (imag) {
     if (e == hipSuccess) e = sgpe::launch_row(r, sgpe::ROW_FWD, false, false, c->row_iters, c->row_points, s);
-    if (e == hipSuccess) e = sgpe::launch_col(col_args(c, true, true), sgpe::NORM_DOT, c->col_iters, c->col_points, s);
+    if (e == hipSuccess) e = sgpe::launch_col(col_args(c, true), sgpe::NORM_DOT, c->col_iters, c->col_points, s);
     r.scale = float(1.0 / (double(p.nx) * double(p.ny)));
     r.partials = c->partials;
     r.n_partials = col_groups(c);
   }
-  const ColArgs ca = col_args(c, true, false);
+  const ColArgs ca = col_args(c, false);
   if (e == hipSuccess) e = hipEventRecord(ev[0], s);
   for (int64_t i = 0; i < n && e == hipSuccess; ++i)
     e = imag ? sgpe::launch_row(r, sgpe::ROW_STEP, true, c->full2x2, c->row_iters, c->row_points, s)

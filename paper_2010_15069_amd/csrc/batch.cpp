@@ -119,8 +119,8 @@ sgpe_status build_tables(BatchClass& k, const std::vector<sgpe_ctx*>& inst) {
     rows[ROWTAB_FWD * n + j] = a;
     rows[ROWTAB_SCALE * n + j] = sc;
     rows[ROWTAB_PARTIALS * n + j] = pa;
-    cols[COLTAB_FULL * n + j] = col_args(c, true, false);
-    cols[COLTAB_HALF * n + j] = col_args(c, true, true);
+    cols[COLTAB_FULL * n + j] = col_args(c, false);
+    cols[COLTAB_HALF * n + j] = col_args(c, true);
     for (int col = 0; col < 2; ++col) {
       lines[(2 * LINETAB_FIRST + col) * n + j] = line_args(c, col, LINE_HALF, LINE_FULL, 1);
       lines[(2 * LINETAB_MID + col) * n + j] = line_args(c, col, LINE_FULL, LINE_FULL, 1);
@@ -170,7 +170,7 @@ hipError_t enqueue_class_imag(const sgpe_batch* b, const BatchClass& k, int64_t 
   const int cnt = int(k.members.size());
   const sgpe_ctx* c0 = b->inst[k.members[0]];
   const RowArgs shape_r = row_args(c0);
-  const ColArgs shape_c = col_args(c0, true, false);
+  const ColArgs shape_c = col_args(c0, false);
   const int rp = c0->row_points, cp = c0->col_points;
   const RowArgs* t_fwd = k.row_tab + ROWTAB_FWD * cnt;
   const RowArgs* t_sc = k.row_tab + ROWTAB_SCALE * cnt;
@@ -202,7 +202,7 @@ hipError_t enqueue_persistent(sgpe_batch* b, int64_t n, bool imag, hipStream_t s
       if (e == hipSuccess)
         e = sgpe::launch_row_batch(row_args(c0), k.row_tab + ROWTAB_FWD * cnt, cnt, sgpe::ROW_FWD, false, false, 8, s);
       if (e == hipSuccess)
-        e = sgpe::launch_col_batch(col_args(c0, true, false), k.col_tab + COLTAB_HALF * cnt, cnt, sgpe::NORM_NONE, 8, s);
+        e = sgpe::launch_col_batch(col_args(c0, false), k.col_tab + COLTAB_HALF * cnt, cnt, sgpe::NORM_NONE, 8, s);
     } else {
       if (e == hipSuccess) e = class_line(b, k, LINETAB_HALF, false, s);
       if (e == hipSuccess) e = class_line(b, k, line_variant(1, n), true, s);
@@ -235,7 +235,7 @@ hipError_t enqueue_persistent(sgpe_batch* b, int64_t n, bool imag, hipStream_t s
       if (e == hipSuccess)
         e = sgpe::launch_row_batch(shape_r, n > 1 ? t_pa : t_sc, cnt, sgpe::ROW_STEP, true, false, 8, s);
       if (e == hipSuccess)
-        e = sgpe::launch_col_batch(col_args(c0, true, false), k.col_tab + COLTAB_HALF * cnt, cnt, sgpe::NORM_SQ, 8, s);
+        e = sgpe::launch_col_batch(col_args(c0, false), k.col_tab + COLTAB_HALF * cnt, cnt, sgpe::NORM_SQ, 8, s);
       if (e == hipSuccess) e = sgpe::launch_row_batch(shape_r, t_pa, cnt, sgpe::ROW_INV, false, false, 8, s);
     } else {
       if (e == hipSuccess && n > 1) e = class_line(b, k, LINETAB_LAST, n % 2 != 0, s);
@@ -593,7 +593,7 @@ static sgpe_status enable_persistent(sgpe_batch* b) {
     a.partials = c->partials;
     a.n_partials = col_groups(c);
     imag[i] = a;
-    col[i] = col_args(c, true, false);
+    col[i] = col_args(c, false);
     line_r[i] = line_args(c, false, LINE_FULL, LINE_FULL, 1);
     line_c[i] = line_args(c, true, LINE_FULL, LINE_FULL, 1);
   }

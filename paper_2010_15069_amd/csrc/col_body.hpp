@@ -62,7 +62,7 @@ __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngrou
   constexpr bool KY_LDS = P == 16 && !KY_GLOBAL;
   constexpr int KY_MAX = KY_LDS ? P / 2 : 1;
   const int nth = blockDim.x;
-  CX kyv[KY_MAX], kyr[(KY_LDS || KY_GLOBAL) ? 1 : P];
+  R kyv[KY_MAX], kyr[(KY_LDS || KY_GLOBAL) ? 1 : P];
   if constexpr (KY_GLOBAL) {
   } else if constexpr (KY_LDS) {
 #pragma unroll
@@ -75,11 +75,11 @@ __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngrou
   CX v[P], nxt[P];
 #pragma unroll
   for (int m = 0; m < P; ++m) v[m] = *reinterpret_cast<const CX*>(base + (off + row_off(m)));
-  // this component's row of M' - 1 at k_x: {d_own, d_other}
-  point_t<R> d = a.kx_tab[2 * x0 + comp], dn = d;
+  // this component's row of M' - 1 at k_x: {own, other}, real in imaginary time as P - 1 is
+  CX d = a.kx_tab[2 * x0 + comp], dn = d;
   TwPlain<N, P, R> tr;
   load_twiddles<N>(tr, t, a.tw);
-  CX* __restrict__ kyl = reinterpret_cast<CX*>(col_lds + kLdsSkew) + 2 * C * (N + N / 16);
+  R* __restrict__ kyl = reinterpret_cast<R*>(col_lds + kLdsSkew + size_t(C) * (2 * (N + N / 16) * CB));
   if constexpr (KY_LDS) {
 #pragma unroll
     for (int k = 0; k < KY_MAX; ++k)
@@ -102,14 +102,12 @@ __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngrou
     for (int m = 0; m < P; ++m) {
       const CX w = v[m];
       const CX o = pair_swap(w);
-      CX q;
+      R q;
       if constexpr (KY_GLOBAL) q = a.ky_tab[sp.at(m)];
       else if constexpr (KY_LDS) q = kyl[sp.at(m)];
       else q = kyr[m];
-      const R c1r = fma_(-d.w, o.y, fma_(d.z, o.x, fma_(-d.y, w.y, d.x * w.x)));
-      const R c1i = fma_(d.w, o.x, fma_(d.z, o.y, fma_(d.y, w.x, d.x * w.y)));
-      const R cr = fma_(-q.y, w.y, fma_(q.x, w.x, fma_(-q.y, c1i, fma_(q.x, c1r, c1r))));
-      const R ci = fma_(q.y, w.x, fma_(q.x, w.y, fma_(q.y, c1r, fma_(q.x, c1i, c1i))));
+      const R c1r = fma_(d.y, o.x, d.x * w.x), c1i = fma_(d.y, o.y, d.x * w.y);
+      const R cr = fma_(q, w.x, fma_(q, c1r, c1r)), ci = fma_(q, w.y, fma_(q, c1i, c1i));
       const CX res = mk2(w.x + cr, w.y + ci);
       if constexpr (NORM == NORM_DOT) {
         acc += static_cast<double>(fma_(w.x, res.x, w.y * res.y));

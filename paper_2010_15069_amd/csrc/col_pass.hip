@@ -11,7 +11,8 @@
 //
 // U_K = P(k_y) M'(k_x) is applied as w + [c1 + q (w + c1)] with c1 = (M' - 1) w and q = P - 1,
 // the bracket formed first and added to w once: the dominant modes of a smooth state are rounded
-// once per step instead of twice per factor (which gives a coherent norm drift).
+// once per step instead of twice per factor (which gives a coherent norm drift).  The pass serves
+// imaginary time alone (a real-time step takes the line pass), where M' and P are real.
 #include "col_body.hpp"
 
 namespace sgpe {

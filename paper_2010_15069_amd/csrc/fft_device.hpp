@@ -55,6 +55,8 @@ __device__ __forceinline__ float exp_(float x) { return expf(x); }
 __device__ __forceinline__ double exp_(double x) { return exp(x); }
 __device__ __forceinline__ float sqrt_(float x) { return sqrtf(x); }
 __device__ __forceinline__ double sqrt_(double x) { return sqrt(x); }
+__device__ __forceinline__ float fmax_(float a, float b) { return fmaxf(a, b); }
+__device__ __forceinline__ double fmax_(double a, double b) { return fmax(a, b); }
 __device__ __forceinline__ float fabs_(float x) { return fabsf(x); }
 __device__ __forceinline__ double fabs_(double x) { return fabs(x); }
 
@@ -641,14 +643,9 @@ __host__ __device__ __forceinline__ SinCosM1 sincos_m1_small(float phi) {
   return out;
 }
 
-__device__ __forceinline__ SinCosM1 sincos_m1(float phi) {
-  if (fabsf(phi) <= 0.785398163f) return sincos_m1_small(phi);
-  return sincos_m1_reduced(phi);
-}
-
 // The same with the routine fixed at compile time: SMALL requires |phi| <= pi/4; the reduced
-// routine is exact for every phi.  Kernels pick one per wave (see wave_all), so a wave runs one
-// straight-line routine instead of both paths under an execution mask.
+// routine is exact for every phi and returns the same bits for small ones.  A wave picks one for all
+// of its points (see small_angles), so it runs one straight line of code.
 template <bool SMALL>
 __device__ __forceinline__ SinCosM1 sincos_m1_t(float phi) {
   if constexpr (SMALL) return sincos_m1_small(phi);
@@ -656,21 +653,78 @@ __device__ __forceinline__ SinCosM1 sincos_m1_t(float phi) {
 }
 constexpr float kSmallPhase = 0.785398163f;   // pi/4
 
-// fp64: (cos(phi) - 1, sin(phi), sin(phi)/phi) from one fp64 library sincos of phi/2, by the
-// half-angle identities cos(phi) - 1 = -2 sin^2(phi/2) (relative accuracy for small phi) and
-// sin(phi) = 2 sin(phi/2) cos(phi/2); one routine for every phi, so SMALL makes no difference.
+// fp64.  |phi| <= pi/4: Taylor polynomials (the first terms left out are below 3e-18).  Beyond: one
+// library sincos of phi/2 and the half-angle identities cos(phi) - 1 = -2 sin^2(phi/2), sin(phi) =
+// 2 sin(phi/2) cos(phi/2).  The general routine chooses by the angle, so a wave's vote does not change
+// results.
 struct SinCosM1d {
   double cm1, s, sinc;
 };
+__device__ __forceinline__ SinCosM1d sincos_m1_small(double phi) {
+  const double r = phi * phi;
+  double p = -1.0 / 121645100408832000.0;   // sin(phi) / phi - 1 = r p
+  p = fma(r, p, 1.0 / 355687428096000.0);
+  p = fma(r, p, -1.0 / 1307674368000.0);
+  p = fma(r, p, 1.0 / 6227020800.0);
+  p = fma(r, p, -1.0 / 39916800.0);
+  p = fma(r, p, 1.0 / 362880.0);
+  p = fma(r, p, -1.0 / 5040.0);
+  p = fma(r, p, 1.0 / 120.0);
+  p = fma(r, p, -1.0 / 6.0);
+  double q = -1.0 / 6402373705728000.0;     // cos(phi) - 1 = r q
+  q = fma(r, q, 1.0 / 20922789888000.0);
+  q = fma(r, q, -1.0 / 87178291200.0);
+  q = fma(r, q, 1.0 / 479001600.0);
+  q = fma(r, q, -1.0 / 3628800.0);
+  q = fma(r, q, 1.0 / 40320.0);
+  q = fma(r, q, -1.0 / 720.0);
+  q = fma(r, q, 1.0 / 24.0);
+  q = fma(r, q, -0.5);
+  SinCosM1d out;
+  p *= r;
+  out.s = fma(phi, p, phi);
+  out.cm1 = r * q;
+  out.sinc = 1.0 + p;
+  return out;
+}
 template <bool SMALL>
 __device__ __forceinline__ SinCosM1d sincos_m1_t(double phi) {
+  if (SMALL || fabs(phi) <= double(kSmallPhase)) return sincos_m1_small(phi);
   SinCosM1d out;
   double h, c;
   sincos(0.5 * phi, &h, &c);
   out.s = 2.0 * h * c;
   out.cm1 = -2.0 * h * h;
-  out.sinc = phi != 0.0 ? out.s / phi : 1.0;
+  out.sinc = out.s / phi;
   return out;
+}
+
+// exp(x) - 1 for |x| <= kSmallExp: x + x^2 p(x), with p of degree 4 in fp32 (Chebyshev; as a factor
+// w + w (exp(x) - 1) the result is within 7e-8 of w exp(x), rms 2.6e-8, where a correctly rounded
+// exp and a product reach 1.1e-7 and 3.6e-8) and Taylor's of degree 12 in fp64 (1e-16 / 14!).
+constexpr float kSmallExp = 0.35f;
+__device__ __forceinline__ float expm1_small(float x) {
+  float p = fmaf(x, 1.3934535e-3f, 8.3637694e-3f);
+  p = fmaf(x, p, 4.16664556e-2f);
+  p = fmaf(x, p, 1.66665733e-1f);
+  p = fmaf(x, p, 0.5f);
+  return fmaf(x * x, p, x);
+}
+__device__ __forceinline__ double expm1_small(double x) {
+  double p = 1.0 / 87178291200.0;
+  p = fma(x, p, 1.0 / 6227020800.0);
+  p = fma(x, p, 1.0 / 479001600.0);
+  p = fma(x, p, 1.0 / 39916800.0);
+  p = fma(x, p, 1.0 / 3628800.0);
+  p = fma(x, p, 1.0 / 362880.0);
+  p = fma(x, p, 1.0 / 40320.0);
+  p = fma(x, p, 1.0 / 5040.0);
+  p = fma(x, p, 1.0 / 720.0);
+  p = fma(x, p, 1.0 / 120.0);
+  p = fma(x, p, 1.0 / 24.0);
+  p = fma(x, p, 1.0 / 6.0);
+  p = fma(x, p, 0.5);
+  return fma(x * x, p, x);
 }
 
 // True in every lane iff p holds in every active lane of the wave (a wave-uniform value).

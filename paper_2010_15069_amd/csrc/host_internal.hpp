@@ -20,9 +20,11 @@ struct sgpe_ctx {
   float4* scratch = nullptr;
   float2* twp_x = nullptr;  // root tables (RowArgsT::tw) of the step kernels
   float2* twp_y = nullptr;
-  // K tables, index = 2*imag + half  (half: h = dt/2, else h = dt)
-  float4* kx_tab[4] = {nullptr, nullptr, nullptr, nullptr};
-  float2* ky_tab[4] = {nullptr, nullptr, nullptr, nullptr};
+  // K tables of h = dt and h = dt/2: complex in real time (LineArgsT), real in imaginary time (ColArgsT)
+  float4* kx_real[2] = {nullptr, nullptr};
+  float2* ky_real[2] = {nullptr, nullptr};
+  float2* kx_imag[2] = {nullptr, nullptr};
+  float* ky_imag[2] = {nullptr, nullptr};
   // spatial Raman coupling Omega_x(x) + Omega_y(y), only with one (full2x2):
   float* hbx = nullptr;     // dt * Omega_x(x_j) / 2
   float* hby = nullptr;     // dt * Omega_y(y_i) / 2
@@ -45,8 +47,10 @@ struct sgpe_ctx {
   double4* psi64 = nullptr;
   double2* twp64_x = nullptr;  // fp64 root tables (every context: the energy kernels transform in fp64)
   double2* twp64_y = nullptr;
-  double4* kx64[4] = {nullptr, nullptr, nullptr, nullptr};
-  double2* ky64[4] = {nullptr, nullptr, nullptr, nullptr};
+  double4* kx64_real[2] = {nullptr, nullptr};
+  double2* ky64_real[2] = {nullptr, nullptr};
+  double2* kx64_imag[2] = {nullptr, nullptr};
+  double* ky64_imag[2] = {nullptr, nullptr};
   double* hbx64 = nullptr;  // dt * Omega_x(x_j) / 2
   double* hby64 = nullptr;  // dt * Omega_y(y_i) / 2
   double4* scratch_q64 = nullptr;  // staging of complex128 inputs (annealing noise)
@@ -96,7 +100,7 @@ sgpe_status apply_schedule(sgpe_ctx* c, const sgpe_schedule& s);   // validated;
 sgpe_schedule get_schedule(const sgpe_ctx* c);
 // Row-pass arguments with the real-space coefficients of a sub-step h (h <= 0: h = dt).
 sgpe::RowArgs row_args(const sgpe_ctx* c, double h = 0.0);
-sgpe::ColArgs col_args(const sgpe_ctx* c, bool imag, bool half);
+sgpe::ColArgs col_args(const sgpe_ctx* c, bool half);
 // Real-time line passes: an op of K(dt/2) or K(dt) along the line, or none.
 enum LineOp { LINE_NONE, LINE_HALF, LINE_FULL };
 sgpe::LineArgs line_args(const sgpe_ctx* c, bool col, LineOp pre, LineOp post, int n_r, double h_sub = 0.0);

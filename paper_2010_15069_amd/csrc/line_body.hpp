@@ -116,8 +116,7 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
     if (stage == 0) {
 #pragma unroll 1
       for (int r = 0; r < a.n_r; ++r) {
-        if constexpr (NLN) row_apply_r_nln<N, false, FULL>(v, a, line, t, comp == 0, hb_line, hb_cross, s * s);
-        else row_apply_r<N, false, FULL>(v, a, line, t, comp == 0, hb_line, hb_cross, s * s);
+        row_apply_r<N, false, FULL, NLN>(v, a, line, t, comp == 0, hb_line, hb_cross, s * s);
       }
     }
   }

@@ -4,6 +4,8 @@
 // itself -- inverse x-FFT, scale, R, forward x-FFT -- shared by every kernel that runs rows.
 #pragma once
 
+#include <type_traits>
+
 #include "fft_device.hpp"
 #include "sgpe_internal.hpp"
 
@@ -83,20 +85,28 @@ struct RCoef {
 };
 
 // Diagonal R (no spatial Raman coupling): w exp(-ph) in imaginary time, w exp(-i ph) in real
-// time, with ph = h (V + g_own n_own + g_ud n_other +- delta/2).  The real-time form is
-// w + w (cm1 - i s), the small correction formed first.
+// time, with ph = h (V + g_own n_own + g_ud n_other +- delta/2).  Both are applied as w plus a small
+// correction formed first.  SMALL: |ph| <= angle_limit; the general forms choose by the angle and give
+// the same bits for small ones, so results do not depend on a wave's vote.
+template <bool IMAG, class T>
+constexpr T angle_limit() { return IMAG ? T(kSmallExp) : T(kSmallPhase); }
+
 template <bool IMAG, bool SMALL, class C, class T>
 __device__ __forceinline__ C apply_r_diag(C w, T ph) {
   if constexpr (!IMAG) {
     const auto sc = sincos_m1_t<SMALL>(ph);
     return mk2(w.x + fma_(w.x, sc.cm1, w.y * sc.s), w.y + fma_(w.y, sc.cm1, -w.x * sc.s));
   } else {
+    if (SMALL || fabs_(ph) <= angle_limit<IMAG, T>()) {
+      const T e = expm1_small(-ph);
+      return mk2(fma_(w.x, e, w.x), fma_(w.y, e, w.y));
+    }
     return vscale(w, exp_(-ph));
   }
 }
 
 // Full 2x2 R: H_R = A 1 + Bx sigma_x + Bz sigma_z (all times h).  The angles (A, |B|) of this
-// point, for the wave's choice of routine.
+// point.
 template <class T>
 struct RFull {
   T ha, hbz, th;
@@ -113,11 +123,20 @@ __device__ __forceinline__ RFull<T> r_full_angles(T n_own, T n_oth, T hv, const 
   f.th = sqrt_(fma_(hbx, hbx, f.hbz * f.hbz));
   return f;
 }
-// Whether the SMALL routines are valid for this point.
-template <bool IMAG, class T>
-__device__ __forceinline__ bool r_full_small(const RFull<T>& f) {
-  if constexpr (!IMAG) return fabs_(f.ha) <= T(kSmallPhase) && f.th <= T(kSmallPhase);
-  else return f.th < T(0.25);
+
+// cosh(th) and sinh(th) / th by Taylor polynomials for th below this
+constexpr float kSmallHyp = 0.25f;
+__device__ __forceinline__ void hyp_small(float th, float& ch, float& shc) {
+  const float t2 = th * th;
+  ch = fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, 2.48015873e-5f, 1.38888889e-3f), 4.16666667e-2f), 0.5f), 1.0f);
+  shc = fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, 2.75573192e-6f, 1.98412698e-4f), 8.33333333e-3f), 1.66666667e-1f), 1.0f);
+}
+__device__ __forceinline__ void hyp_small(double th, double& ch, double& shc) {
+  const double t2 = th * th;
+  ch = fma(t2, fma(t2, fma(t2, fma(t2, fma(t2, fma(t2, 1.0 / 479001600.0, 1.0 / 3628800.0), 1.0 / 40320.0),
+                                   1.0 / 720.0), 1.0 / 24.0), 0.5), 1.0);
+  shc = fma(t2, fma(t2, fma(t2, fma(t2, fma(t2, fma(t2, 1.0 / 6227020800.0, 1.0 / 39916800.0), 1.0 / 362880.0),
+                                    1.0 / 5040.0), 1.0 / 120.0), 1.0 / 6.0), 1.0);
 }
 
 template <bool IMAG, bool SMALL, class C, class T>
@@ -135,28 +154,19 @@ __device__ __forceinline__ C apply_r_full(C w, C o, const RFull<T>& f, T hbx, T 
     const T ci = fma_(-se.s, w.x, fma_(se.cm1, w.y, fma_(-se.s, mr, fma_(se.cm1, mi, mi))));
     return mk2(w.x + cr, w.y + ci);
   } else {
-    const T ea = exp_(-f.ha);
-    T ch, shc;  // cosh(th), sinh(th)/th
-    if constexpr (sizeof(T) == 8) {
+    T ea, ch, shc;  // exp(-A), cosh(th), sinh(th)/th
+    if (SMALL || fabs_(f.ha) <= angle_limit<IMAG, T>()) ea = T(1) + expm1_small(-f.ha);
+    else ea = exp_(-f.ha);
+    if (SMALL || f.th < T(kSmallHyp)) {
+      hyp_small(f.th, ch, shc);
+    } else if constexpr (sizeof(T) == 8) {
       ch = cosh(f.th);
-      shc = f.th > 1e-4 ? sinh(f.th) / f.th : fma(f.th * f.th, 1.0 / 6.0, 1.0);   // next term th^4/120
-    } else if constexpr (SMALL) {
-      const float t2 = f.th * f.th;
-      ch = fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, 2.48015873e-5f, 1.38888889e-3f), 4.16666667e-2f), 0.5f), 1.0f);
-      shc = fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, 2.75573192e-6f, 1.98412698e-4f), 8.33333333e-3f),
-                           1.66666667e-1f), 1.0f);
+      shc = sinh(f.th) / f.th;
     } else {
-      if (f.th < 0.25f) {
-        const float t2 = f.th * f.th;
-        ch = fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, 2.48015873e-5f, 1.38888889e-3f), 4.16666667e-2f), 0.5f), 1.0f);
-        shc = fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, 2.75573192e-6f, 1.98412698e-4f), 8.33333333e-3f),
-                             1.66666667e-1f), 1.0f);
-      } else {
-        const float ep = expf(f.th);
-        const float em = 1.0f / ep;
-        ch = 0.5f * (ep + em);
-        shc = 0.5f * (ep - em) / f.th;
-      }
+      const float ep = expf(f.th);
+      const float em = 1.0f / ep;
+      ch = 0.5f * (ep + em);
+      shc = 0.5f * (ep - em) / f.th;
     }
     const T m_own = ea * fma_(-sgn * shc, f.hbz, ch);
     const T m_x = -ea * shc * hbx;
@@ -165,15 +175,11 @@ __device__ __forceinline__ C apply_r_full(C w, C o, const RFull<T>& f, T hbx, T 
 }
 
 // -------------------------------------------------------------------------------------------
-// Row pass
+// R on the thread's points
 // -------------------------------------------------------------------------------------------
-// R on the thread's 16 points.  For each point index the wave takes one routine: the short one
-// when every lane's angles allow it (the common case), else the general one -- a wave-uniform
-// branch, so a wave never runs both.
-// hbx_r: this lane's h Omega_x / 2 at its P positions, hb_row: h Omega_y / 2 of the row (full
-// 2x2 variant only; loaded by the caller ahead of the transforms).  A: any argument struct with the
-// real-space fields of RowArgsT (x along the line the lane holds, y across).  gs: the square of the
-// scale that v still lacks (a power of two, so folding it into the couplings is exact).
+// A: any argument struct with the real-space fields of RowArgsT (x along the line the lane holds, y
+// across).  gs: the square of the scale that v still lacks (a power of two, so folding it into the
+// couplings is exact).
 template <class R, class A>
 __device__ __forceinline__ RCoef<R> r_coefs(const A& a, bool up, R gs) {
   RCoef<R> c;
@@ -187,76 +193,122 @@ __device__ __forceinline__ RCoef<R> r_coefs(const A& a, bool up, R gs) {
   return c;
 }
 
-template <int N, bool IMAG, bool FULL, int P, class C, class R, class A>
+// Imaginary time: whether the SMALL routines hold for every point of the wave, from bounds: the
+// potential at the ends of the line, the largest density of the lane's points, the largest coupling.
+// The bounds are sums of maxima over different points, and a wave that they send the general way gets
+// the same bits.
+template <bool FULL, bool NLN, int P, class C, class R, class A>
+__device__ __forceinline__ bool small_angles(const C (&v)[P], const A& a, const RCoef<R>& c, R hvy,
+                                             const R (&hbx_r)[P], R hb_row) {
+  R n = R(0);
+#pragma unroll
+  for (int m = 0; m < P; ++m) n = fmax_(n, fmax_(fabs_(v[m].x), fabs_(v[m].y)));
+  n = R(2) * n * n;   // at least the largest density (and no density that R would want to keep)
+  n += pair_swap(n);
+  const R g = fmax_(fmax_(fabs_(c.hg_uu), fabs_(c.hg_dd)), fabs_(c.hg_ud)) * n;
+  const R pot = fma_(a.hvx * a.x0, a.x0, hvy), det = fabs_(a.hdelta2);
+  R angle = NLN ? (FULL ? pot : pot + det) : (FULL ? pot + g : pot + det + g);
+  // the second mean-field factor of N L N sees densities that L has changed, by less than
+  // exp(2 (0.35 + 0.25)) < 4 below the limits
+  if constexpr (NLN) angle = fmax_(angle, R(2) * g);
+  bool ok = angle <= R(kSmallExp);
+  if constexpr (FULL) {
+    R b = R(0);
+#pragma unroll
+    for (int m = 0; m < P; ++m) b = fmax_(b, fabs_(hbx_r[m]));
+    b += fabs_(hb_row) + det + (NLN ? R(0) : g);
+    ok = ok && b <= R(0.99f * kSmallHyp);
+  }
+  return wave_all(ok);
+}
+
+// hbx_r: this lane's h Omega_x / 2 at its P positions, hb_row: h Omega_y / 2 of the row (full
+// 2x2 variant only; loaded by the caller ahead of the transforms).  NLN: R(h) split to second order as
+// N(h/2) L(h) N(h/2), the mean-field phase with the densities of its input, the exponential of the
+// linear real-space terms (trap, detuning, spatial coupling), the mean-field phase again with the
+// updated densities.
+//
+// A wave takes the SMALL routines or the general ones by a vote of its lanes.  Real time votes per
+// point and factor.  Imaginary time votes once for all points, so that the small forms are one straight
+// line without branches, whose points fill each other's dependency chains (full 2x2 row pass at 2048^2:
+// with the polynomial exp, 68 -> 52 us; one vote in real time was 2-4 % slower than sixteen).
+template <int N, bool IMAG, bool FULL, bool NLN, int P, class C, class R, class A>
 __device__ __forceinline__ void row_apply_r(C (&v)[P], const A& a, int row, int t, bool up,
                                             const R (&hbx_r)[P], R hb_row, R gs = R(1)) {
   const LanePos<N / P> pos = real_pos<N, P>(t);
   const RCoef<R> c = r_coefs(a, up, gs);
   const R y = fma_(static_cast<R>(row), a.dy, a.y0);
   const R hvy = a.hvy * y * y;
-#pragma unroll
-  for (int m = 0; m < P; ++m) {
-    const int j = pos.at(m);
-    const R x = fma_(static_cast<R>(j), a.dx, a.x0);
-    const R hv = fma_(a.hvx * x, x, hvy);
-    const R n_own = fma_(v[m].x, v[m].x, v[m].y * v[m].y);
-    if constexpr (!FULL) {
+  auto apply = [&](auto small) {
+    constexpr bool SMALL = decltype(small)::value;
+    // Opaque to the compiler: the terms that depend on the position alone would else be formed once
+    // for both forms (and once for all sub-steps of a pass) and held, a register each per point.
+    R hv0 = hvy, j0 = static_cast<R>(pos.p0), jb = static_cast<R>(pos.b), hb0 = hb_row;
+    if constexpr (IMAG || NLN) asm volatile("; %4" : "+v"(hv0), "+v"(j0), "+v"(jb), "+v"(hb0) : "i"(int(SMALL)));
+    auto diag = [&](C w, R ph) {
+      if constexpr (!IMAG) {
+        if (wave_all(fabs_(ph) <= angle_limit<IMAG, R>())) return apply_r_diag<IMAG, true>(w, ph);
+      }
+      return apply_r_diag<IMAG, SMALL>(w, ph);
+    };
+    auto half_n = [&](C w) {
+      const R n_own = fma_(w.x, w.x, w.y * w.y);
       const R n_oth = pair_swap(n_own);
-      const R ph = fma_(c.hg_own, n_own, fma_(c.hg_ud, n_oth, hv + c.hd_own));
-      if (IMAG || wave_all(fabs_(ph) <= R(kSmallPhase))) v[m] = apply_r_diag<IMAG, true>(v[m], ph);
-      else v[m] = apply_r_diag<IMAG, false>(v[m], ph);
-    } else {
-      const R hbx = hbx_r[m] + hb_row;
-      const C o = pair_swap(v[m]);
-      const R n_oth = fma_(o.x, o.x, o.y * o.y);
-      const RFull<R> f = r_full_angles(n_own, n_oth, hv, c, hbx);
-      if (wave_all(r_full_small<IMAG>(f))) v[m] = apply_r_full<IMAG, true>(v[m], o, f, hbx, c.sgn);
-      else v[m] = apply_r_full<IMAG, false>(v[m], o, f, hbx, c.sgn);
-    }
-  }
-}
-
-// R(h) split to second order as N(h/2) L(h) N(h/2): the mean-field phase with the densities of
-// its input, the exponential of the linear real-space terms (trap, detuning, spatial coupling),
-// the mean-field phase again with the updated densities.  Coefficients as in row_apply_r.
-template <int N, bool IMAG, bool FULL, int P, class C, class R, class A>
-__device__ __forceinline__ void row_apply_r_nln(C (&v)[P], const A& a, int row, int t, bool up,
-                                                const R (&hbx_r)[P], R hb_row, R gs = R(1)) {
-  const LanePos<N / P> pos = real_pos<N, P>(t);
-  const RCoef<R> c = r_coefs(a, up, gs);
-  const R y = fma_(static_cast<R>(row), a.dy, a.y0);
-  const R hvy = a.hvy * y * y;
-  auto half_n = [&](C w) {
-    const R n_own = fma_(w.x, w.x, w.y * w.y);
-    const R n_oth = pair_swap(n_own);
-    const R ph = R(0.5) * fma_(c.hg_own, n_own, c.hg_ud * n_oth);
-    if (IMAG || wave_all(fabs_(ph) <= R(kSmallPhase))) return apply_r_diag<IMAG, true>(w, ph);
-    return apply_r_diag<IMAG, false>(w, ph);
-  };
+      return diag(w, R(0.5) * fma_(c.hg_own, n_own, c.hg_ud * n_oth));
+    };
 #pragma unroll
-  for (int m = 0; m < P; ++m) {
-    const int j = pos.at(m);
-    const R x = fma_(static_cast<R>(j), a.dx, a.x0);
-    const R hv = fma_(a.hvx * x, x, hvy);
-    C w = half_n(v[m]);
-    if constexpr (!FULL) {
-      const R ph = hv + c.hd_own;
-      if (IMAG || wave_all(fabs_(ph) <= R(kSmallPhase))) w = apply_r_diag<IMAG, true>(w, ph);
-      else w = apply_r_diag<IMAG, false>(w, ph);
-    } else {
-      const R hbx = hbx_r[m] + hb_row;
-      const C o = pair_swap(w);
-      RFull<R> f;
-      f.ha = hv;
-      f.hbz = c.hdelta2;
-      f.th = sqrt_(fma_(hbx, hbx, f.hbz * f.hbz));
-      if (wave_all(r_full_small<IMAG>(f))) w = apply_r_full<IMAG, true>(w, o, f, hbx, c.sgn);
-      else w = apply_r_full<IMAG, false>(w, o, f, hbx, c.sgn);
+    for (int m = 0; m < P; ++m) {
+      if constexpr (IMAG && !SMALL) {
+        // a branch the compiler cannot fold keeps it from running the general form of all points
+        // side by side, which takes every register there is (240 VGPRs and up, where the small form
+        // takes 168)
+        int go = 1;
+        asm volatile("" : "+s"(go));
+        if (go == 0) continue;
+      }
+      const R x = fma_(m == 0 ? j0 : jb + R(N / P * m), a.dx, a.x0);   // the position is exact
+      const R hv = fma_(a.hvx * x, x, hv0);
+      C w = v[m];
+      if constexpr (NLN) w = half_n(w);
+      if constexpr (!FULL) {
+        R ph = hv + c.hd_own;
+        if constexpr (!NLN) {
+          const R n_own = fma_(w.x, w.x, w.y * w.y);
+          const R n_oth = pair_swap(n_own);
+          ph = fma_(c.hg_own, n_own, fma_(c.hg_ud, n_oth, ph));
+        }
+        w = diag(w, ph);
+      } else {
+        const R hbx = hbx_r[m] + hb0;
+        const C o = pair_swap(w);
+        RFull<R> f;
+        if constexpr (NLN) {
+          f.ha = hv;
+          f.hbz = c.hdelta2;
+          f.th = sqrt_(fma_(hbx, hbx, f.hbz * f.hbz));
+        } else {
+          f = r_full_angles(fma_(w.x, w.x, w.y * w.y), fma_(o.x, o.x, o.y * o.y), hv, c, hbx);
+        }
+        if (!IMAG && wave_all(fabs_(f.ha) <= R(kSmallPhase) && f.th <= R(kSmallPhase)))
+          w = apply_r_full<IMAG, true>(w, o, f, hbx, c.sgn);
+        else
+          w = apply_r_full<IMAG, SMALL>(w, o, f, hbx, c.sgn);
+      }
+      if constexpr (NLN) w = half_n(w);
+      v[m] = w;
     }
-    v[m] = half_n(w);
+  };
+  if constexpr (IMAG) {
+    if (small_angles<FULL, NLN>(v, a, c, hvy, hbx_r, hb_row)) apply(std::true_type{});
+    else apply(std::false_type{});
+  } else {
+    apply(std::false_type{});
   }
 }
 
+// -------------------------------------------------------------------------------------------
+// Row pass
+// -------------------------------------------------------------------------------------------
 // A workgroup handles ITERS groups of rows_per_block rows, one after the other; the next group's
 // data is loaded into registers before the current group is transformed, so its memory latency
 // hides behind this group's arithmetic.  P points per lane: T = N / P lanes per transform.
@@ -329,13 +381,9 @@ __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
       }
 #pragma unroll
       for (int m = 0; m < P; ++m) v[m] = vscale(v[m], s);
-      if constexpr (MODE == ROW_STEP_NLN) {
-        row_apply_r_nln<N, IMAG, FULL>(v, a, row0 + it * a.rows_per_block, t, comp == 0, hbx_r,
-                                       FULL ? hby_r[it] : R(0));
-        fwd_pass<N>(v, lds, t, tr);
-      } else if constexpr (MODE == ROW_STEP) {
-        row_apply_r<N, IMAG, FULL>(v, a, row0 + it * a.rows_per_block, t, comp == 0, hbx_r,
-                                   FULL ? hby_r[it] : R(0));
+      if constexpr (STEP) {
+        row_apply_r<N, IMAG, FULL, MODE == ROW_STEP_NLN>(v, a, row0 + it * a.rows_per_block, t, comp == 0, hbx_r,
+                                                         FULL ? hby_r[it] : R(0));
         fwd_pass<N>(v, lds, t, tr);
       }
     }
@@ -391,8 +439,8 @@ __device__ __forceinline__ void row_var_body(const RowArgs& a, int wg) {
     for (int m = 0; m < P; ++m) v[m] = vscale(v[m], s);
   }
   for (int r = 0; r < a.var_r; ++r) {
-    if (a.var_nln) row_apply_r_nln<N, IMAG, FULL>(v, a, row, t, comp == 0, hbx_r, hb_row);
-    else row_apply_r<N, IMAG, FULL>(v, a, row, t, comp == 0, hbx_r, hb_row);
+    if (a.var_nln) row_apply_r<N, IMAG, FULL, true>(v, a, row, t, comp == 0, hbx_r, hb_row);
+    else row_apply_r<N, IMAG, FULL, false>(v, a, row, t, comp == 0, hbx_r, hb_row);
     if (mid && r == 0) {
       const float c = row_scale(a, pv);
       check_scale(a, c, wg);

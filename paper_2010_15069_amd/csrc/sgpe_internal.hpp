@@ -83,8 +83,9 @@ struct ColArgsT {
   int nx, ny;
   int cols;                  // columns per workgroup
   const cplx_t<T>* tw;       // the same for ny
-  const point_t<T>* kx_tab;  // per k_x: {d11, d12} {d21, d22} as complex (M'(k_x) - 1)
-  const cplx_t<T>* ky_tab;   // per k_y: P(k_y) - 1
+  // imaginary time: M'(k_x) and P(k_y) are real
+  const cplx_t<T>* kx_tab;   // per k_x and component: its row of M'(k_x) - 1 as {own, other}
+  const T* ky_tab;           // per k_y: P(k_y) - 1
   double* partials;          // one double per workgroup (norm modes)
 };
 using ColArgs = ColArgsT<float>;
@@ -100,8 +101,8 @@ struct LineArgsT {
   int nx;                    // row length of the state in memory
   int lines;                 // lines (rows or columns) per workgroup
   const cplx_t<T>* tw;       // RowArgsT::tw for the line's length
-  const void* op_pre;        // M' - 1 as in ColArgsT::kx_tab (rows) or P - 1 as in ky_tab (columns);
-  const void* op_post;       //   NULL: that op is not applied
+  const void* op_pre;        // rows: per k_x and component its row of M'(k_x) - 1, {own, other} complex
+  const void* op_post;       //   (point_t); columns: P(k_y) - 1, complex (cplx_t); NULL: not applied
   int n_r;                   // real-space sub-steps R(h) in turn (0, 1 or 2)
   T x0, dx, y0, dy;
   T hvx, hvy;
