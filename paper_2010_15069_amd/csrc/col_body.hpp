@@ -117,8 +117,14 @@ __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngrou
       v[m] = res;
     }
 
+    // The sum is complete here: left to the compiler, its additions move behind the inverse transform
+    // and the products wait there in two registers each (1024 points: 152 VGPRs instead of 114, two
+    // waves per SIMD less at 2048 points).
+    if constexpr (NORM != NORM_NONE) asm volatile("" : "+v"(acc));
+
     inv_pass<N>(v, lds, t, tr);
 
+    if constexpr (many_waves<WT, N>()) forget(off);
 #pragma unroll
     for (int m = 0; m < P; ++m) store_state<WT>(reinterpret_cast<CX*>(out + (off + row_off(m))), v[m]);
     if (it + 1 < ITERS) {

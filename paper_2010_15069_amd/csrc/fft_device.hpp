@@ -87,6 +87,17 @@ __device__ __forceinline__ void store_state(C* p, C v) {
   }
 }
 
+// Makes the compiler form anew what it would derive from x, instead of holding what it derived earlier
+// across the transforms: the offsets of a pass's loads, wanted again by its stores, take a register per
+// point.  Worth it where the registers decide how many waves are resident (row pass at 16 points per
+// lane: 142 -> 122 VGPRs, 168 -> 138 with a spatial Raman coupling; column pass 126 -> 96): batches,
+// complex128 and lines of 2048 points and more (24-instance sweep 15.0 -> 14.7 ms, complex128 at 1024^2
+// 42.4 -> 40.5 us per step, 2048^2 90.0 -> 88.5).  A single complex64 grid of shorter lines is resident
+// as a whole either way, and the offsets then only delay its stores (1024^2: 23.4 -> 23.8 us per step).
+template <bool WT, int N>
+constexpr bool many_waves() { return !WT || N >= 2048; }
+__device__ __forceinline__ void forget(uint32_t& x) { asm volatile("" : "+v"(x)); }
+
 // ---------------------------------------------------------------------------------------------
 // Batched launches (grid x = work items of one instance, grid y = instances).  The dispatcher
 // deals a launch's workgroups to the eight XCDs in turn, by linear workgroup index (x fastest),
@@ -733,9 +744,30 @@ __device__ __forceinline__ bool wave_all(bool p) { return __builtin_amdgcn_ballo
 // ---------------------------------------------------------------------------------------------
 // Deterministic reductions in fp64.
 // ---------------------------------------------------------------------------------------------
+// Across the wave without LDS traffic: lanes 1, 2, 4 and 8 apart by DPP permutations, rows of 16 and
+// halves by the permlane swaps (shuffles through LDS cost two trips of ~100 cycles per step).  Every
+// lane ends with the same bits: each step adds the two halves of a group, whichever half a lane is in.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  v += dpp_move<0xB1>(v);    // quad_perm [1,0,3,2]
+  v += dpp_move<0x4E>(v);    // quad_perm [2,3,0,1]
+  v += dpp_move<0x141>(v);   // row_half_mirror: the other quad of eight lanes
+  v += dpp_move<0x140>(v);   // row_mirror: the other eight lanes of the row
+  {
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  }
+  {
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  }
   return v;
 }
 

@@ -46,7 +46,7 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
   }
   const LdsView<C> lds = lds_line<N, C>(line_lds, lane_line, a.lines, comp);
   const LanePos<T> rp = real_pos<N, P>(t), sp = spec_pos<N, P>(t);
-  const uint32_t off0 = off + static_cast<uint32_t>(rp.p0) * pstride, offb = off + static_cast<uint32_t>(rp.b) * pstride;
+  uint32_t off0 = off + static_cast<uint32_t>(rp.p0) * pstride, offb = off + static_cast<uint32_t>(rp.b) * pstride;
   const uint32_t mstride = static_cast<uint32_t>(T) * pstride;
   const char* __restrict__ base = reinterpret_cast<const char*>(a.psi);
   char* __restrict__ out = reinterpret_cast<char*>(a.psi);
@@ -119,6 +119,10 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
         row_apply_r<N, false, FULL, NLN>(v, a, line, t, comp == 0, hb_line, hb_cross, s * s);
       }
     }
+  }
+  if constexpr (many_waves<WT, N>() || N >= 1024) {   // (1024^2: 16.5 -> 16.2 us per step)
+    forget(off0);
+    forget(offb);
   }
 #pragma unroll
   for (int m = 0; m < P; ++m)

@@ -15,12 +15,12 @@ namespace sgpe {
 // -------------------------------------------------------------------------------------------
 // Sum of the previous column pass's partials -> scale for the row pass.  Every wave computes
 // the same sum in the same order (lane l adds partials l, l + 64, ... in turn, then a fixed
-// butterfly across the wave), so every workgroup applies bit-identical scales.  Up to 64 K
-// partials are loaded at kernel start as K masked loads per lane, ahead of the data (a
-// runtime-length loop of loads would make the wave wait for every outstanding load); more
-// partials, or workgroups narrower than a wave, take the loop after the inverse transform.
-// K = 4 (256 partials), and 16 (1024) for complex128 rows of up to 1024 points, whose 1-column
-// tiles leave nx partials.
+// butterfly across the wave), so every workgroup applies bit-identical scales.  Up to 64 K partials
+// are loaded at kernel start as masked loads, ahead of the data, and summed while the data is on its
+// way; more, or workgroups narrower than a wave, take a loop behind the data's loads.
+// K = 4 (256 partials: one per compute unit), and 16 (1024) for complex128 rows of up to 1024 points,
+// whose 1-column tiles leave nx partials.  (16 everywhere: 18 VGPRs more in the row passes, of which
+// the full 2x2 one at 2048 points would then keep two waves per SIMD instead of three.)
 // -------------------------------------------------------------------------------------------
 template <class R, int N>
 constexpr int prefetch_per_lane() { return sizeof(R) == 8 && N <= 1024 ? 16 : 4; }
@@ -28,14 +28,13 @@ constexpr int prefetch_per_lane() { return sizeof(R) == 8 && N <= 1024 ? 16 : 4;
 template <class A, int K>
 __device__ __forceinline__ void prefetch_partials(const A& a, double (&pv)[K]) {
   const int lane = threadIdx.x & 63;
-  // a uniform branch around unconditional loads (indices clamped into range; the surplus
+  // uniform branches around unconditional loads (indices clamped into range; the surplus
   // masked out at the sum), so no lane-dependent control flow waits on a load
-  if (a.partials != nullptr && a.n_partials <= 64 * K && blockDim.x >= 64) {
+  const bool early = a.partials != nullptr && a.n_partials <= 64 * K && blockDim.x >= 64;
 #pragma unroll
-    for (int k = 0; k < K; ++k) pv[k] = a.partials[min(lane + 64 * k, a.n_partials - 1)];
-  } else {
-#pragma unroll
-    for (int k = 0; k < K; ++k) pv[k] = 0.0;
+  for (int k = 0; k < K; ++k) {
+    pv[k] = 0.0;
+    if (early && 64 * k < a.n_partials) pv[k] = a.partials[min(lane + 64 * k, a.n_partials - 1)];
   }
 }
 
@@ -44,13 +43,19 @@ __device__ __forceinline__ decltype(A::scale) row_scale(const A& a, const double
   if (a.partials == nullptr) return a.scale;
   double s = 0.0;
   if (blockDim.x >= 64) {
+    const int lane = threadIdx.x & 63;
     if (a.n_partials <= 64 * K) {
-      const int lane = threadIdx.x & 63;
 #pragma unroll
       for (int k = 0; k < K; ++k) s += (lane + 64 * k < a.n_partials) ? pv[k] : 0.0;
     } else {
-      const int lane = threadIdx.x & 63;
-      for (int i = lane; i < a.n_partials; i += 64) s += a.partials[i];
+      // eight loads in flight at a time (a loop of load and add waits for each)
+      for (int i0 = 0; i0 < a.n_partials; i0 += 512) {
+        double q[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) q[k] = a.partials[min(i0 + 64 * k + lane, a.n_partials - 1)];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += i0 + 64 * k + lane < a.n_partials ? q[k] : 0.0;
+      }
     }
     s = wave_sum(s);
   } else {
@@ -360,7 +365,12 @@ __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) hby_r[it] = a.hby[row0 + it * a.rows_per_block];
   }
+  // the norm's sum, square root and division while the state's loads are in flight
   R s = R(1);
+  if constexpr (MODE != ROW_FWD) {
+    s = row_scale(a, pv);
+    check_scale(a, s, wg);
+  }
 
 #pragma unroll
   for (int it = 0; it < ITERS; ++it) {
@@ -375,10 +385,6 @@ __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
       fwd_pass<N>(v, lds, t, tr);
     } else {
       inv_pass<N>(v, lds, t, tr);
-      if (it == 0) {
-        s = row_scale(a, pv);
-        check_scale(a, s, wg);
-      }
 #pragma unroll
       for (int m = 0; m < P; ++m) v[m] = vscale(v[m], s);
       if constexpr (STEP) {
@@ -387,6 +393,7 @@ __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
         fwd_pass<N>(v, lds, t, tr);
       }
     }
+    if constexpr (many_waves<WT, N>()) forget(off);
 #pragma unroll
     for (int m = 0; m < P; ++m) store_state<WT>(reinterpret_cast<C*>(out + (off + PB * to.at(m))), v[m]);
     if (it + 1 < ITERS) {
@@ -431,10 +438,11 @@ __device__ __forceinline__ void row_var_body(const RowArgs& a, int wg) {
     hb_row = a.hby[row] * a.hfrac;
   }
   const bool mid = (flags & VAR_MID_SCALE) != 0;
+  const float norm_scale = row_scale(a, pv);
+  check_scale(a, norm_scale, wg);
   if (flags & (VAR_INV | VAR_SCALE)) {
     if (flags & VAR_INV) inv_pass<N>(v, lds, t, tr);
-    const float s = mid ? a.scale : row_scale(a, pv);
-    if (!mid) check_scale(a, s, wg);
+    const float s = mid ? a.scale : norm_scale;
 #pragma unroll
     for (int m = 0; m < P; ++m) v[m] = vscale(v[m], s);
   }
@@ -442,10 +450,8 @@ __device__ __forceinline__ void row_var_body(const RowArgs& a, int wg) {
     if (a.var_nln) row_apply_r<N, IMAG, FULL, true>(v, a, row, t, comp == 0, hbx_r, hb_row);
     else row_apply_r<N, IMAG, FULL, false>(v, a, row, t, comp == 0, hbx_r, hb_row);
     if (mid && r == 0) {
-      const float c = row_scale(a, pv);
-      check_scale(a, c, wg);
 #pragma unroll
-      for (int m = 0; m < P; ++m) v[m] = vscale(v[m], c);
+      for (int m = 0; m < P; ++m) v[m] = vscale(v[m], norm_scale);
     }
   }
   if (flags & VAR_NORM_OUT) {
