@@ -186,23 +186,32 @@ void k_tables_imag(const sgpe_params& p, double h, std::vector<sgpe::cplx_t<T>>&
   }
 }
 
-// Default schedule (from measured sweeps on MI355X).  Points per lane: 16 where the grid alone
-// fills the device; on small grids fewer points per lane (more lanes, a shorter instruction
-// stream per lane) cut each pass's latency.  Row prefetching (two row groups per workgroup) pays
-// only for small rows whose one-group grid is a single round of resident workgroups (two per
-// compute unit): then nothing else would overlap the first loads and last stores.  Column
-// prefetching needs the narrower tile and measured slower everywhere; it stays off by default.
-int default_points(int n, size_t npts) {
+// Default points per lane for lines of length n (from measured sweeps on MI355X; us per step).  More
+// points per lane are fewer instructions per point and fewer waves.
+// * 4 on small grids, where a pass is one lane's chain of latencies: rows below 2^18 points, columns
+//   below 2^17 (8 instances of 128^2: 12.0 imaginary / 8.1 real with 4 and 8, 12.8 / 9.8 with 8 and 8).
+// * 8 below 2^20 points (1024 x 512: 15.6 / 11.0 with 8, 17.9 / 13.2 with 16; 512 x 1024: 18.4 / 12.2
+//   against 20.3 / 14.7).
+// * From there 16 on long lines (1024^2: 23.3 / 16.4; 8 and 8: 26.4 / 18.4), 8 on rows up to 256 points
+//   (256 x 2048: 24.2 / 16.5 against 25.1 / 17.6) and columns up to 512 (2048 x 256: 16.3 / 11.8
+//   against 17.1 / 12.8; 8 instances of 512^2: 37.1 / 29.8 against 38.1 / 33.2), whose shorter
+//   transforms hold fewer registers at 8 without a third exchange more.
+// Row prefetching (two row groups per workgroup) pays only for small rows whose one-group grid is a
+// single round of resident workgroups (two per compute unit): then nothing else would overlap the first
+// loads and last stores.  Column prefetching needs the narrower tile and measured slower everywhere; it
+// stays off by default.
+int default_points(int n, size_t npts, bool col) {
   if (n > sgpe::kMaxNSmallP) return 16;
-  if (npts >= (size_t(1) << 19)) return 16;
-  return npts >= (size_t(1) << 17) ? 8 : 4;
+  if (npts < (size_t(1) << (col ? 17 : 18))) return 4;
+  if (npts < (size_t(1) << 20)) return 8;
+  return n <= (col ? 512 : 256) ? 8 : 16;
 }
 
 void default_schedule(sgpe_ctx* c) {
   const int nx = c->p.nx, ny = c->p.ny;
   const size_t npts = size_t(nx) * size_t(ny);
-  c->row_points = default_points(nx, npts);
-  c->col_points = default_points(ny, npts);
+  c->row_points = default_points(nx, npts, false);
+  c->col_points = default_points(ny, npts, true);
   c->rows = sgpe::row_rows_per_block(nx, ny, c->row_points, c->max_lds);
   c->cols = sgpe::col_default_cols(nx, ny, c->col_points, c->max_lds);
   c->row_iters = 1;

@@ -320,8 +320,8 @@ sgpe_status set_class_schedule(sgpe_batch* b, BatchClass& k, const sgpe_schedule
 sgpe_schedule class_default(const sgpe_ctx* c0, size_t members) {
   const size_t total = members * size_t(c0->p.nx) * size_t(c0->p.ny);
   sgpe_schedule s{};   // row_tile 0: the default for the points per lane
-  s.row_points = default_points(c0->p.nx, total);
-  s.col_points = default_points(c0->p.ny, total);
+  s.row_points = default_points(c0->p.nx, total, false);
+  s.col_points = default_points(c0->p.ny, total, true);
   s.row_iters = 1;
   s.col_iters = 1;
   s.col_tile = sgpe::col_default_cols(c0->p.nx, c0->p.ny, s.col_points, c0->max_lds);

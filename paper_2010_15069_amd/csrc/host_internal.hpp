@@ -94,7 +94,7 @@ constexpr int kMaxPartials = 4096;   // norm partials per column pass (one per w
 sgpe_status dev_alloc(sgpe_ctx* c, void** ptr, size_t bytes);
 sgpe_status status_of(hipError_t e);
 void default_schedule(sgpe_ctx* c);
-int default_points(int n, size_t npts);   // points per lane for a transform of length n, npts points in all
+int default_points(int n, size_t npts, bool col);   // points per lane of rows (columns) of length n, npts points in all
 int col_groups(const sgpe_ctx* c);
 sgpe_status apply_schedule(sgpe_ctx* c, const sgpe_schedule& s);   // validated; EINVAL changes nothing
 sgpe_schedule get_schedule(const sgpe_ctx* c);
