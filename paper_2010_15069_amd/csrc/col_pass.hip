@@ -21,13 +21,16 @@ namespace sgpe {
 // One instance: workgroup blockIdx.x of the pass.  A batch of instances of one grid shape:
 // grid of (items, instances) read by batch_item (all of an instance on one XCD), the instance's
 // arguments from a device table.
+// Columns of 2048 points and more may run two schedule tiles side by side (see col_wide, api.cpp).
+constexpr int col_threads(int n, int iters) { return iters == 2 ? 256 : n >= 2048 ? 1024 : 512; }
+
 template <int N, int NORM, int ITERS, int P>
-__global__ void __launch_bounds__(ITERS == 2 ? 256 : 512) col_kernel(ColArgs a) {
+__global__ void __launch_bounds__(col_threads(N, ITERS)) col_kernel(ColArgs a) {
   col_body<N, NORM, ITERS, P, true>(a, blockIdx.x, gridDim.x);
 }
 
 template <int N, int NORM, int P>
-__global__ void __launch_bounds__(512) col_kernel_batch(const ColArgs* __restrict__ tab) {
+__global__ void __launch_bounds__(col_threads(N, 1)) col_kernel_batch(const ColArgs* __restrict__ tab) {
   const int2 w = batch_item();
   col_body<N, NORM, 1, P, false>(tab[w.x], w.y, gridDim.x);
 }
@@ -77,7 +80,7 @@ static hipError_t col_launch_n(const ColArgs& a, const ColArgs* tab, int count, 
 
 static hipError_t col_dispatch(const ColArgs& a, const ColArgs* tab, int count, int norm, int iters, int points,
                                hipStream_t s) {
-  if (!schedule_supported(a.ny, a.cols, iters, points)) return hipErrorInvalidValue;
+  if (!col_launch_supported(a.ny, a.cols, iters, points)) return hipErrorInvalidValue;
   if (a.nx % (a.cols * iters) != 0) return hipErrorInvalidValue;
   if (tab && (iters != 1 || count < 1 || count > 65535)) return hipErrorInvalidValue;
   switch (a.ny) {

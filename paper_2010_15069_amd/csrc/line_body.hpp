@@ -120,7 +120,9 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
       }
     }
   }
-  if constexpr (!WT || N == 1024) {   // (1024^2: 16.5 -> 16.2 us per step; 2048 x 256: 13.6 -> 13.8 with it)
+  // (1024^2: 16.5 -> 16.2 us per step; rows of 2048 x 256: 13.6 -> 13.8 with it; wide column workgroups
+  // must stay within 128 VGPRs)
+  if constexpr (!WT || N == 1024 || (COL && !FULL && N >= 2048)) {
     forget(off0);
     forget(offb);
   }

@@ -21,13 +21,17 @@
 
 namespace sgpe {
 
+// threads of a workgroup: columns may run wide (col_wide, api.cpp) where the pass holds its registers at
+// four waves per SIMD, which it does with the diagonal real-space exponential
+constexpr int line_threads(int n, bool col, bool full) { return col && !full && n >= 2048 ? 1024 : 512; }
+
 template <int N, bool COL, bool FULL, bool NLN, int P>
-__global__ void __launch_bounds__(512) line_kernel(LineArgs a) {
+__global__ void __launch_bounds__(line_threads(N, COL, FULL)) line_kernel(LineArgs a) {
   line_body<N, COL, FULL, NLN, P, true>(a, blockIdx.x, gridDim.x);
 }
 
 template <int N, bool COL, bool FULL, int P>
-__global__ void __launch_bounds__(512) line_kernel_batch(const LineArgs* __restrict__ tab) {
+__global__ void __launch_bounds__(line_threads(N, COL, FULL)) line_kernel_batch(const LineArgs* __restrict__ tab) {
   const int2 w = batch_item();
   line_body<N, COL, FULL, false, P, false>(tab[w.x], w.y, gridDim.x);
 }
@@ -77,7 +81,8 @@ static hipError_t line_launch_n(const LineArgs& a, const LineArgs* tab, int coun
 template <bool COL>
 static hipError_t line_dispatch(const LineArgs& a, const LineArgs* tab, int count, int n, int n_lines, bool full,
                                 bool nln, int points, hipStream_t s) {
-  if (!schedule_supported(n, a.lines, 1, points) || n_lines % a.lines != 0) return hipErrorInvalidValue;
+  if (!(COL && !full ? col_launch_supported : schedule_supported)(n, a.lines, 1, points) || n_lines % a.lines != 0)
+    return hipErrorInvalidValue;
   if (tab && (count < 1 || count > 65535)) return hipErrorInvalidValue;
   switch (n) {
     case 16: return line_launch_n<16, COL>(a, tab, count, n_lines, full, nln, points, s);

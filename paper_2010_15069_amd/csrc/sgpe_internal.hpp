@@ -153,6 +153,12 @@ inline bool schedule_supported(int n, int groups, int iters, int points) {
   return threads <= (iters == 2 ? 256 : 512);
 }
 
+// Complex64 column launches of 2048 and 4096 points may hold twice the threads (col_wide, api.cpp).
+inline bool col_launch_supported(int n, int groups, int iters, int points) {
+  if (n >= 2048 && points == 16 && iters == 1 && 2 * groups * (n / points) == 1024) groups >>= 1;
+  return schedule_supported(n, groups, iters, points);
+}
+
 hipError_t launch_row(const RowArgs& a, int mode, bool imag, bool full2x2, int iters, int points, hipStream_t s);
 hipError_t launch_col(const ColArgs& a, int norm_mode, int iters, int points, hipStream_t s);
 // complex128: 16 or 8 points per lane (8 for lengths up to kMaxNSmallP), one row group / column

@@ -39,3 +39,21 @@ def test_every_length_and_points_per_lane(Solver, axis, n, points):
     g = s.set_psi(psi).step_real(2).step_imag(2).get_psi()
     err = np.linalg.norm(g - o.psi) / np.linalg.norm(o.psi)
     assert err <= 1e-6, err
+
+
+@pytest.mark.parametrize("nx,ny", [(1024, 2048), (512, 4096), (256, 2048)])
+@pytest.mark.parametrize("raman", [0.0, 1.5])
+def test_wide_column_workgroups(Solver, nx, ny, raman):
+    # columns of 2048 and 4096 points on grids wide enough for two tiles per workgroup, and one that is
+    # not; the same tolerance (a step of each kind)
+    p = Params(nx=nx, ny=ny, xmax=8.0, ymax=7.0, g_uu=4.0, g_dd=3.0, g_ud=2.0, k_l=1.1, omega=0.6, delta=0.3,
+               omega_r0=raman, omega_rw=2.0, dt=1e-4)
+    psi = gaussian_state(p, sigma=2.0, seed=ny, noise=0.1).astype(np.complex64).astype(complex)
+    print(f"case: {nx}x{ny}, raman {raman}", flush=True)
+    o = OracleGPE(p, workers=8)
+    o.set_psi(psi)
+    o.step_real(1)
+    o.step_imag(2)
+    g = Solver(p).set_psi(psi).step_real(1).step_imag(2).get_psi()
+    err = np.linalg.norm(g - o.psi) / np.linalg.norm(o.psi)
+    assert err <= 1e-6, err
