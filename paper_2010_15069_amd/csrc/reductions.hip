@@ -51,12 +51,14 @@ int col_default_cols(int nx, int ny, int points, size_t max_lds) {
   return c;
 }
 
-// Energy kernels (fp64, register-resident transforms): 8 points per lane below 1024 points, 16
-// from there; T = N / points lanes per component of a line, two components per lane pair.  Lines per
-// workgroup: up to 128 / T (a workgroup of at most 256 threads, 512 at 4096 points), but no more
-// than keeps ~256 workgroups on the grid (small grids are latency-bound: more workgroups, each
-// shorter).
-__host__ __device__ constexpr int energy_points(int n) { return n >= 1024 ? 16 : 8; }
+// Energy kernels (fp64, register-resident transforms): 8 points per lane (half the registers of 16, twice
+// the waves: 2048^2 takes 91 us per call instead of 111), but 16 for 1024 points, where two lines then fit
+// 256 threads and a column block reads 32-byte row segments (32 us per call, 41 with 8), and for 4096,
+// whose line would take 1024 threads; T = N / points lanes per component of a line, two components per
+// lane pair.  Lines per workgroup: up to 128 / T (a workgroup of at most 256 threads, 512 at 2048 and 4096
+// points), but no more than keeps ~256 workgroups on the grid (small grids are latency-bound: more
+// workgroups, each shorter).
+__host__ __device__ constexpr int energy_points(int n) { return n == 1024 || n > 2048 ? 16 : 8; }
 
 size_t energy_lds_bytes(int n, int lines) { return 2 * row_lds_bytes(n, lines); }
 
@@ -92,8 +94,9 @@ int norm_blocks() { return 256; }
 //     spatial Raman term Omega(r) Re(u* d) of the real-space energy.
 // Row kernel: the real-space terms, the norm and the rows' k_x terms; column kernel: the columns'
 // k_y terms.  The DFTs are the step kernels' register-resident forward transform (fwd_pass: radix-P
-// stages exchanged through LDS, natural order in and out) instantiated in fp64 on the state widened to fp64 as it is loaded, so the energy of a complex64
-// state carries no transform error of its own.  Each lane holds one component of one line.  The
+// stages exchanged through LDS, positions as real_pos and spec_pos give them) instantiated in fp64 on the
+// state widened to fp64 as it is loaded, so the energy of a complex64 state carries no transform error of
+// its own.  Each lane holds one component of one line.  The
 // partials are scaled so that their combination reads E = (w / N ek + w er) / norm
 // + w ei norm0 / norm^2 (w = dx dy, N = nx ny), as for a 2-D sum.
 // -------------------------------------------------------------------------------------------
@@ -180,18 +183,6 @@ __device__ __forceinline__ void energy_row_body(const EnergyArgs& a, int block) 
   }
 }
 
-template <int N, class Q>
-__global__ void __launch_bounds__(512) energy_row_kernel(EnergyArgs a) {
-  energy_row_body<N, Q>(a, blockIdx.x);
-}
-
-// Batched: grid y = the members of a batch class, each with its own arguments.
-template <int N, class Q>
-__global__ void __launch_bounds__(512) energy_row_kernel_batch(const EnergyArgs* __restrict__ tab) {
-  const EnergyArgs a = tab[blockIdx.y];
-  energy_row_body<N, Q>(a, blockIdx.x);
-}
-
 // Columns of column block `block` (of a.nx / a.cols; the blocks spread over the XCDs as the column
 // pass spreads its tiles).
 template <int N, class Q>
@@ -222,14 +213,50 @@ __device__ __forceinline__ void energy_col_body(const EnergyArgs& a, int block) 
 }
 
 template <int N, class Q>
+__global__ void __launch_bounds__(512) energy_row_kernel(EnergyArgs a) {
+  energy_row_body<N, Q>(a, blockIdx.x);
+}
+
+template <int N, class Q>
 __global__ void __launch_bounds__(512) energy_col_kernel(EnergyArgs a) {
   energy_col_body<N, Q>(a, blockIdx.x);
+}
+
+// Square grids: the row blocks and the column blocks are independent and of one shape, so one launch
+// holds both (the first `row_blocks` blocks are the rows').
+template <int N, class Q>
+__global__ void __launch_bounds__(512) energy_square_kernel(EnergyArgs a, int row_blocks) {
+  if (static_cast<int>(blockIdx.x) < row_blocks) energy_row_body<N, Q>(a, blockIdx.x);
+  else energy_col_body<N, Q>(a, blockIdx.x - row_blocks);
+}
+
+// Batched: grid y = the members of a batch class, each with its own arguments.
+template <int N, class Q>
+__global__ void __launch_bounds__(512) energy_row_kernel_batch(const EnergyArgs* __restrict__ tab) {
+  const EnergyArgs a = tab[blockIdx.y];
+  energy_row_body<N, Q>(a, blockIdx.x);
 }
 
 template <int N, class Q>
 __global__ void __launch_bounds__(512) energy_col_kernel_batch(const EnergyArgs* __restrict__ tab) {
   const EnergyArgs a = tab[blockIdx.y];
   energy_col_body<N, Q>(a, blockIdx.x);
+}
+
+// The grid's threads over the n points of psi in turn, eight loads of a thread in flight at a time (the
+// norm of a 2048^2 grid, 64 MiB in complex64: 22 -> 11 us).  f sees the points in the order of a plain loop.
+template <class Q, class F>
+__device__ __forceinline__ void for_each_point(const Q* __restrict__ psi, long long n, F f) {
+  const long long stride = 256LL * gridDim.x;
+  long long i = blockIdx.x * 256LL + threadIdx.x;
+  for (; i + 7 * stride < n; i += 8 * stride) {
+    Q w[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) w[k] = psi[i + k * stride];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) f(w[k]);
+  }
+  for (; i < n; i += stride) f(psi[i]);
 }
 
 // -------------------------------------------------------------------------------------------
@@ -240,11 +267,10 @@ __global__ void __launch_bounds__(256) norm_kernel(const Q* __restrict__ psi, lo
                                                    double* __restrict__ partials) {
   __shared__ double red[64];
   double acc = 0.0;
-  for (long long i = blockIdx.x * 256LL + threadIdx.x; i < n; i += 256LL * gridDim.x) {
-    const Q w = psi[i];
+  for_each_point(psi, n, [&](const Q& w) {
     const double ur = w.x, ui = w.y, dr = w.z, di = w.w;
     acc += ur * ur + ui * ui + dr * dr + di * di;
-  }
+  });
   const double s = block_sum(acc, red);
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
@@ -309,7 +335,33 @@ hipError_t launch_energy_col(const EnergyArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int N>
+hipError_t launch_energy_square(const EnergyArgs& a, hipStream_t s) {
+  constexpr int T = N / energy_points(N);
+  const int rows = N / a.rows;
+  const dim3 grid(rows + N / a.cols), block(2 * T * a.rows);
+  const size_t lds = energy_lds_bytes(N, a.rows);
+  if (a.psi64) hipLaunchKernelGGL((energy_square_kernel<N, double4>), grid, block, lds, s, a, rows);
+  else hipLaunchKernelGGL((energy_square_kernel<N, float4>), grid, block, lds, s, a, rows);
+  return hipGetLastError();
+}
+
 hipError_t launch_energy(const EnergyArgs& a, hipStream_t s) {
+  // one launch instead of two (22.6 -> 18.5 us per call at 256^2, 38 -> 32 at 1024^2); 4096^2 keeps two
+  // (its rows and columns fill the device many times over)
+  if (a.nx == a.ny && a.rows == a.cols) {
+    switch (a.nx) {
+      case 16: return launch_energy_square<16>(a, s);
+      case 32: return launch_energy_square<32>(a, s);
+      case 64: return launch_energy_square<64>(a, s);
+      case 128: return launch_energy_square<128>(a, s);
+      case 256: return launch_energy_square<256>(a, s);
+      case 512: return launch_energy_square<512>(a, s);
+      case 1024: return launch_energy_square<1024>(a, s);
+      case 2048: return launch_energy_square<2048>(a, s);
+      default: break;
+    }
+  }
   hipError_t e = hipErrorInvalidValue;
   switch (a.nx) {
     case 16: e = launch_energy_row<16>(a, s); break;
@@ -393,10 +445,9 @@ __global__ void __launch_bounds__(256) nonfinite_kernel(const Q* __restrict__ ps
                                                         double* __restrict__ partials) {
   __shared__ double red[64];
   double bad = 0.0;
-  for (long long i = blockIdx.x * 256LL + threadIdx.x; i < n; i += 256LL * gridDim.x) {
-    const Q w = psi[i];
+  for_each_point(psi, n, [&](const Q& w) {
     bad += (isfinite(w.x) && isfinite(w.y) && isfinite(w.z) && isfinite(w.w)) ? 0.0 : 1.0;
-  }
+  });
   const double s = block_sum(bad, red);
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
