@@ -111,9 +111,8 @@ __device__ __forceinline__ void persist_class(const PersistArgs& a, const Persis
   }
 }
 
-// Two waves per SIMD: the three grid sizes' bodies and their item loops need ~219 VGPRs; held to
-// 168 for three waves they spill 200 bytes per lane, and the sweep ran at 243k instead of 311k
-// instance-steps/s.
+// At least two waves per SIMD; the three grid sizes' bodies and their item loops take 153 VGPRs in
+// imaginary time and 168 in real time, without a spill, so three are resident.
 template <bool IMAG>
 __global__ void __launch_bounds__(256, 2) persist_kernel(PersistArgs a) {
   const int grp = static_cast<int>(blockIdx.x % kPersistGroups);

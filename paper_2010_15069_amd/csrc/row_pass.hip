@@ -1,7 +1,8 @@
 // HIP kernels of the split-step solver for gfx950: the row pass.
 //
 // One imaginary-time Strang step K(dt/2) R(dt) K(dt/2) (Sec. 3.2) is computed by two fused sweeps over
-// the state (a real-time step takes one, see line_launch.hpp), which lives in HBM as [ny][nx] float4 {re_up, im_up, re_dn, im_dn}:
+// the state (a real-time step takes one, see line_launch.hpp), which lives in HBM as [ny][nx] float4
+// {re_up, im_up, re_dn, im_dn}:
 //
 //   row pass    -- per row: inverse x-FFT, scale, real-space 2x2 exponential R (trap, detuning,
 //                  mean field, spatial Raman coupling; Eqs. (H2)-(H4)), forward x-FFT;
@@ -9,8 +10,8 @@
 //                  uniform Raman coupling; Eqs. (H1), (H4)), inverse y-FFT.
 //
 // Between sweeps the state is in the mixed representation (k_x, y).  Adjacent K(dt/2) halves of
-// consecutive steps are merged into one K(dt) in the column pass, so a run of n steps costs
-// 2n + 2 sweeps.  In imaginary time the column pass also produces the norm that the next row pass
+// consecutive steps are merged into one K(dt) in the column pass, so a run of n imaginary-time steps
+// costs 2n + 3 sweeps.  The column pass also produces the norm that the next row pass
 // rescales by (Parseval), so renormalisation costs no extra sweep.
 //
 // Thread layout: lanes 2j and 2j+1 own the up and down component of the same 16 positions of a
@@ -24,7 +25,6 @@
 #include "row_body.hpp"
 
 namespace sgpe {
-
 
 // Row groups are sized for 256 threads (row_rows_per_block); only a 4096-point row at 16 points
 // per lane needs 512.  The tighter bound gives the variants' two real-space routines the

@@ -79,7 +79,8 @@ def traffic_record(kf: str, kw: str, cf: str, cw: str) -> dict:
     kfm, kwm = counter_medians(kf), counter_medians(kw)
     alg = BYTES_PER_POINT_PASS * 1024 * 1024
     want = {"row_pass": "row_kernel<1024, 2, true, false, 1, 16>", "col_pass": "col_kernel<1024, 1, 1, 16>",
-            "row_pass_real": "row_kernel<1024, 2, false, false, 1, 16>", "col_pass_real": "col_kernel<1024, 0, 1, 16>"}
+            "row_pass_real": "line_kernel<1024, false, false, false, 16>",
+            "col_pass_real": "line_kernel<1024, true, false, false, 16>"}
     rec = {"workload": "metric_1024", "kernel_hash": kernel_hash(),
            "schedule": {"col_tile": 4, "row_iters": 1, "col_iters": 1, "row_points": 16, "col_points": 16,
                         "row_tile": 1},
