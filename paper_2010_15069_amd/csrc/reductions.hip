@@ -1,6 +1,7 @@
 // HIP kernels of the split-step solver for gfx950: energy and norm reductions, and the
 // workgroup geometry shared by all passes.
 #include <algorithm>
+#include <type_traits>
 
 #include "col_body.hpp"
 #include "fft_device.hpp"
@@ -52,7 +53,7 @@ int col_default_cols(int nx, int ny, int points, size_t max_lds) {
 }
 
 // Energy kernels (fp64, register-resident transforms): 8 points per lane (half the registers of 16, twice
-// the waves: 2048^2 takes 91 us per call instead of 111), but 16 for 1024 points, where two lines then fit
+// the waves: 2048^2 took 91 us per call instead of 111), but 16 for 1024 points, where two lines then fit
 // 256 threads and a column block reads 32-byte row segments (32 us per call, 41 with 8), and for 4096,
 // whose line would take 1024 threads; T = N / points lanes per component of a line, two components per
 // lane pair.  Lines per workgroup: up to 128 / T (a workgroup of at most 256 threads, 512 at 2048 and 4096
@@ -102,28 +103,49 @@ int norm_blocks() { return 256; }
 // -------------------------------------------------------------------------------------------
 extern __shared__ __align__(16) unsigned char energy_lds[];
 
-// The lane's component of state point i (Q: float4 for a complex64 state, double4 for complex128),
-// widened to fp64.
+// One component of a state point (Q: float4 for a complex64 state, double4 for complex128).
 template <class Q>
-__device__ __forceinline__ double2 energy_load(const EnergyArgs& a, size_t i, int comp) {
+using Half = std::conditional_t<sizeof(Q) == sizeof(double4), double2, float2>;
+
+// The lane's component of state point i.
+template <class Q>
+__device__ __forceinline__ Half<Q> energy_load(const EnergyArgs& a, size_t i, int comp) {
   if constexpr (sizeof(Q) == sizeof(double4)) {
     return reinterpret_cast<const double2*>(a.psi64)[2 * i + comp];
   } else {
-    const float2 v = reinterpret_cast<const float2*>(a.psi)[2 * i + comp];
-    return make_double2(v.x, v.y);
+    return reinterpret_cast<const float2*>(a.psi)[2 * i + comp];
   }
 }
 
 __device__ __forceinline__ int energy_freq(int j, int n) { return j < n / 2 ? j : j - n; }
 
-// Point i of the state as four doubles {re_up, im_up, re_dn, im_dn}.
+// Point i of the state.
 template <class Q>
-__device__ __forceinline__ double4 energy_point(const EnergyArgs& a, size_t i) {
-  if constexpr (sizeof(Q) == sizeof(double4)) {
-    return a.psi64[i];
-  } else {
-    const float4 v = a.psi[i];
-    return make_double4(v.x, v.y, v.z, v.w);
+__device__ __forceinline__ Q energy_point(const EnergyArgs& a, size_t i) {
+  if constexpr (sizeof(Q) == sizeof(double4)) return a.psi64[i];
+  else return a.psi[i];
+}
+
+// block_sum of four values at once (each in the same order): v is the sums for thread 0.
+__device__ __forceinline__ void block_sums(double (&v)[4], double* red) {
+  const int n = blockDim.x;
+  const bool waves = (n & 63) == 0;   // else a workgroup smaller than one wave (small grids)
+  const int parts = waves ? n >> 6 : n, part = waves ? threadIdx.x >> 6 : threadIdx.x;
+  if (waves) {
+#pragma unroll
+    for (double& x : v) x = wave_sum(x);
+  }
+  if (!waves || (threadIdx.x & 63) == 0) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) red[4 * part + k] = v[k];
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+#pragma unroll
+  for (double& x : v) x = 0.0;
+  for (int p = 0; p < parts; ++p) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] += red[4 * p + k];
   }
 }
 
@@ -132,38 +154,56 @@ template <int N, class Q>
 __device__ __forceinline__ void energy_row_body(const EnergyArgs& a, int block) {
   constexpr int P = energy_points(N);
   constexpr int T = N / P;
-  __shared__ double red[64];
+  __shared__ double red[4 * 64];
   const int tid = threadIdx.x, comp = tid & 1, pair = tid >> 1;
   const int t = pair & (T - 1), r = pair / T;
   const int row = block * a.rows + r;
   const size_t row0 = size_t(row) * N;
-  // The real-space terms and the norm, point by point with both components in one load (a loop of
-  // few registers of its own; the transform's loads below then find the row in the L2).
+  // The real-space terms and the norm: P/2 points per thread with both components in one load, four
+  // loads in flight.  At 8 points per lane the transform's loads, which find the row in the L2, go out
+  // with them (16 points: 250 VGPRs).  The roots wait until the sums have given their registers back
+  // (2048 points: 109 VGPRs instead of 130, which would leave one workgroup per CU).  With the four sums
+  // in one round of barriers, per energy call: 2048^2 91.5 -> 87.3 us, 512^2 20.6 -> 19.6, 64^2 17.5 -> 16.9.
   const double y = a.ymin + a.dy * row;
   const double om_row = a.om_y ? a.om_y[row] : 0.0;
   double er = 0.0, ei = 0.0, nr = 0.0;
-#pragma unroll 2
-  for (int j = tid & (2 * T - 1); j < N; j += 2 * T) {
-    const double4 q = energy_point<Q>(a, row0 + j);
-    const double x = a.xmin + a.dx * j;
-    const double V = a.wx2h * x * x + a.wy2h * y * y;
-    const double nu = q.x * q.x + q.y * q.y, nd = q.z * q.z + q.w * q.w;
-    // spatial Raman coupling Omega(r) and the uniform one Omega (its k-space sum, by Parseval)
-    const double om = (a.om_x ? a.om_x[j] + om_row : 0.0) + a.omega;
-    er += V * (nu + nd) + 0.5 * a.delta * (nu - nd) + om * (q.x * q.z + q.y * q.w);
-    ei += 0.5 * a.g_uu * nu * nu + 0.5 * a.g_dd * nd * nd + a.g_ud * nu * nd;
-    nr += nu + nd;
+  const LanePos<T> rp = real_pos<N, P>(t);
+  Half<Q> w[P];
+  auto load = [&] {
+#pragma unroll
+    for (int m = 0; m < P; ++m) w[m] = energy_load<Q>(a, row0 + rp.at(m), comp);
+  };
+#pragma unroll 1
+  for (int j0 = tid & (2 * T - 1); j0 < N; j0 += 8 * T) {
+    Q q[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q[i] = energy_point<Q>(a, row0 + j0 + 2 * T * i);
+    if constexpr (P == 8) load();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int j = j0 + 2 * T * i;
+      const double ux = q[i].x, uy = q[i].y, dx = q[i].z, dy = q[i].w;
+      const double x = a.xmin + a.dx * j;
+      const double V = a.wx2h * x * x + a.wy2h * y * y;
+      const double nu = ux * ux + uy * uy, nd = dx * dx + dy * dy;
+      // spatial Raman coupling Omega(r) and the uniform one Omega (its k-space sum, by Parseval)
+      const double om = (a.om_x ? a.om_x[j] + om_row : 0.0) + a.omega;
+      er += V * (nu + nd) + 0.5 * a.delta * (nu - nd) + om * (ux * dx + uy * dy);
+      ei += 0.5 * a.g_uu * nu * nu + 0.5 * a.g_dd * nd * nd + a.g_ud * nu * nd;
+      nr += nu + nd;
+    }
   }
-  // keep the transform's loads (and their registers) after the loop above
-  asm volatile("" ::: "memory");
-  const LanePos<T> rp = real_pos<N, P>(t), sp = spec_pos<N, P>(t);
+  int tt = t;
+  asm volatile("" : "+v"(tt), "+v"(er), "+v"(ei), "+v"(nr)::"memory");
+  if constexpr (P != 8) load();
   double2 v[P];
 #pragma unroll
-  for (int m = 0; m < P; ++m) v[m] = energy_load<Q>(a, row0 + rp.at(m), comp);
+  for (int m = 0; m < P; ++m) v[m] = make_double2(w[m].x, w[m].y);
   TwPlain<N, P, double> tr;
-  load_twiddles<N>(tr, t, a.twx);
+  load_twiddles<N>(tr, tt, a.twx);
   const LdsView<double2> lds = lds_line<N, double2>(energy_lds, r, a.rows, comp);
-  fwd_pass<N>(v, lds, t, tr);
+  fwd_pass<N>(v, lds, tt, tr);
+  const LanePos<T> sp = spec_pos<N, P>(tt);
   const double kl = comp == 0 ? a.k_l : -a.k_l;
   double ex = 0.0;   // the rows' k_x terms
 #pragma unroll
@@ -171,15 +211,13 @@ __device__ __forceinline__ void energy_row_body(const EnergyArgs& a, int block) 
     const double kx = energy_freq(sp.at(m), N) * a.dkx;
     ex += (0.5 * kx * kx + kl * kx) * (v[m].x * v[m].x + v[m].y * v[m].y);
   }
-  const double se = block_sum(er, red);
-  const double sx = block_sum(ex, red);
-  const double si = block_sum(ei, red);
-  const double sn = block_sum(nr, red);
+  double s[4] = {er, ex, ei, nr};
+  block_sums(s, red);
   if (tid == 0) {
-    // w / N * (ny * sx) = w * sx / nx: the k_x terms join the real-space linear ones
-    a.row_partials[kEnergyRowParts * block] = se + sx / double(N);
-    a.row_partials[kEnergyRowParts * block + 1] = si;
-    a.row_partials[kEnergyRowParts * block + 2] = sn;
+    // w / N * (ny * sum) = w * sum / nx: the k_x terms join the real-space linear ones
+    a.row_partials[kEnergyRowParts * block] = s[0] + s[1] / double(N);
+    a.row_partials[kEnergyRowParts * block + 1] = s[2];
+    a.row_partials[kEnergyRowParts * block + 2] = s[3];
   }
 }
 
@@ -197,7 +235,10 @@ __device__ __forceinline__ void energy_col_body(const EnergyArgs& a, int block) 
   const LanePos<T> rp = real_pos<N, P>(t), sp = spec_pos<N, P>(t);
   double2 v[P];
 #pragma unroll
-  for (int m = 0; m < P; ++m) v[m] = energy_load<Q>(a, size_t(rp.at(m)) * a.nx + x, comp);
+  for (int m = 0; m < P; ++m) {
+    const Half<Q> w = energy_load<Q>(a, size_t(rp.at(m)) * a.nx + x, comp);
+    v[m] = make_double2(w.x, w.y);
+  }
   TwPlain<N, P, double> tr;
   load_twiddles<N>(tr, t, a.twy);
   const LdsView<double2> lds = lds_line<N, double2>(energy_lds, cc, C, comp);
