@@ -32,7 +32,6 @@ struct sgpe_ctx {
   double* omy = nullptr;    // Omega_y(y_i)
   double* partials = nullptr;
   double* epart = nullptr;  // energy partials (row: 2 per block, then col: 1 per block)
-  double* npart = nullptr;  // norm partials
   size_t max_lds = 0;       // dynamic LDS bytes available per workgroup
   int rows = 1;             // rows per row-pass workgroup
   int cols = 1;             // columns per column-pass workgroup
@@ -64,7 +63,9 @@ struct sgpe_ctx {
   unsigned int* status_host = nullptr;
   unsigned int* status_dev = nullptr;
   std::vector<void*> allocations;
-  double* host_part = nullptr;   // pinned host copy of reduction partials, grown on demand
+  // reduction partials on the host (pinned, fine-grained, mapped), grown on demand
+  double* host_part = nullptr;
+  double* host_part_dev = nullptr;   // its device address
   size_t host_part_n = 0;
   // A K-R-K step call (either precision) on a state the context owns leaves its last step's K(dt/2)
   // pending (1: real time, with its last R along columns if tail_col, else along rows; 2: imaginary
@@ -73,10 +74,10 @@ struct sgpe_ctx {
   // (flush_tail, from check_ctx).
   int tail_pending = 0;
   bool tail_col = false;
-  // sgpe_relax_imag's ring of energy checks in flight (allocated on its first call): the energies
-  // on the device, their pinned host copies, and an event after each copy
-  double* relax_dev = nullptr;
+  // sgpe_relax_imag's ring of energy checks in flight (allocated on its first call): the energies in
+  // pinned, mapped host memory, its device address, and an event after each check
   double* relax_host = nullptr;
+  double* relax_dev = nullptr;
   hipEvent_t relax_ev[4] = {nullptr, nullptr, nullptr, nullptr};
 };
 
@@ -114,6 +115,9 @@ sgpe_status flush_tail(sgpe_ctx* c);
 // Arguments of the energy kernels for the context's state, with the given partial buffers
 // (kEnergyRowParts per row block, then one per column block).
 sgpe::EnergyArgs energy_args(const sgpe_ctx* c, double* row_partials, double* col_partials);
+// Makes the context's pinned host buffer (host_part, host_part_dev) hold at least n doubles.  Returns
+// SGPE_ENOMEM if it cannot grow, SGPE_EDEVICE on a device error.
+sgpe_status host_partials(sgpe_ctx* c, size_t n);
 // Copies n doubles of reduction partials from the device into the context's pinned host buffer
 // (queued on the context's stream, which is then synchronised) and points *host at it.  Returns
 // SGPE_ENOMEM if the buffer cannot grow, SGPE_EDEVICE on a device error.  A pinned destination

@@ -103,6 +103,12 @@ int norm_blocks() { return 256; }
 // -------------------------------------------------------------------------------------------
 extern __shared__ __align__(16) unsigned char energy_lds[];
 
+// A result of a reduction, to device memory or to pinned host memory that the host reads once the stream
+// is done.
+__device__ __forceinline__ void store_partial(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // One component of a state point (Q: float4 for a complex64 state, double4 for complex128).
 template <class Q>
 using Half = std::conditional_t<sizeof(Q) == sizeof(double4), double2, float2>;
@@ -313,7 +319,7 @@ __global__ void __launch_bounds__(256) norm_kernel(const Q* __restrict__ psi, lo
     acc += ur * ur + ui * ui + dr * dr + di * di;
   });
   const double s = block_sum(acc, red);
-  if (threadIdx.x == 0) partials[blockIdx.x] = s;
+  if (threadIdx.x == 0) store_partial(partials + blockIdx.x, s);
 }
 
 // One workgroup combines the energy kernels' partials on the device: each kind summed in a fixed
@@ -338,7 +344,7 @@ __device__ __forceinline__ void energy_finish_body(const EnergyArgs& a, double* 
   if (threadIdx.x == 0) {
     const double w = a.dx * a.dy;
     const double nrm = w * nr;
-    out[0] = (w / (double(a.nx) * double(a.ny)) * ek + w * er) / nrm + w * ei * a.norm0 / (nrm * nrm);
+    store_partial(out, (w / (double(a.nx) * double(a.ny)) * ek + w * er) / nrm + w * ei * a.norm0 / (nrm * nrm));
   }
 }
 
@@ -490,7 +496,7 @@ __global__ void __launch_bounds__(256) nonfinite_kernel(const Q* __restrict__ ps
     bad += (isfinite(w.x) && isfinite(w.y) && isfinite(w.z) && isfinite(w.w)) ? 0.0 : 1.0;
   });
   const double s = block_sum(bad, red);
-  if (threadIdx.x == 0) partials[blockIdx.x] = s;
+  if (threadIdx.x == 0) store_partial(partials + blockIdx.x, s);
 }
 
 hipError_t launch_nonfinite(const float4* psi, long long npts, double* partials, int nblocks, hipStream_t s) {

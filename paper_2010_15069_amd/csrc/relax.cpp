@@ -4,8 +4,8 @@
 // The paper fixes no stopping rule; the two rules here are the library's.
 //
 // The call enqueues chunks of check_every steps, each followed by an energy check: the energy
-// kernels, their device-side combination (launch_energy_finish) into a slot of a small device ring,
-// an asynchronous copy of that one double into pinned host memory, and an event.  The host reads
+// kernels, their device-side combination (launch_energy_finish) into a slot of a small ring in pinned
+// host memory that the device writes, and an event.  The host reads
 // check k while the chunks of checks k+1 .. k+kAhead are already queued behind it, so the device
 // does not wait for the host between chunks, and each check costs the energy kernels' own time
 // rather than a drained queue.  The price: when check k meets the rule, the queued chunks still run
@@ -23,12 +23,12 @@
 
 namespace {
 
-constexpr int kRing = 4;     // device / pinned slots (kAhead + 1 of them are ever in use)
+constexpr int kRing = 4;     // slots (kAhead + 1 of them are ever in use)
 constexpr int64_t kAhead = 2;
 
 static_assert(kAhead + 1 <= kRing, "a slot is reused only after its check has been read");
 
-// The ring (device slots, pinned copies, events), allocated on the first call and kept by the
+// The ring (slots and events), allocated on the first call and kept by the
 // context.
 sgpe_status relax_buffers(sgpe_ctx* c) {
   if (c->relax_dev) return SGPE_OK;
@@ -41,15 +41,17 @@ sgpe_status relax_buffers(sgpe_ctx* c) {
   }
   if (!c->relax_host) {
     void* h = nullptr;
-    if (hipHostMalloc(&h, kRing * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc(&h, kRing * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
       (void)hipGetLastError();
       return SGPE_ENOMEM;
     }
     c->relax_host = static_cast<double*>(h);
   }
   void* d = nullptr;
-  const sgpe_status st = sgpe_host::dev_alloc(c, &d, kRing * sizeof(double));
-  if (st != SGPE_OK) return st;
+  if (hipHostGetDevicePointer(&d, c->relax_host, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    return SGPE_EDEVICE;
+  }
   c->relax_dev = static_cast<double*>(d);
   return SGPE_OK;
 }
@@ -58,8 +60,6 @@ sgpe_status relax_buffers(sgpe_ctx* c) {
 hipError_t enqueue_check(sgpe_ctx* c, const sgpe::EnergyArgs& a, int slot) {
   hipError_t e = sgpe::launch_energy(a, c->stream);
   if (e == hipSuccess) e = sgpe::launch_energy_finish(a, c->relax_dev + slot, c->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(c->relax_host + slot, c->relax_dev + slot, sizeof(double), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipEventRecord(c->relax_ev[slot], c->stream);
   return e;
 }
