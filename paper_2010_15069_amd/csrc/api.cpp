@@ -133,7 +133,7 @@ double kval(int j, int n, double d) {
 //   M'(k_x) = e^{-h kx^2/2 (i)} [ c 1 - s (b . sigma) ],  b = (omega/2, k_l k_x),
 //   P(k_y)  = e^{-h ky^2/2 (i)};
 // stored as M' - 1 (per component its row, {own, other}) and P - 1, to relative accuracy.  Real time:
-// complex entries.
+// complex entries, times the 1/nx and 1/ny of the line passes' inverse transforms (powers of two).
 template <class T = float>
 void k_tables_real(const sgpe_params& p, double h, std::vector<sgpe::point_t<T>>& kx_out,
                    std::vector<sgpe::cplx_t<T>>& ky_out) {
@@ -153,14 +153,16 @@ void k_tables_real(const sgpe_params& p, double h, std::vector<sgpe::point_t<T>>
     const double m12r = pi * s * bx, m12i = -pr * s * bx;
     const double m22r = pr * c - pi * s * bz, m22i = pi * c + pr * s * bz;
     // per component: {d_own, d_other} of its row of M' - 1 (up: d11, d12; down: d22, d21)
-    kx_out[2 * size_t(j)] = mk4(m11r - 1.0, m11i, m12r, m12i, T());
-    kx_out[2 * size_t(j) + 1] = mk4(m22r - 1.0, m22i, m12r, m12i, T());
+    const double w = 1.0 / p.nx;
+    kx_out[2 * size_t(j)] = mk4(w * (m11r - 1.0), w * m11i, w * m12r, w * m12i, T());
+    kx_out[2 * size_t(j) + 1] = mk4(w * (m22r - 1.0), w * m22i, w * m12r, w * m12i, T());
   }
   for (int i = 0; i < p.ny; ++i) {
     const double ky = kval(i, p.ny, dy);
     const double be = 0.5 * h * ky * ky;
     const double sh = std::sin(0.5 * be);
-    ky_out[i] = mk2h(-2.0 * sh * sh, -std::sin(be), T());
+    const double w = 1.0 / p.ny;
+    ky_out[i] = mk2h(-2.0 * w * sh * sh, -w * std::sin(be), T());
   }
 }
 

@@ -15,8 +15,10 @@ extern __shared__ __align__(16) unsigned char line_lds[];
 //
 // Both ops run through one loop body, so an op is the same instructions whether it shares a pass with R
 // or has one of its own: a call that leaves its last ops to a later pass gives the bits of one that
-// does not.  The 1/N of each inverse transform waits for the store (R takes it through its couplings);
-// all of it is a power of two.
+// does not.  The 1/N of an op's inverse transform is applied in k-space, where it costs nothing: the
+// tables hold (U - 1) / N, and w + (U - 1) w becomes w / N + (U - 1) w / N.  It is a power of two, so
+// the roundings are the same; and R sees the state itself, whose densities have N^2 more range than
+// those of N times the state (a linear problem, g = 0, with values above 1e19 / N gave inf * 0).
 template <int N, bool COL, bool FULL, bool NLN, int P, bool WT, class R>
 __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngroups) {
   using C = cplx_t<R>;
@@ -66,13 +68,13 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
   // loaded where used); at 16 points the transform needs the registers (254 VGPRs without a spill at 1024
   // points; with the values held, 53 spilled and a step took 26.1 us at 1024^2 instead of 19.3), and
   // they are loaded where used.
-  R s = R(1);
+  constexpr R inv_n = R(1) / R(N);
 #pragma unroll 1
   for (int stage = 0; stage < 2; ++stage) {
     const void* const op = stage == 0 ? a.op_pre : a.op_post;
     if (op != nullptr) {
       if constexpr (COL) {
-        const C* __restrict__ tab = static_cast<const C*>(op);   // P(k_y) - 1
+        const C* __restrict__ tab = static_cast<const C*>(op);   // (P(k_y) - 1) / N
         constexpr bool EARLY = P < 16;
         C q[EARLY ? P : 1];
         if constexpr (EARLY) {
@@ -86,10 +88,10 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
           if constexpr (EARLY) e = q[m];
           else e = tab[sp.at(m)];
           const C w = v[m];
-          v[m] = mk2(w.x + fma_(-e.y, w.y, e.x * w.x), w.y + fma_(e.y, w.x, e.x * w.y));
+          v[m] = mk2(fma_(w.x, inv_n, fma_(-e.y, w.y, e.x * w.x)), fma_(w.y, inv_n, fma_(e.y, w.x, e.x * w.y)));
         }
       } else {
-        // this component's row of M'(k_x) - 1, {own, other}
+        // this component's row of (M'(k_x) - 1) / N, {own, other}
         const Q* __restrict__ tab = static_cast<const Q*>(op);
         constexpr bool EARLY = P < 16;
         Q d[EARLY ? P : 1];
@@ -107,16 +109,15 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
           const C o = pair_swap(w);
           const R cr = fma_(-e.w, o.y, fma_(e.z, o.x, fma_(-e.y, w.y, e.x * w.x)));
           const R ci = fma_(e.w, o.x, fma_(e.z, o.y, fma_(e.y, w.x, e.x * w.y)));
-          v[m] = mk2(w.x + cr, w.y + ci);
+          v[m] = mk2(fma_(w.x, inv_n, cr), fma_(w.y, inv_n, ci));
         }
       }
       inv_pass<N>(v, lds, t, tr);
-      s *= R(1) / R(N);
     }
     if (stage == 0) {
 #pragma unroll 1
       for (int r = 0; r < a.n_r; ++r) {
-        row_apply_r<N, false, FULL, NLN>(v, a, line, t, comp == 0, hb_line, hb_cross, s * s);
+        row_apply_r<N, false, FULL, NLN>(v, a, line, t, comp == 0, hb_line, hb_cross);
       }
     }
   }
@@ -128,7 +129,7 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
   }
 #pragma unroll
   for (int m = 0; m < P; ++m)
-    store_state<WT>(reinterpret_cast<C*>(out + (m == 0 ? off0 : offb + mstride * m)), vscale(v[m], s));
+    store_state<WT>(reinterpret_cast<C*>(out + (m == 0 ? off0 : offb + mstride * m)), v[m]);
 }
 
 }  // namespace sgpe

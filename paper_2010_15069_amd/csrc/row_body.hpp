@@ -183,16 +183,15 @@ __device__ __forceinline__ C apply_r_full(C w, C o, const RFull<T>& f, T hbx, T 
 // R on the thread's points
 // -------------------------------------------------------------------------------------------
 // A: any argument struct with the real-space fields of RowArgsT (x along the line the lane holds, y
-// across).  gs: the square of the scale that v still lacks (a power of two, so folding it into the
-// couplings is exact).
+// across).
 template <class R, class A>
-__device__ __forceinline__ RCoef<R> r_coefs(const A& a, bool up, R gs) {
+__device__ __forceinline__ RCoef<R> r_coefs(const A& a, bool up) {
   RCoef<R> c;
   c.sgn = up ? R(1) : R(-1);
   c.hd_own = up ? a.hdelta2 : -a.hdelta2;
-  c.hg_uu = a.hg_uu * gs;
-  c.hg_dd = a.hg_dd * gs;
-  c.hg_ud = a.hg_ud * gs;
+  c.hg_uu = a.hg_uu;
+  c.hg_dd = a.hg_dd;
+  c.hg_ud = a.hg_ud;
   c.hg_own = up ? c.hg_uu : c.hg_dd;
   c.hdelta2 = a.hdelta2;
   return c;
@@ -239,9 +238,9 @@ __device__ __forceinline__ bool small_angles(const C (&v)[P], const A& a, const 
 // with the polynomial exp, 68 -> 52 us; one vote in real time was 2-4 % slower than sixteen).
 template <int N, bool IMAG, bool FULL, bool NLN, int P, class C, class R, class A>
 __device__ __forceinline__ void row_apply_r(C (&v)[P], const A& a, int row, int t, bool up,
-                                            const R (&hbx_r)[P], R hb_row, R gs = R(1)) {
+                                            const R (&hbx_r)[P], R hb_row) {
   const LanePos<N / P> pos = real_pos<N, P>(t);
-  const RCoef<R> c = r_coefs(a, up, gs);
+  const RCoef<R> c = r_coefs<R>(a, up);
   const R y = fma_(static_cast<R>(row), a.dy, a.y0);
   const R hvy = a.hvy * y * y;
   auto apply = [&](auto small) {

@@ -101,8 +101,9 @@ struct LineArgsT {
   int nx;                    // row length of the state in memory
   int lines;                 // lines (rows or columns) per workgroup
   const cplx_t<T>* tw;       // RowArgsT::tw for the line's length
-  const void* op_pre;        // rows: per k_x and component its row of M'(k_x) - 1, {own, other} complex
-  const void* op_post;       //   (point_t); columns: P(k_y) - 1, complex (cplx_t); NULL: not applied
+  const void* op_pre;        // rows: per k_x and component its row of (M'(k_x) - 1) / N, {own, other} complex
+  const void* op_post;       //   (point_t); columns: (P(k_y) - 1) / N, complex (cplx_t); N the line's length;
+                             //   NULL: not applied
   int n_r;                   // real-space sub-steps R(h) in turn (0, 1 or 2)
   T x0, dx, y0, dy;
   T hvx, hvy;

@@ -55,3 +55,31 @@ def test_a_few_steps(env, precision, nx, ny, form):
         err = np.linalg.norm(g - ref.psi) / np.linalg.norm(ref.psi)
         assert err <= TOL[precision], (n, err)
         assert np.array_equal(lent.set_psi(psi).step_real(n).get_psi(), g), n
+
+
+@pytest.mark.parametrize("form", ["diagonal", "raman", "nln", "rkr", "rkr_nln"])
+@pytest.mark.parametrize("precision,scale", [("c64", 1e18), ("c128", 1e152)])
+def test_large_values_of_a_linear_problem(env, precision, scale, form):
+    # without interactions a step is linear in the state, so it may be as large as its densities allow
+    # (n = 1e36 in complex64, 1e304 in complex128): a pass must not form them of larger values than these
+    torch, m = env
+    if precision == "c128" and form not in ("diagonal", "raman"):
+        pytest.skip("complex128 runs the default split")
+    p = Params(nx=256, ny=256, xmax=8.0, ymax=6.0, g_uu=0.0, g_dd=0.0, g_ud=0.0, k_l=1.3, omega=0.7, delta=0.2,
+               wx=1.0, wy=1.4, omega_r0=0.0 if form == "diagonal" else 1.5, omega_rw=2.0, dt=2e-3)
+    split = {"nln": ("krk", "nln"), "rkr": ("rkr", "frozen"), "rkr_nln": ("rkr", "nln")}.get(form, ("krk", "frozen"))
+    psi = gaussian_state(p, sigma=1.5, seed=5, noise=1e-2)
+    psi = (psi / abs(psi).max()).astype(np.complex64).astype(complex)
+    ref = OracleGPE(p)
+    ref.set_splitting(*split)
+    ref.set_psi(psi)
+    ref.step_real(3)
+    print(f"case: {precision} {form}, values up to {scale:g}", flush=True)
+    s = m.Solver(p, precision=precision)
+    if precision == "c64":
+        s.set_splitting(*split)
+    # the library's own rounding of scale psi: the scale is a power of two
+    scale = 2.0 ** np.floor(np.log2(scale))
+    g = s.set_psi(psi * scale).step_real(3).get_psi() / scale
+    err = np.linalg.norm(g - ref.psi) / np.linalg.norm(ref.psi)
+    assert err <= TOL[precision], err
