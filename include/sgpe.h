@@ -360,8 +360,10 @@ sgpe_status sgpe_set_col_tile(sgpe_ctx* ctx, int32_t columns);
  *   col_points  the same for the y transforms and ny
  *   row_tile    rows per row-pass workgroup (power of two); 0 in sgpe_set_schedule: the default
  *               for row_points (256-thread workgroups)
- * A workgroup has 2 * lines * (n / points) threads, at most 512 (256 when prefetching), and its
- * LDS must fit the device. */
+ * A workgroup has 2 * lines * (n / points) threads, at most 512 (256 when prefetching; 1024 for a
+ * complex64 column tile of 2048- or 4096-point columns, which the default takes on grids wide enough
+ * to leave a workgroup per compute unit), and its LDS must fit the device.  A real-time pass along
+ * columns with a spatial Raman coupling takes a tile of 1024 threads in two halves. */
 typedef struct {
   int32_t col_tile;
   int32_t row_iters;

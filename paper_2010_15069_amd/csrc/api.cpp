@@ -209,6 +209,20 @@ int default_points(int n, size_t npts, bool col) {
   return n <= (col ? 512 : 256) ? 8 : 16;
 }
 
+// The default column tile from one of at most 512 threads: twice that where such a tile of 2048- or
+// 4096-point columns fills its workgroup with a row segment of only 32 or 16 bytes, the wider tile fits
+// the LDS, and one workgroup per compute unit is left.  The pass holds its registers at the four waves per
+// SIMD of 1024 threads (96 VGPRs), so the same waves are resident and the segments are twice as long
+// (per step, imaginary / real time: 2048^2 79.8 / 64.6 -> 73.1 / 56.8 us, 1024 x 4096 126 / 79 -> 94 / 70,
+// 512 x 4096 67.8 / 44.2 -> 54.7 / 40.1).
+int wide_cols(const sgpe_ctx* c, int cols, int points) {
+  const int nx = c->p.nx, ny = c->p.ny;
+  return 2 * cols * (ny / points) == 512 && nx / (2 * cols) >= c->n_cu &&
+                 sgpe::col_tile_supported(nx, ny, 2 * cols, 1, points, c->max_lds)
+             ? 2 * cols
+             : cols;
+}
+
 void default_schedule(sgpe_ctx* c) {
   const int nx = c->p.nx, ny = c->p.ny;
   const size_t npts = size_t(nx) * size_t(ny);
@@ -225,6 +239,7 @@ void default_schedule(sgpe_ctx* c) {
     const int cc = std::max(1, nx / c->n_cu);
     if ((cc & (cc - 1)) == 0 && sgpe::col_cols_supported(nx, ny, cc, 1, c->col_points, c->max_lds)) c->cols = cc;
   }
+  c->cols = wide_cols(c, c->cols, c->col_points);
   // One row per workgroup where a row takes at least two waves (measured at 256^2-2048^2: fastest,
   // or within 1 % at 512^2; one 4-row workgroup per CU was 8 % slower per step at 1024^2 and row
   // prefetch slower everywhere).  Smaller rows keep the derived tile.
@@ -238,23 +253,13 @@ void default_schedule(sgpe_ctx* c) {
     c->row_iters = 2;
 }
 
-// Schedule tiles per column-pass workgroup, side by side: two where a tile of 2048- or 4096-point columns
-// fills a workgroup of 512 threads with a row segment of only 32 or 16 bytes, the wider tile fits the
-// LDS, and one workgroup per compute unit is left.  The pass holds its registers at the four waves per
-// SIMD of 1024 threads (96 VGPRs), so the same waves are resident and the segments are twice as long
-// (per step, imaginary / real time: 2048^2 79.8 / 64.6 -> 73.1 / 56.8 us, 1024 x 4096 126 / 79 -> 94 / 70,
-// 512 x 4096 67.8 / 44.2 -> 54.7 / 40.1).
-static int col_wide(const sgpe_ctx* c) {
-  const int cols = 2 * c->cols;
-  const bool fills = c->prec != SGPE_C128 && c->p.ny >= 2048 && c->col_points == 16 && c->col_iters == 1 &&
-                     cols * (c->p.ny / 16) == 512;
-  return fills && c->p.nx % cols == 0 && c->p.nx / cols >= c->n_cu &&
-                 sgpe::col_lds_bytes(c->p.ny, cols) <= c->max_lds
-             ? 2
-             : 1;
-}
+int col_groups(const sgpe_ctx* c) { return c->p.nx / (c->cols * c->col_iters); }
 
-int col_groups(const sgpe_ctx* c) { return c->p.nx / (c->cols * col_wide(c) * c->col_iters); }
+// Columns per workgroup of a real-time pass along columns: the schedule's tile, or half of it where that
+// takes more than the 512 threads of a pass with a spatial coupling (line_threads).
+static int line_cols(const sgpe_ctx* c) {
+  return c->full2x2 && 2 * c->cols * (c->p.ny / c->col_points) > 512 ? c->cols / 2 : c->cols;
+}
 
 sgpe_status apply_schedule(sgpe_ctx* c, const sgpe_schedule& s) {
   const sgpe_params& p = c->p;
@@ -266,7 +271,7 @@ sgpe_status apply_schedule(sgpe_ctx* c, const sgpe_schedule& s) {
       p.ny % (rows * s.row_iters) != 0 ||
       sgpe::row_lds_bytes(p.nx, rows) > c->max_lds)
     return SGPE_EINVAL;
-  if (!sgpe::col_cols_supported(p.nx, p.ny, s.col_tile, s.col_iters, s.col_points, c->max_lds)) return SGPE_EINVAL;
+  if (!sgpe::col_tile_supported(p.nx, p.ny, s.col_tile, s.col_iters, s.col_points, c->max_lds)) return SGPE_EINVAL;
   c->rows = rows;
   c->cols = s.col_tile;
   c->row_iters = s.row_iters;
@@ -353,7 +358,7 @@ sgpe::ColArgsT<T> col_args_t(const sgpe_ctx* c, bool half) {
   }
   a.nx = c->p.nx;
   a.ny = c->p.ny;
-  a.cols = c->cols * col_wide(c);
+  a.cols = c->cols;
   a.partials = c->partials;
   return a;
 }
@@ -369,7 +374,7 @@ sgpe::LineArgsT<T> line_args_t(const sgpe_ctx* c, bool col, LineOp pre, LineOp p
   sgpe::LineArgsT<T> a{};
   a.psi = r.psi;
   a.nx = p.nx;
-  a.lines = col ? c->cols * (c->full2x2 ? 1 : col_wide(c)) : c->rows;
+  a.lines = col ? line_cols(c) : c->rows;
   auto op = [&](LineOp o) -> const void* {
     if (o == LINE_NONE) return nullptr;
     const bool half = o == LINE_HALF;
@@ -1012,8 +1017,8 @@ sgpe_status sgpe_set_col_tile(sgpe_ctx* c, int32_t columns) {
   const sgpe_params& p = c->p;
   if (columns < 1) return SGPE_EINVAL;
   int iters = c->col_iters;
-  if (!sgpe::col_cols_supported(p.nx, p.ny, columns, iters, c->col_points, c->max_lds)) iters = 1;
-  if (!sgpe::col_cols_supported(p.nx, p.ny, columns, iters, c->col_points, c->max_lds)) return SGPE_EINVAL;
+  if (!sgpe::col_tile_supported(p.nx, p.ny, columns, iters, c->col_points, c->max_lds)) iters = 1;
+  if (!sgpe::col_tile_supported(p.nx, p.ny, columns, iters, c->col_points, c->max_lds)) return SGPE_EINVAL;
   c->cols = columns;
   c->col_iters = iters;
   return SGPE_OK;

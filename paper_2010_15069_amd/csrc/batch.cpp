@@ -324,7 +324,7 @@ sgpe_schedule class_default(const sgpe_ctx* c0, size_t members) {
   s.col_points = default_points(c0->p.ny, total, true);
   s.row_iters = 1;
   s.col_iters = 1;
-  s.col_tile = sgpe::col_default_cols(c0->p.nx, c0->p.ny, s.col_points, c0->max_lds);
+  s.col_tile = wide_cols(c0, sgpe::col_default_cols(c0->p.nx, c0->p.ny, s.col_points, c0->max_lds), s.col_points);
   return s;
 }
 

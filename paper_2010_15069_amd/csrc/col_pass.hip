@@ -21,7 +21,7 @@ namespace sgpe {
 // One instance: workgroup blockIdx.x of the pass.  A batch of instances of one grid shape:
 // grid of (items, instances) read by batch_item (all of an instance on one XCD), the instance's
 // arguments from a device table.
-// Columns of 2048 points and more may run two schedule tiles side by side (see col_wide, api.cpp).
+// Columns of 2048 points and more may take tiles of 1024 threads (see wide_cols, api.cpp).
 constexpr int col_threads(int n, int iters) { return iters == 2 ? 256 : n >= 2048 ? 1024 : 512; }
 
 template <int N, int NORM, int ITERS, int P>

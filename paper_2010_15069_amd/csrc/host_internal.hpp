@@ -96,6 +96,7 @@ sgpe_status dev_alloc(sgpe_ctx* c, void** ptr, size_t bytes);
 sgpe_status status_of(hipError_t e);
 void default_schedule(sgpe_ctx* c);
 int default_points(int n, size_t npts, bool col);   // points per lane of rows (columns) of length n, npts points in all
+int wide_cols(const sgpe_ctx* c, int cols, int points);   // the default column tile, from one of <= 512 threads
 int col_groups(const sgpe_ctx* c);
 sgpe_status apply_schedule(sgpe_ctx* c, const sgpe_schedule& s);   // validated; EINVAL changes nothing
 sgpe_schedule get_schedule(const sgpe_ctx* c);

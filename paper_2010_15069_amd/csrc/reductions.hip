@@ -33,10 +33,14 @@ int row_rows_per_block(int nx, int ny, int points, size_t max_lds) {
   return rows;
 }
 
-bool col_cols_supported(int nx, int ny, int cols, int iters, int points, size_t max_lds) {
+bool col_tile_supported(int nx, int ny, int cols, int iters, int points, size_t max_lds) {
+  if (!col_launch_supported(ny, cols, iters, points)) return false;
   if (cols > nx || nx % (cols * iters) != 0) return false;
-  if (!schedule_supported(ny, cols, iters, points)) return false;
   return col_lds_bytes(ny, cols) <= max_lds;
+}
+
+bool col_cols_supported(int nx, int ny, int cols, int iters, int points, size_t max_lds) {
+  return schedule_supported(ny, cols, iters, points) && col_tile_supported(nx, ny, cols, iters, points, max_lds);
 }
 
 int col_default_cols(int nx, int ny, int points, size_t max_lds) {

@@ -154,7 +154,7 @@ inline bool schedule_supported(int n, int groups, int iters, int points) {
   return threads <= (iters == 2 ? 256 : 512);
 }
 
-// Complex64 column launches of 2048 and 4096 points may hold twice the threads (col_wide, api.cpp).
+// Complex64 column tiles of 2048 and 4096 points may hold twice the threads (wide_cols, api.cpp).
 inline bool col_launch_supported(int n, int groups, int iters, int points) {
   if (n >= 2048 && points == 16 && iters == 1 && 2 * groups * (n / points) == 1024) groups >>= 1;
   return schedule_supported(n, groups, iters, points);
@@ -274,6 +274,8 @@ hipError_t launch_probe_cols_wl(const float4* src, float4* dst, int nx, int ny, 
 // max_lds: the device's LDS bytes per workgroup (minus the kernels' static LDS).
 int row_rows_per_block(int nx, int ny, int points, size_t max_lds);
 int col_default_cols(int nx, int ny, int points, size_t max_lds);
+// a complex64 column tile that a schedule may ask for, and one of at most 512 threads
+bool col_tile_supported(int nx, int ny, int cols, int iters, int points, size_t max_lds);
 bool col_cols_supported(int nx, int ny, int cols, int iters, int points, size_t max_lds);
 bool energy_fits(int nx, int ny, size_t max_lds);
 int energy_rows_per_block(int nx, int ny);

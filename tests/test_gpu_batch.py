@@ -188,3 +188,33 @@ def test_workgroup_placement_follows_dispatch_order(sgpe):
         assert xcd.max() < 8
         shift = (xcd.astype(np.int64) - np.arange(gx * gy)) % 8
         assert np.all(shift == shift[0]), np.unique(shift)
+
+
+@pytest.mark.parametrize("raman", [0.0, 1.5])
+def test_classes_of_long_columns(sgpe, raman):
+    # columns of 2048 points: the class's default is the wide tile (1024 threads), in real time with a
+    # spatial coupling taken in halves; against single contexts with that schedule and with a narrower one
+    p = Params(nx=1024, ny=2048, xmax=8.0, ymax=7.0, g_uu=4.0, g_dd=3.0, g_ud=2.0, k_l=1.1, omega=0.6, delta=0.3,
+               omega_r0=raman, omega_rw=2.0, dt=1e-3)
+    ps = [p, p.replace(g_ud=1.0, delta=-0.2)]
+    psi0 = states(ps, seed=40)
+    print(f"case: 2 instances of 1024x2048, raman {raman}", flush=True)
+    b = sgpe.Batch(ps)
+    for i, psi in enumerate(psi0):
+        b.set_psi(i, psi)
+    default = b.get_schedule(0)
+    assert default["col_tile"] == 4
+    narrow = dict(default, col_tile=2)
+    for schedule in (default, narrow):
+        b.set_schedule(0, schedule)
+        assert b.get_schedule(0) == schedule
+        b.step_imag(3).step_real(3).step_real(2)
+        for i, q in enumerate(ps):
+            s = sgpe.Solver(q)
+            s.set_schedule(schedule)
+            # the batch completes every call (a single context would merge the two real ones)
+            s.set_psi(psi0[i]).step_imag(3).step_real(3).synchronize()
+            psi0[i] = s.step_real(2).get_psi()
+            assert np.array_equal(b.get_psi(i), psi0[i]), (schedule, i)
+            s.close()
+    b.close()

@@ -57,3 +57,32 @@ def test_wide_column_workgroups(Solver, nx, ny, raman):
     g = Solver(p).set_psi(psi).step_real(1).step_imag(2).get_psi()
     err = np.linalg.norm(g - o.psi) / np.linalg.norm(o.psi)
     assert err <= 1e-6, err
+
+
+@pytest.mark.parametrize("nx,ny,tiles", [(1024, 2048, (1, 2, 4)), (512, 4096, (1, 2))])
+@pytest.mark.parametrize("raman", [0.0, 1.5])
+def test_an_explicit_column_tile_is_the_one_that_runs(Solver, nx, ny, tiles, raman):
+    # the default's 1024-thread tile is a tile of the schedule: it is what get_schedule gives, a narrower
+    # one can be had, and tiles do not change a point's arithmetic (imaginary time: the grouping of the
+    # norm's fp64 partials, rel. 1e-6 as for the narrower grids)
+    p = Params(nx=nx, ny=ny, xmax=8.0, ymax=7.0, g_uu=4.0, g_dd=3.0, g_ud=2.0, k_l=1.1, omega=0.6, delta=0.3,
+               omega_r0=raman, omega_rw=2.0, dt=1e-4)
+    psi = gaussian_state(p, sigma=2.0, seed=ny, noise=0.1).astype(np.complex64).astype(complex)
+    d = Solver(p)
+    assert d.get_schedule()["col_tile"] == tiles[-1]
+    real = d.set_psi(psi).step_real(3).get_psi()
+    imag = d.step_imag(2).get_psi()
+    for tile in tiles:
+        print(f"case: {nx}x{ny}, raman {raman}, column tile {tile}", flush=True)
+        s = Solver(p)
+        s.set_schedule(col_tile=tile)
+        assert s.get_schedule()["col_tile"] == tile
+        assert np.array_equal(s.set_psi(psi).step_real(3).get_psi(), real)
+        g = s.step_imag(2).get_psi()
+        assert np.linalg.norm(g - imag) <= 1e-6 * np.linalg.norm(imag)
+        if tile == tiles[-1]:
+            assert np.array_equal(g, imag)   # a saved default is the default
+        s.close()
+    with pytest.raises(Exception, match="SGPE_EINVAL"):
+        d.set_schedule(col_tile=2 * tiles[-1])
+    assert d.get_schedule()["col_tile"] == tiles[-1]
