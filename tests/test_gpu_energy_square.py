@@ -60,3 +60,9 @@ def test_a_value_that_is_not_finite_is_found(sgpe, n, where):
         s.set_psi_device(torch.from_numpy(t).cuda())
     assert e.value.status == 4
     s.close()
+
+
+@pytest.mark.parametrize("precision", ["c64", "c128"])
+def test_square_energy_and_norm_256(sgpe, precision):
+    # the square size between those above
+    test_square_energy_and_norm(sgpe, 256, precision)

@@ -147,3 +147,51 @@ def test_forced_barrier_give_up_is_reported(api):
                          stderr=subprocess.STDOUT, text=True, timeout=120)
     assert out.returncode == 0, out.stdout
     assert "GAVE-UP 3" in out.stdout, out.stdout        # SGPE_EDEVICE
+
+
+REAL_CALLS = [2, 3, 8, 5]   # no resident step, an odd and an even number of them: the last pass along either axis
+
+
+@pytest.mark.parametrize("graph", [True, False])
+def test_real_time_calls_of_either_parity(api, graph):
+    Batch, Solver, _ = api
+    ps = sweep_instances(seed=8, sizes=(128, 256, 512), per_size=2)
+    starts = [initial_state(p, "tf", seed=60 + i) for i, p in enumerate(ps)]
+    b = Batch(ps)
+    for i, s0 in enumerate(starts):
+        b.set_psi(i, s0)
+    b.use_graph(graph)
+    b.use_persistent(True)
+    singles = [Solver(p).set_schedule(**_single_schedule(p.nx)).set_psi(starts[i]) for i, p in enumerate(ps)]
+    for n in REAL_CALLS:
+        print(f"case: 6 instances, persistent, {n} real steps, graph={graph}", flush=True)
+        b.step_real(n)
+        b.synchronize()
+        for i, s in enumerate(singles):
+            s.step_real(n).synchronize()
+            assert np.array_equal(b.get_psi(i), s.get_psi()), (n, i)
+    for s in singles:
+        s.close()
+    b.close()
+
+
+@pytest.mark.parametrize("steps", [40, 41])
+def test_real_time_against_the_oracle(api, steps):
+    # unequal axes of the box and the trap, so that an axis taken for the other shows
+    Batch, _, _ = api
+    p = Params(nx=128, ny=128, xmax=8.0, ymax=6.0, g_uu=20.0, g_dd=15.0, g_ud=10.0, k_l=1.5, omega=0.8, delta=0.2,
+               wx=1.0, wy=1.4, dt=1e-3)
+    psi0 = initial_state(p, "tf", seed=9)
+    b = Batch([p, p.replace(g_ud=5.0)])
+    b.set_psi(0, psi0)
+    b.set_psi(1, psi0)
+    b.use_persistent(True)
+    print(f"case: persistent, {steps} real steps against the oracle", flush=True)
+    b.step_real(steps)
+    o = OracleGPE(p, workers=WORKERS)
+    o.set_psi(psi0)
+    o.step_real(steps)
+    err = float(np.linalg.norm(b.get_psi(0) - o.psi) / np.linalg.norm(o.psi))
+    # the bar of the imaginary-time comparison above
+    assert err <= 1e-5, err
+    b.close()

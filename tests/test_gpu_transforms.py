@@ -86,3 +86,22 @@ def test_an_explicit_column_tile_is_the_one_that_runs(Solver, nx, ny, tiles, ram
     with pytest.raises(Exception, match="SGPE_EINVAL"):
         d.set_schedule(col_tile=2 * tiles[-1])
     assert d.get_schedule()["col_tile"] == tiles[-1]
+
+
+@pytest.mark.parametrize("nx,ny", [(1024, 2048), (512, 4096)])
+@pytest.mark.parametrize("raman", [0.0, 1.5])
+def test_wide_columns_with_the_full_op_on_both_sides(Solver, nx, ny, raman):
+    # three steps (the third pass along columns, with K(dt) before and after R) and a call that continues
+    # them; the tolerance of the pairs above for five steps: 1.4e-7 sqrt(22) = 6.6e-7 < 1e-6
+    p = Params(nx=nx, ny=ny, xmax=8.0, ymax=7.0, g_uu=4.0, g_dd=3.0, g_ud=2.0, k_l=1.1, omega=0.6, delta=0.3,
+               omega_r0=raman, omega_rw=2.0, dt=1e-4)
+    psi = gaussian_state(p, sigma=2.0, seed=ny + 1, noise=0.1).astype(np.complex64).astype(complex)
+    print(f"case: {nx}x{ny}, raman {raman}, 3 + 2 real steps", flush=True)
+    o = OracleGPE(p, workers=8)
+    o.set_psi(psi)
+    o.step_real(5)
+    s, one = Solver(p), Solver(p)
+    g = s.set_psi(psi).step_real(3).step_real(2).get_psi()
+    err = np.linalg.norm(g - o.psi) / np.linalg.norm(o.psi)
+    assert err <= 1e-6, err
+    assert np.array_equal(g, one.set_psi(psi).step_real(5).get_psi())
