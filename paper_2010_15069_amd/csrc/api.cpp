@@ -907,8 +907,7 @@ sgpe_status sgpe_create_ex(const sgpe_params* p, int32_t precision, void* hip_st
   c->p = *p;
   c->device = dev;
   c->stream = static_cast<hipStream_t>(hip_stream);
-  // the kernels' static LDS (reduction scratch) is < 256 bytes
-  c->max_lds = prop.sharedMemPerBlock > 256 ? size_t(prop.sharedMemPerBlock) - 256 : 0;
+  c->max_lds = prop.sharedMemPerBlock > sgpe::kStaticLds ? size_t(prop.sharedMemPerBlock) - sgpe::kStaticLds : 0;
   c->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1;
   c->prec = precision;
   default_schedule(c);

@@ -25,7 +25,8 @@ template <int N, int NORM, int ITERS, int P, bool WT, class R>
 __device__ __forceinline__ void col_body(const ColArgsT<R>& a, int wg, int ngroups) {
   using CX = cplx_t<R>;
   constexpr uint32_t PB = sizeof(point_t<R>), CB = sizeof(CX);   // bytes per point / component
-  __shared__ double red[64];
+  __shared__ double red[kRedDoubles];
+  static_assert(sizeof red <= kStaticLds);
   constexpr int T = N / P;
   const int C = a.cols;
   const int tid = threadIdx.x;

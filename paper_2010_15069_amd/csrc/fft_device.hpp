@@ -771,7 +771,7 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// Sum over the workgroup in a fixed order; every thread must call it; red must hold 64 doubles.
+// Sum over the workgroup in a fixed order; every thread must call it; red must hold kRedDoubles.
 // Result valid in every thread.
 __device__ __forceinline__ double block_sum(double v, double* red) {
   const int n = blockDim.x;

@@ -106,6 +106,8 @@ int norm_blocks() { return 256; }
 // + w ei norm0 / norm^2 (w = dx dy, N = nx ny), as for a 2-D sum.
 // -------------------------------------------------------------------------------------------
 extern __shared__ __align__(16) unsigned char energy_lds[];
+using EnergyRed = double[kEnergyRedDoubles];
+static_assert(sizeof(EnergyRed) <= kStaticLds);
 
 // A result of a reduction, to device memory or to pinned host memory that the host reads once the stream
 // is done.
@@ -136,7 +138,8 @@ __device__ __forceinline__ Q energy_point(const EnergyArgs& a, size_t i) {
   else return a.psi[i];
 }
 
-// block_sum of four values at once (each in the same order): v is the sums for thread 0.
+// block_sum of four values at once (each in the same order): v is the sums for thread 0; red must hold
+// kEnergyRedDoubles.
 __device__ __forceinline__ void block_sums(double (&v)[4], double* red) {
   const int n = blockDim.x;
   const bool waves = (n & 63) == 0;   // else a workgroup smaller than one wave (small grids)
@@ -161,10 +164,9 @@ __device__ __forceinline__ void block_sums(double (&v)[4], double* red) {
 
 // Rows block*rows .. block*rows + rows - 1 of the state a describes.
 template <int N, class Q>
-__device__ __forceinline__ void energy_row_body(const EnergyArgs& a, int block) {
+__device__ __forceinline__ void energy_row_body(const EnergyArgs& a, int block, double* red) {
   constexpr int P = energy_points(N);
   constexpr int T = N / P;
-  __shared__ double red[4 * 64];
   const int tid = threadIdx.x, comp = tid & 1, pair = tid >> 1;
   const int t = pair & (T - 1), r = pair / T;
   const int row = block * a.rows + r;
@@ -234,10 +236,9 @@ __device__ __forceinline__ void energy_row_body(const EnergyArgs& a, int block) 
 // Columns of column block `block` (of a.nx / a.cols; the blocks spread over the XCDs as the column
 // pass spreads its tiles).
 template <int N, class Q>
-__device__ __forceinline__ void energy_col_body(const EnergyArgs& a, int block) {
+__device__ __forceinline__ void energy_col_body(const EnergyArgs& a, int block, double* red) {
   constexpr int P = energy_points(N);
   constexpr int T = N / P;
-  __shared__ double red[64];
   const int C = a.cols;
   const int tid = threadIdx.x, comp = tid & 1, pair = tid >> 1;
   const int cc = pair & (C - 1), t = pair / C;
@@ -265,33 +266,38 @@ __device__ __forceinline__ void energy_col_body(const EnergyArgs& a, int block) 
 
 template <int N, class Q>
 __global__ void __launch_bounds__(512) energy_row_kernel(EnergyArgs a) {
-  energy_row_body<N, Q>(a, blockIdx.x);
+  __shared__ EnergyRed red;
+  energy_row_body<N, Q>(a, blockIdx.x, red);
 }
 
 template <int N, class Q>
 __global__ void __launch_bounds__(512) energy_col_kernel(EnergyArgs a) {
-  energy_col_body<N, Q>(a, blockIdx.x);
+  __shared__ EnergyRed red;
+  energy_col_body<N, Q>(a, blockIdx.x, red);
 }
 
 // Square grids: the row blocks and the column blocks are independent and of one shape, so one launch
 // holds both (the first `row_blocks` blocks are the rows').
 template <int N, class Q>
 __global__ void __launch_bounds__(512) energy_square_kernel(EnergyArgs a, int row_blocks) {
-  if (static_cast<int>(blockIdx.x) < row_blocks) energy_row_body<N, Q>(a, blockIdx.x);
-  else energy_col_body<N, Q>(a, blockIdx.x - row_blocks);
+  __shared__ EnergyRed red;
+  if (static_cast<int>(blockIdx.x) < row_blocks) energy_row_body<N, Q>(a, blockIdx.x, red);
+  else energy_col_body<N, Q>(a, blockIdx.x - row_blocks, red);
 }
 
 // Batched: grid y = the members of a batch class, each with its own arguments.
 template <int N, class Q>
 __global__ void __launch_bounds__(512) energy_row_kernel_batch(const EnergyArgs* __restrict__ tab) {
+  __shared__ EnergyRed red;
   const EnergyArgs a = tab[blockIdx.y];
-  energy_row_body<N, Q>(a, blockIdx.x);
+  energy_row_body<N, Q>(a, blockIdx.x, red);
 }
 
 template <int N, class Q>
 __global__ void __launch_bounds__(512) energy_col_kernel_batch(const EnergyArgs* __restrict__ tab) {
+  __shared__ EnergyRed red;
   const EnergyArgs a = tab[blockIdx.y];
-  energy_col_body<N, Q>(a, blockIdx.x);
+  energy_col_body<N, Q>(a, blockIdx.x, red);
 }
 
 // The grid's threads over the n points of psi in turn, eight loads of a thread in flight at a time (the
@@ -316,7 +322,7 @@ __device__ __forceinline__ void for_each_point(const Q* __restrict__ psi, long l
 template <class Q>
 __global__ void __launch_bounds__(256) norm_kernel(const Q* __restrict__ psi, long long n,
                                                    double* __restrict__ partials) {
-  __shared__ double red[64];
+  __shared__ double red[kRedDoubles];
   double acc = 0.0;
   for_each_point(psi, n, [&](const Q& w) {
     const double ur = w.x, ui = w.y, dr = w.z, di = w.w;
@@ -330,7 +336,7 @@ __global__ void __launch_bounds__(256) norm_kernel(const Q* __restrict__ psi, lo
 // order (thread-strided, then block_sum's fixed tree), then the energy per particle of the state
 // rescaled to norm0, E = (w / N ek + w er) / norm + w ei norm0 / norm^2 with norm = w nr.
 __device__ __forceinline__ void energy_finish_body(const EnergyArgs& a, double* out) {
-  __shared__ double red[64];
+  __shared__ double red[kRedDoubles];
   const int nrows = a.ny / a.rows, ncols = a.nx / a.cols;
   double er = 0.0, ei = 0.0, nr = 0.0, ek = 0.0;
 #pragma unroll 4
@@ -494,7 +500,7 @@ hipError_t launch_energy_batch(const EnergyArgs* tab, int count, int nx, int ny,
 template <class Q>
 __global__ void __launch_bounds__(256) nonfinite_kernel(const Q* __restrict__ psi, long long n,
                                                         double* __restrict__ partials) {
-  __shared__ double red[64];
+  __shared__ double red[kRedDoubles];
   double bad = 0.0;
   for_each_point(psi, n, [&](const Q& w) {
     bad += (isfinite(w.x) && isfinite(w.y) && isfinite(w.z) && isfinite(w.w)) ? 0.0 : 1.0;

@@ -406,7 +406,8 @@ __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
 // The general row pass of the splitting variants (one row group per workgroup); see RowVarFlags.
 template <int N, bool IMAG, bool FULL, int P>
 __device__ __forceinline__ void row_var_body(const RowArgs& a, int wg) {
-  __shared__ double red[64];
+  __shared__ double red[kRedDoubles];
+  static_assert(sizeof red <= kStaticLds);
   constexpr int T = N / P;
   const int tid = threadIdx.x;
   const int comp = tid & 1;

@@ -271,7 +271,7 @@ hipError_t launch_probe_cols_wl(const float4* src, float4* dst, int nx, int ny, 
                                 bool write_through, hipStream_t s);
 
 // Workgroup geometry helpers (shared with the host so that partial counts match).
-// max_lds: the device's LDS bytes per workgroup (minus the kernels' static LDS).
+// max_lds: the device's LDS bytes per workgroup minus kStaticLds.
 int row_rows_per_block(int nx, int ny, int points, size_t max_lds);
 int col_default_cols(int nx, int ny, int points, size_t max_lds);
 // a complex64 column tile that a schedule may ask for, and one of at most 512 threads
@@ -281,6 +281,10 @@ bool energy_fits(int nx, int ny, size_t max_lds);
 int energy_rows_per_block(int nx, int ny);
 int energy_cols_per_block(int nx, int ny, size_t max_lds);
 constexpr int kLdsSkew = 128;   // bytes, shared out among a workgroup's lines (lds_line)
+// Reduction scratch of a workgroup (doubles): block_sum's, and the energy row blocks' four sums.  kStaticLds
+// bounds the static LDS of every kernel whose dynamic LDS is checked against max_lds.
+constexpr int kRedDoubles = 64, kEnergyRedDoubles = 4 * kRedDoubles;
+constexpr size_t kStaticLds = kEnergyRedDoubles * sizeof(double);
 size_t energy_lds_bytes(int n, int lines);
 size_t row_lds_bytes(int nx, int rows);
 size_t col_lds_bytes(int ny, int cols);
