@@ -121,9 +121,15 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
       }
     }
   }
-  // (1024^2: 16.5 -> 16.2 us per step; rows of 2048 x 256: 13.6 -> 13.8 with it; wide column workgroups
-  // must stay within 128 VGPRs)
-  if constexpr (!WT || N == 1024 || (COL && !FULL && N >= 2048)) {
+  // Formed anew (see forget) the offsets free 28 to 30 VGPRs at 16 points per lane, of 140 to 182: up to one
+  // more wave per SIMD, and the wide column workgroups stay within 128 but for a few.  Held: at 4 and 8 points, where
+  // four waves and more are resident either way and a pass is one lane's chain of latencies (1024 x 256:
+  // 7.9 us per step, 8.3 formed anew; with a spatial coupling 9.1 and 9.4); in rows of 2048 and 4096
+  // points, whose grids of few rows are resident as a whole and whose workgroups of 4096 points are not
+  // joined by another (4096 x 256: 16.9 and 17.3; 2048 x 256 with a coupling: 12.7 and 12.9); and with a
+  // coupling in lines below 1024 points (2048 x 128 at 16 points: 11.9 and 12.7).  Elsewhere, held -> formed
+  // anew: 1024^2 16.4 -> 16.1, 512 x 2048 20.0 -> 19.8, 64 x 4096 with a coupling 19.6 -> 18.5.
+  if constexpr (!WT || (P == 16 && (COL || N <= 1024) && (!FULL || N >= 1024))) {
     forget(off0);
     forget(offb);
   }

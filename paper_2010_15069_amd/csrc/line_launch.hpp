@@ -22,8 +22,8 @@
 namespace sgpe {
 
 // threads of a workgroup: column tiles may be wide (wide_cols, api.cpp) where the pass holds its registers
-// at four waves per SIMD, which it does with the diagonal real-space exponential; with a spatial coupling
-// a wide tile is taken in halves (line_cols, api.cpp)
+// at four waves per SIMD, which it does with the diagonal real-space exponential (but for 2 to 4 values
+// that spill); with a spatial coupling a wide tile is taken in halves (line_cols, api.cpp)
 constexpr int line_threads(int n, bool col, bool full) { return col && !full && n >= 2048 ? 1024 : 512; }
 
 template <int N, bool COL, bool FULL, bool NLN, int P>
