@@ -56,14 +56,14 @@ int col_default_cols(int nx, int ny, int points, size_t max_lds) {
   return c;
 }
 
-// Energy kernels (fp64, register-resident transforms): 8 points per lane (half the registers of 16, twice
-// the waves: 2048^2 took 91 us per call instead of 111), but 16 for 1024 points, where two lines then fit
-// 256 threads and a column block reads 32-byte row segments (32 us per call, 41 with 8), and for 4096,
-// whose line would take 1024 threads; T = N / points lanes per component of a line, two components per
-// lane pair.  Lines per workgroup: up to 128 / T (a workgroup of at most 256 threads, 512 at 2048 and 4096
-// points), but no more than keeps ~256 workgroups on the grid (small grids are latency-bound: more
+// Energy kernels (fp64, register-resident transforms): T = N / points lanes per component of a line, two
+// components per lane pair.  16 points per lane from 1024 points on, where a line still fills two waves
+// and, at 1024, two lines fit 256 threads and a column block reads 32-byte row segments (us per call with
+// 16 and 8: 1024^2 27 and 35, 2048^2 74 and 77, 2048 x 512 35.6 and 36.4); 8 below, for more and shorter
+// waves (512^2 19.5 and 18.3).  Lines per workgroup: up to 128 / T (a workgroup of at most 256 threads, 512
+// at 4096 points), but no more than keeps ~256 workgroups on the grid (small grids are latency-bound: more
 // workgroups, each shorter).
-__host__ __device__ constexpr int energy_points(int n) { return n == 1024 || n > 2048 ? 16 : 8; }
+__host__ __device__ constexpr int energy_points(int n) { return n >= 1024 ? 16 : 8; }
 
 size_t energy_lds_bytes(int n, int lines) { return 2 * row_lds_bytes(n, lines); }
 
@@ -173,9 +173,9 @@ __device__ __forceinline__ void energy_row_body(const EnergyArgs& a, int block, 
   const size_t row0 = size_t(row) * N;
   // The real-space terms and the norm: P/2 points per thread with both components in one load, four
   // loads in flight.  At 8 points per lane the transform's loads, which find the row in the L2, go out
-  // with them (16 points: 250 VGPRs).  The roots wait until the sums have given their registers back
-  // (2048 points: 109 VGPRs instead of 130, which would leave one workgroup per CU).  With the four sums
-  // in one round of barriers, per energy call: 2048^2 91.5 -> 87.3 us, 512^2 20.6 -> 19.6, 64^2 17.5 -> 16.9.
+  // with them (16 points would hold 250 VGPRs instead of 166).  The roots wait until the sums have given
+  // their registers back.  With the four sums in one round of barriers, per energy call: 512^2 20.6 ->
+  // 19.6 us, 64^2 17.5 -> 16.9.
   const double y = a.ymin + a.dy * row;
   const double om_row = a.om_y ? a.om_y[row] : 0.0;
   double er = 0.0, ei = 0.0, nr = 0.0;
