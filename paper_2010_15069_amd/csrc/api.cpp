@@ -473,7 +473,7 @@ static sgpe_status run_steps_c128(sgpe_ctx* c, int64_t n) {
   if (cont) {
     e = sgpe::launch_col(col_args_t<double>(c, false), sgpe::NORM_DOT, c->col_points, s);
   } else {
-    e = sgpe::launch_row(ra, sgpe::ROW_FWD, false, false, c->row_points, s);
+    e = sgpe::launch_row(ra, sgpe::ROW_FWD, false, c->row_points, s);
     if (e == hipSuccess) e = sgpe::launch_col(col_args_t<double>(c, true), sgpe::NORM_NONE, c->col_points, s);
   }
   const bool defer = c->own_psi;
@@ -484,7 +484,7 @@ static sgpe_status run_steps_c128(sgpe_ctx* c, int64_t n) {
       r.partials = c->partials;
       r.n_partials = col_groups(c);
     }
-    e = sgpe::launch_row(r, sgpe::ROW_STEP, true, c->full2x2, c->row_points, s);
+    e = sgpe::launch_row(r, sgpe::ROW_STEP, c->full2x2, c->row_points, s);
     const bool last = (i == n);
     if (last && defer) break;   // the last K(dt/2) and the inverse x-transform wait (flush_tail)
     if (e == hipSuccess)
@@ -499,7 +499,7 @@ static sgpe_status run_steps_c128(sgpe_ctx* c, int64_t n) {
     r.scale = 1.0 / npts;
     r.partials = c->partials;
     r.n_partials = col_groups(c);
-    e = sgpe::launch_row(r, sgpe::ROW_INV, false, false, c->row_points, s);
+    e = sgpe::launch_row(r, sgpe::ROW_INV, false, c->row_points, s);
   }
   return status_of(e);
 }
@@ -541,7 +541,7 @@ sgpe_status run_steps(sgpe_ctx* c, int64_t n, bool imag, std::vector<hipEvent_t>
   if (cont) {
     e = sgpe::launch_col(col_args(c, false), sgpe::NORM_DOT, c->col_iters, c->col_points, s);
   } else {
-    e = sgpe::launch_row(ra, sgpe::ROW_FWD, false, false, c->row_iters, c->row_points, s);
+    e = sgpe::launch_row(ra, sgpe::ROW_FWD, false, c->row_iters, c->row_points, s);
     if (e == hipSuccess)
       e = sgpe::launch_col(col_args(c, true), sgpe::NORM_NONE, c->col_iters, c->col_points, s);
   }
@@ -557,7 +557,7 @@ sgpe_status run_steps(sgpe_ctx* c, int64_t n, bool imag, std::vector<hipEvent_t>
       r.n_partials = col_groups(c);
     }
     if (ev) (void)hipEventRecord((*ev)[evi++], s);
-    e = sgpe::launch_row(r, step_mode, true, c->full2x2, c->row_iters, c->row_points, s);
+    e = sgpe::launch_row(r, step_mode, c->full2x2, c->row_iters, c->row_points, s);
     if (e != hipSuccess) return status_of(e);
     if (ev) (void)hipEventRecord((*ev)[evi++], s);
     const bool last = (i == n);
@@ -574,7 +574,7 @@ sgpe_status run_steps(sgpe_ctx* c, int64_t n, bool imag, std::vector<hipEvent_t>
   r.scale = inv_n;
   r.partials = c->partials;
   r.n_partials = col_groups(c);
-  e = sgpe::launch_row(r, sgpe::ROW_INV, false, false, c->row_iters, c->row_points, s);
+  e = sgpe::launch_row(r, sgpe::ROW_INV, false, c->row_iters, c->row_points, s);
   return status_of(e);
 }
 
@@ -597,7 +597,7 @@ sgpe_status flush_tail(sgpe_ctx* c) {
     r.scale = 1.0 / (double(c->p.nx) * double(c->p.ny));
     r.partials = c->partials;
     r.n_partials = col_groups(c);
-    return status_of(sgpe::launch_row(r, sgpe::ROW_INV, false, false, c->row_points, c->stream));
+    return status_of(sgpe::launch_row(r, sgpe::ROW_INV, false, c->row_points, c->stream));
   }
   hipError_t e = sgpe::launch_col(col_args(c, true), sgpe::NORM_SQ, c->col_iters, c->col_points, c->stream);
   if (e != hipSuccess) return status_of(e);
@@ -605,7 +605,7 @@ sgpe_status flush_tail(sgpe_ctx* c) {
   r.scale = float(1.0 / (double(c->p.nx) * double(c->p.ny)));
   r.partials = c->partials;
   r.n_partials = col_groups(c);
-  e = sgpe::launch_row(r, sgpe::ROW_INV, false, false, c->row_iters, c->row_points, c->stream);
+  e = sgpe::launch_row(r, sgpe::ROW_INV, false, c->row_iters, c->row_points, c->stream);
   return status_of(e);
 }
 
@@ -656,7 +656,7 @@ static sgpe_status run_steps_variant(sgpe_ctx* c, int64_t n, bool imag) {
       r.inv_npts = 1.0;
     }
     r.partials_out = c->partials;
-    if (e == hipSuccess) e = sgpe::launch_row(r, sgpe::ROW_VAR, true, c->full2x2, 1, c->row_points, s);
+    if (e == hipSuccess) e = sgpe::launch_row(r, sgpe::ROW_VAR, c->full2x2, 1, c->row_points, s);
   };
   row(sgpe::VAR_FWD, 1, nullptr, 0);
   for (int64_t i = 1; i <= n; ++i) {
@@ -1307,7 +1307,7 @@ sgpe_status sgpe_profile_kernels(sgpe_ctx* c, int32_t imag, int64_t n, double* r
   if (e == hipSuccess) e = hipMemcpyAsync(c->scratch, c->psi, bytes, hipMemcpyDeviceToDevice, s);
   RowArgs r = row_args(c);
   if (imag) {
-    if (e == hipSuccess) e = sgpe::launch_row(r, sgpe::ROW_FWD, false, false, c->row_iters, c->row_points, s);
+    if (e == hipSuccess) e = sgpe::launch_row(r, sgpe::ROW_FWD, false, c->row_iters, c->row_points, s);
     if (e == hipSuccess) e = sgpe::launch_col(col_args(c, true), sgpe::NORM_DOT, c->col_iters, c->col_points, s);
     r.scale = float(1.0 / (double(p.nx) * double(p.ny)));
     r.partials = c->partials;
@@ -1316,7 +1316,7 @@ sgpe_status sgpe_profile_kernels(sgpe_ctx* c, int32_t imag, int64_t n, double* r
   const ColArgs ca = col_args(c, false);
   if (e == hipSuccess) e = hipEventRecord(ev[0], s);
   for (int64_t i = 0; i < n && e == hipSuccess; ++i)
-    e = imag ? sgpe::launch_row(r, sgpe::ROW_STEP, true, c->full2x2, c->row_iters, c->row_points, s)
+    e = imag ? sgpe::launch_row(r, sgpe::ROW_STEP, c->full2x2, c->row_iters, c->row_points, s)
              : line_pass(c, false, LINE_FULL, LINE_FULL, 1);
   if (e == hipSuccess) e = hipEventRecord(ev[1], s);
   if (e == hipSuccess) e = hipEventRecord(ev[2], s);

@@ -176,15 +176,15 @@ hipError_t enqueue_class_imag(const sgpe_batch* b, const BatchClass& k, int64_t 
   const RowArgs* t_sc = k.row_tab + ROWTAB_SCALE * cnt;
   const RowArgs* t_pa = renormalise ? k.row_tab + ROWTAB_PARTIALS * cnt : t_sc;
   auto ctab = [&](bool half) { return k.col_tab + int(half ? COLTAB_HALF : COLTAB_FULL) * cnt; };
-  hipError_t e = sgpe::launch_row_batch(shape_r, t_fwd, cnt, sgpe::ROW_FWD, false, false, rp, s);
+  hipError_t e = sgpe::launch_row_batch(shape_r, t_fwd, cnt, sgpe::ROW_FWD, false, rp, s);
   if (e == hipSuccess) e = sgpe::launch_col_batch(shape_c, ctab(true), cnt, sgpe::NORM_NONE, cp, s);
   for (int64_t i = 1; i <= n && e == hipSuccess; ++i) {
-    e = sgpe::launch_row_batch(shape_r, i > 1 ? t_pa : t_sc, cnt, sgpe::ROW_STEP, true, k.full2x2, rp, s);
+    e = sgpe::launch_row_batch(shape_r, i > 1 ? t_pa : t_sc, cnt, sgpe::ROW_STEP, k.full2x2, rp, s);
     const bool last = (i == n);
     if (e == hipSuccess)
       e = sgpe::launch_col_batch(shape_c, ctab(last), cnt, last ? sgpe::NORM_SQ : sgpe::NORM_DOT, cp, s);
   }
-  if (e == hipSuccess) e = sgpe::launch_row_batch(shape_r, t_pa, cnt, sgpe::ROW_INV, false, false, rp, s);
+  if (e == hipSuccess) e = sgpe::launch_row_batch(shape_r, t_pa, cnt, sgpe::ROW_INV, false, rp, s);
   return e;
 }
 
@@ -200,7 +200,7 @@ hipError_t enqueue_persistent(sgpe_batch* b, int64_t n, bool imag, hipStream_t s
     const sgpe_ctx* c0 = b->inst[k.members[0]];
     if (imag) {
       if (e == hipSuccess)
-        e = sgpe::launch_row_batch(row_args(c0), k.row_tab + ROWTAB_FWD * cnt, cnt, sgpe::ROW_FWD, false, false, 8, s);
+        e = sgpe::launch_row_batch(row_args(c0), k.row_tab + ROWTAB_FWD * cnt, cnt, sgpe::ROW_FWD, false, 8, s);
       if (e == hipSuccess)
         e = sgpe::launch_col_batch(col_args(c0, false), k.col_tab + COLTAB_HALF * cnt, cnt, sgpe::NORM_NONE, 8, s);
     } else {
@@ -233,10 +233,10 @@ hipError_t enqueue_persistent(sgpe_batch* b, int64_t n, bool imag, hipStream_t s
       const RowArgs* t_sc = k.row_tab + ROWTAB_SCALE * cnt;
       const RowArgs* t_pa = k.row_tab + ROWTAB_PARTIALS * cnt;
       if (e == hipSuccess)
-        e = sgpe::launch_row_batch(shape_r, n > 1 ? t_pa : t_sc, cnt, sgpe::ROW_STEP, true, false, 8, s);
+        e = sgpe::launch_row_batch(shape_r, n > 1 ? t_pa : t_sc, cnt, sgpe::ROW_STEP, false, 8, s);
       if (e == hipSuccess)
         e = sgpe::launch_col_batch(col_args(c0, false), k.col_tab + COLTAB_HALF * cnt, cnt, sgpe::NORM_SQ, 8, s);
-      if (e == hipSuccess) e = sgpe::launch_row_batch(shape_r, t_pa, cnt, sgpe::ROW_INV, false, false, 8, s);
+      if (e == hipSuccess) e = sgpe::launch_row_batch(shape_r, t_pa, cnt, sgpe::ROW_INV, false, 8, s);
     } else {
       if (e == hipSuccess && n > 1) e = class_line(b, k, LINETAB_LAST, n % 2 != 0, s);
       if (e == hipSuccess) e = class_line(b, k, LINETAB_HALF, n % 2 == 0, s);

@@ -82,7 +82,7 @@ __device__ __forceinline__ void persist_class(const PersistArgs& a, const Persis
       const RowArgs* rows = s == 0 ? a.row_first : a.row_step;
       for (int i = first; i < k.n_row; i += k.wg_count) {
         const int4 it = a.row_items[k.row_begin + i];
-        row_body<N, ROW_STEP, true, false, 1, 8, true>(rows[it.x], it.y);
+        row_body<N, ROW_STEP, false, 1, 8, true>(rows[it.x], it.y);
         __syncthreads();
       }
       if (!persist_barrier(a, ++nb)) return;

@@ -319,7 +319,7 @@ __device__ __forceinline__ void row_apply_r(C (&v)[P], const A& a, int row, int 
 // The kernels' dynamic LDS, typed per precision where it is used.
 extern __shared__ __align__(16) unsigned char row_lds[];
 
-template <int N, int MODE, bool IMAG, bool FULL, int ITERS, int P, bool WT, class R>
+template <int N, int MODE, bool FULL, int ITERS, int P, bool WT, class R>
 __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
   using C = cplx_t<R>;
   constexpr int T = N / P;
@@ -387,7 +387,7 @@ __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
 #pragma unroll
       for (int m = 0; m < P; ++m) v[m] = vscale(v[m], s);
       if constexpr (STEP) {
-        row_apply_r<N, IMAG, FULL, MODE == ROW_STEP_NLN>(v, a, row0 + it * a.rows_per_block, t, comp == 0, hbx_r,
+        row_apply_r<N, true, FULL, MODE == ROW_STEP_NLN>(v, a, row0 + it * a.rows_per_block, t, comp == 0, hbx_r,
                                                          FULL ? hby_r[it] : R(0));
         fwd_pass<N>(v, lds, t, tr);
       }
@@ -404,7 +404,7 @@ __device__ __forceinline__ void row_body(const RowArgsT<R>& a, int wg) {
 }
 
 // The general row pass of the splitting variants (one row group per workgroup); see RowVarFlags.
-template <int N, bool IMAG, bool FULL, int P>
+template <int N, bool FULL, int P>
 __device__ __forceinline__ void row_var_body(const RowArgs& a, int wg) {
   __shared__ double red[kRedDoubles];
   static_assert(sizeof red <= kStaticLds);
@@ -440,15 +440,15 @@ __device__ __forceinline__ void row_var_body(const RowArgs& a, int wg) {
   const bool mid = (flags & VAR_MID_SCALE) != 0;
   const float norm_scale = row_scale(a, pv);
   check_scale(a, norm_scale, wg);
-  if (flags & (VAR_INV | VAR_SCALE)) {
-    if (flags & VAR_INV) inv_pass<N>(v, lds, t, tr);
+  if (flags & VAR_INV) {
+    inv_pass<N>(v, lds, t, tr);
     const float s = mid ? a.scale : norm_scale;
 #pragma unroll
     for (int m = 0; m < P; ++m) v[m] = vscale(v[m], s);
   }
   for (int r = 0; r < a.var_r; ++r) {
-    if (a.var_nln) row_apply_r<N, IMAG, FULL, true>(v, a, row, t, comp == 0, hbx_r, hb_row);
-    else row_apply_r<N, IMAG, FULL, false>(v, a, row, t, comp == 0, hbx_r, hb_row);
+    if (a.var_nln) row_apply_r<N, true, FULL, true>(v, a, row, t, comp == 0, hbx_r, hb_row);
+    else row_apply_r<N, true, FULL, false>(v, a, row, t, comp == 0, hbx_r, hb_row);
     if (mid && r == 0) {
 #pragma unroll
       for (int m = 0; m < P; ++m) v[m] = vscale(v[m], norm_scale);

@@ -25,11 +25,10 @@ enum RowMode : int {
 };
 
 // Stages of the general row pass (ROW_VAR), run in this order when their flag is set: inverse
-// x-FFT and scale, or only the scale; var_r real-space sub-steps R(h) in turn (each in closed form
+// x-FFT and scale; var_r real-space sub-steps R(h) in turn (each in closed form
 // with frozen densities, or as N(h/2) L(h) N(h/2) when var_nln); the norm partial; forward x-FFT.
 enum RowVarFlags : int {
   VAR_INV = 1,        // inverse x-FFT, then the scale (`scale`, or from the partials)
-  VAR_SCALE = 2,      // scale only, from the partials (the state is in real space on entry)
   VAR_NORM_OUT = 4,   // one fp64 partial of sum |psi|^2 per workgroup into partials_out
   VAR_FWD = 8,        // forward x-FFT
   VAR_MID_SCALE = 16, // the scale after the inverse x-FFT is `scale`; the scale from the partials
@@ -160,17 +159,17 @@ inline bool col_launch_supported(int n, int groups, int iters, int points) {
   return schedule_supported(n, groups, iters, points);
 }
 
-hipError_t launch_row(const RowArgs& a, int mode, bool imag, bool full2x2, int iters, int points, hipStream_t s);
+hipError_t launch_row(const RowArgs& a, int mode, bool full2x2, int iters, int points, hipStream_t s);
 hipError_t launch_col(const ColArgs& a, int norm_mode, int iters, int points, hipStream_t s);
 // complex128: 16 or 8 points per lane (8 for lengths up to kMaxNSmallP), one row group / column
 // tile per workgroup, the step modes only
-hipError_t launch_row(const RowArgsT<double>& a, int mode, bool imag, bool full2x2, int points, hipStream_t s);
+hipError_t launch_row(const RowArgsT<double>& a, int mode, bool full2x2, int points, hipStream_t s);
 hipError_t launch_col(const ColArgsT<double>& a, int norm_mode, int points, hipStream_t s);
 // Batches of instances of one grid shape: `shape` gives the geometry (every table entry must
 // share nx, ny, rows_per_block / cols); instance i's arguments are tab[i] (device memory), and
 // the launch holds (ny / rows or nx / cols) x count workgroups, and batch_item places all of an
 // instance's workgroups on one XCD.  One row group / column tile per workgroup.
-hipError_t launch_row_batch(const RowArgs& shape, const RowArgs* tab, int count, int mode, bool imag, bool full2x2,
+hipError_t launch_row_batch(const RowArgs& shape, const RowArgs* tab, int count, int mode, bool full2x2,
                             int points, hipStream_t s);
 hipError_t launch_col_batch(const ColArgs& shape, const ColArgs* tab, int count, int norm_mode, int points,
                             hipStream_t s);

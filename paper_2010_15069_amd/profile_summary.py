@@ -78,7 +78,7 @@ def traffic_record(kf: str, kw: str, cf: str, cw: str) -> dict:
     write_scale = copy_bytes / (copy_write * 1024)
     kfm, kwm = counter_medians(kf), counter_medians(kw)
     alg = BYTES_PER_POINT_PASS * 1024 * 1024
-    want = {"row_pass": "row_kernel<1024, 2, true, false, 1, 16>", "col_pass": "col_kernel<1024, 1, 1, 16>",
+    want = {"row_pass": "row_kernel<1024, 2, false, 1, 16>", "col_pass": "col_kernel<1024, 1, 1, 16>",
             "row_pass_real": "line_kernel<1024, false, false, false, 16>",
             "col_pass_real": "line_kernel<1024, true, false, false, 16>"}
     rec = {"workload": "metric_1024", "kernel_hash": kernel_hash(),
