@@ -55,12 +55,24 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
   C v[P];
 #pragma unroll
   for (int m = 0; m < P; ++m) v[m] = *reinterpret_cast<const C*>(base + (m == 0 ? off0 : offb + mstride * m));
+  // In complex128 at 16 points per lane the state takes 64 VGPRs, the roots up to 64, the couplings 32 and
+  // the library's sincos the rest: 4096-point lines, whose 512 threads have 256, spilled 105 to 181 of
+  // them, and 2048-point columns (256 threads) were left with one wave per SIMD.  There the roots are
+  // loaded for each op and the couplings for each R, neither is held across the other, and the op's
+  // table values go four points at a time: 21 to 49 spilled, two waves in the columns.  Real time, us
+  // per step: 1024 x 4096 with a coupling 251 -> 196 (two sweeps per step took 261), 4096 x 256 48 -> 38,
+  // 4096^2 1490 -> 925, 1024 x 2048 69 -> 60.  Rows of 2048 points stay at one wave either way and lost
+  // 3-5 %.
+  constexpr bool LEAN = sizeof(R) == 8 && P == 16 && N >= (COL ? 2048 : 4096);
   TwPlain<N, P, R> tr;
-  load_twiddles<N>(tr, t, a.tw);
+  if constexpr (!LEAN) load_twiddles<N>(tr, t, a.tw);
   R hb_line[P], hb_cross = R(0);
-  if constexpr (FULL) {
+  auto load_hb = [&](const LanePos<T>& pos) {
 #pragma unroll
-    for (int m = 0; m < P; ++m) hb_line[m] = a.hbx[rp.at(m)] * a.hfrac;
+    for (int m = 0; m < P; ++m) hb_line[m] = a.hbx[pos.at(m)] * a.hfrac;
+  };
+  if constexpr (FULL) {
+    if constexpr (!LEAN) load_hb(rp);
     hb_cross = a.hby[line] * a.hfrac;
   }
   // An op's table values of the lane's points are loaded before the forward transform, so that their
@@ -73,6 +85,11 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
   for (int stage = 0; stage < 2; ++stage) {
     const void* const op = stage == 0 ? a.op_pre : a.op_post;
     if (op != nullptr) {
+      if constexpr (LEAN) {
+        int tt = t;
+        asm volatile("" : "+v"(tt));
+        load_twiddles<N>(tr, tt, a.tw);
+      }
       if constexpr (COL) {
         const C* __restrict__ tab = static_cast<const C*>(op);   // (P(k_y) - 1) / N
         constexpr bool EARLY = P < 16;
@@ -84,6 +101,7 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
         fwd_pass<N>(v, lds, t, tr);
 #pragma unroll
         for (int m = 0; m < P; ++m) {
+          if (LEAN && m % 4 == 0) __builtin_amdgcn_sched_barrier(0);
           C e;
           if constexpr (EARLY) e = q[m];
           else e = tab[sp.at(m)];
@@ -102,6 +120,7 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
         fwd_pass<N>(v, lds, t, tr);
 #pragma unroll
         for (int m = 0; m < P; ++m) {
+          if (LEAN && m % 4 == 0) __builtin_amdgcn_sched_barrier(0);
           Q e;
           if constexpr (EARLY) e = d[m];
           else e = tab[2 * sp.at(m) + comp];
@@ -117,7 +136,12 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
     if (stage == 0) {
 #pragma unroll 1
       for (int r = 0; r < a.n_r; ++r) {
-        row_apply_r<N, false, FULL, NLN>(v, a, line, t, comp == 0, hb_line, hb_cross);
+        if constexpr (FULL && LEAN) {
+          int tt = t;
+          asm volatile("" : "+v"(tt));
+          load_hb(real_pos<N, P>(tt));
+        }
+        row_apply_r<N, false, FULL, NLN, NLN || LEAN>(v, a, line, t, comp == 0, hb_line, hb_cross);
       }
     }
   }

@@ -236,7 +236,7 @@ __device__ __forceinline__ bool small_angles(const C (&v)[P], const A& a, const 
 // point and factor.  Imaginary time votes once for all points, so that the small forms are one straight
 // line without branches, whose points fill each other's dependency chains (full 2x2 row pass at 2048^2:
 // with the polynomial exp, 68 -> 52 us; one vote in real time was 2-4 % slower than sixteen).
-template <int N, bool IMAG, bool FULL, bool NLN, int P, class C, class R, class A>
+template <int N, bool IMAG, bool FULL, bool NLN, bool ANEW = IMAG || NLN, int P, class C, class R, class A>
 __device__ __forceinline__ void row_apply_r(C (&v)[P], const A& a, int row, int t, bool up,
                                             const R (&hbx_r)[P], R hb_row) {
   const LanePos<N / P> pos = real_pos<N, P>(t);
@@ -245,10 +245,10 @@ __device__ __forceinline__ void row_apply_r(C (&v)[P], const A& a, int row, int 
   const R hvy = a.hvy * y * y;
   auto apply = [&](auto small) {
     constexpr bool SMALL = decltype(small)::value;
-    // Opaque to the compiler: the terms that depend on the position alone would else be formed once
-    // for both forms (and once for all sub-steps of a pass) and held, a register each per point.
+    // ANEW: opaque to the compiler.  The terms that depend on the position alone would else be formed
+    // once for both forms (and once for all sub-steps of a pass) and held, a register each per point.
     R hv0 = hvy, j0 = static_cast<R>(pos.p0), jb = static_cast<R>(pos.b), hb0 = hb_row;
-    if constexpr (IMAG || NLN) asm volatile("; %4" : "+v"(hv0), "+v"(j0), "+v"(jb), "+v"(hb0) : "i"(int(SMALL)));
+    if constexpr (ANEW) asm volatile("; %4" : "+v"(hv0), "+v"(j0), "+v"(jb), "+v"(hb0) : "i"(int(SMALL)));
     auto diag = [&](C w, R ph) {
       if constexpr (!IMAG) {
         if (wave_all(fabs_(ph) <= angle_limit<IMAG, R>())) return apply_r_diag<IMAG, true>(w, ph);
