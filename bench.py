@@ -410,7 +410,8 @@ def complex128_rates(torch, stream, timed, p, p_imag, psi0, steps=300, warmup=20
         res[f"split_steps_per_s_{kind}"] = steps / (total_ms * 1e-3)
         s.close()
     res["hbm_roofline_frac_imag"] = 128 * p.nx * p.ny * res["split_steps_per_s_imag"] / (HBM_PEAK_GBS * 1e9)
-    res["note"] = "complex128 state: 32 B per point per sweep, 128 B per point per step"
+    res["note"] = ("complex128 state: 32 B per point each way; 128 B per point per step in imaginary time (two "
+                   "sweeps), 64 B in real time (one)")
     return res
 
 

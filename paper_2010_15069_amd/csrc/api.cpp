@@ -212,7 +212,7 @@ int default_points(int n, size_t npts, bool col) {
 // The default column tile from one of at most 512 threads: twice that where such a tile of 2048- or
 // 4096-point columns fills its workgroup with a row segment of only 32 or 16 bytes, the wider tile fits
 // the LDS, and one workgroup per compute unit is left.  The pass holds its registers at the four waves per
-// SIMD of 1024 threads (96 VGPRs), so the same waves are resident and the segments are twice as long
+// SIMD of 1024 threads (90 VGPRs), so the same waves are resident and the segments are twice as long
 // (per step, imaginary / real time: 2048^2 79.8 / 64.6 -> 73.1 / 56.8 us, 1024 x 4096 126 / 79 -> 94 / 70,
 // 512 x 4096 67.8 / 44.2 -> 54.7 / 40.1).
 int wide_cols(const sgpe_ctx* c, int cols, int points) {

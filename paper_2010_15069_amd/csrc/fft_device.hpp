@@ -90,7 +90,7 @@ __device__ __forceinline__ void store_state(C* p, C v) {
 // Makes the compiler form anew what it would derive from x, instead of holding what it derived earlier
 // across the transforms: the offsets of a pass's loads, wanted again by its stores, take a register per
 // point.  Worth it where the registers decide how many waves are resident (row pass at 16 points per
-// lane: 142 -> 122 VGPRs, 168 -> 138 with a spatial Raman coupling; column pass 126 -> 96): batches,
+// lane: 142 -> 123 VGPRs, 168 -> 138 with a spatial Raman coupling; column pass 126 -> 90): batches,
 // complex128 and lines of 2048 points and more (24-instance sweep 15.0 -> 14.7 ms, complex128 at 1024^2
 // 42.4 -> 40.5 us per step, 2048^2 90.0 -> 88.5).  A single complex64 grid of shorter lines is resident
 // as a whole either way, and the offsets then only delay its stores (1024^2: 23.4 -> 23.8 us per step).
@@ -132,7 +132,7 @@ struct LanePos {
 // each kLdsSkew / lines bytes further than its slots: lanes that own neighbouring lines (column tiles)
 // would else meet in the same banks.  A lane's accesses of a stage are then one register and constants;
 // with the lines interleaved slot by slot, a stride only the launch knows, each took an address of its
-// own (the column pass at 1024 points: 213 VGPRs, now 147).  Skews of 0, 128 and 256 bytes: 28.8, 24.6 and
+// own (that change took the column pass at 1024 points from 213 to 147 VGPRs).  Skews of 0, 128 and 256 bytes: 28.8, 24.6 and
 // 25.7 us per step at 1024^2 (imaginary time, paired accesses).  Both changes: 24.3 -> 24.0 us per step
 // at 1024^2 in imaginary time and 17.7 -> 16.6 in real time, 7.8 -> 7.4 at 64^2, the 24-instance sweep
 // 17.0 -> 16.3 ms.
@@ -208,7 +208,7 @@ __device__ __forceinline__ LdsView<V> lds_line(unsigned char* lds, int line, int
 // rounded roots or smaller: 1.07e-7 and 1.33e-7 at N = 1024, P = 16, against 1.09e-7 and 1.35e-7.
 // Larger grids are bound by instruction issue at the two waves per SIMD that the registers allow; a
 // row pass at 1024 points went from 1945 to 1658 VALU instructions and from 192 to 142 VGPRs, the column
-// pass from 1990 to 1663 and from 242 to 213.  Per step, rounded roots -> shears: 26.8 -> 24.2 us at
+// pass from 1990 to 1663 instructions.  Per step, rounded roots -> shears: 26.8 -> 24.2 us at
 // 1024^2 and 135 -> 118 us at 2048^2 (imaginary time), 20.0 -> 17.5 us at 1024^2 (real time).
 // ---------------------------------------------------------------------------------------------
 // p and u of the fixed rotations by pi/8, pi/4 and 3 pi/8
@@ -711,8 +711,9 @@ __device__ __forceinline__ SinCosM1d sincos_m1_t(double phi) {
 }
 
 // exp(x) - 1 for |x| <= kSmallExp: x + x^2 p(x), with p of degree 4 in fp32 (Chebyshev; as a factor
-// w + w (exp(x) - 1) the result is within 7e-8 of w exp(x), rms 2.6e-8, where a correctly rounded
-// exp and a product reach 1.1e-7 and 3.6e-8) and Taylor's of degree 12 in fp64 (1e-16 / 14!).
+// w + w (exp(x) - 1) the result is within 9.3e-8 of w exp(x), rms 2.6e-8, where a correctly rounded
+// exp and a product reach 1.2e-7 and 3.6e-8) and Taylor's of degree 12 in fp64 (the first term left out
+// is 0.35^15 / 15! = 1.1e-19).
 constexpr float kSmallExp = 0.35f;
 __device__ __forceinline__ float expm1_small(float x) {
   float p = fmaf(x, 1.3934535e-3f, 8.3637694e-3f);

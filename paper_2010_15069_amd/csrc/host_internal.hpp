@@ -31,7 +31,7 @@ struct sgpe_ctx {
   double* omx = nullptr;    // Omega_x(x_j) (energy)
   double* omy = nullptr;    // Omega_y(y_i)
   double* partials = nullptr;
-  double* epart = nullptr;  // energy partials (row: 2 per block, then col: 1 per block)
+  double* epart = nullptr;  // energy partials (kEnergyRowParts per row block, then one per column block)
   size_t max_lds = 0;       // dynamic LDS bytes available per workgroup
   int rows = 1;             // rows per row-pass workgroup
   int cols = 1;             // columns per column-pass workgroup

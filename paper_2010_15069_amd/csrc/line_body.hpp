@@ -77,9 +77,9 @@ __device__ __forceinline__ void line_body(const LineArgsT<R>& a, int wg, int ngr
   }
   // An op's table values of the lane's points are loaded before the forward transform, so that their
   // latency hides behind it, at 8 or 4 points per lane (complex128 at 64^2: 7.3 us per step, against 7.6
-  // loaded where used); at 16 points the transform needs the registers (254 VGPRs without a spill at 1024
-  // points; with the values held, 53 spilled and a step took 26.1 us at 1024^2 instead of 19.3), and
-  // they are loaded where used.
+  // loaded where used); at 16 points they would take the registers of another wave (1024-point rows with
+  // a coupling: 205 VGPRs instead of 152) and are loaded where used (2048^2: 55 us per step, 61 held;
+  // 2048 x 1024 31.2 and 32.7; 1024^2 level).
   constexpr R inv_n = R(1) / R(N);
 #pragma unroll 1
   for (int stage = 0; stage < 2; ++stage) {

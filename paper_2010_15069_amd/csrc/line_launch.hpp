@@ -11,10 +11,10 @@
 // step are the same four.  (Imaginary time cannot do this: the norm of K(dt/2) R K(dt/2) psi is needed
 // before the next R, and it is not known from data along one axis.)
 //
-// Bound: two passes' worth of VALU work per launch (about 2600 wave instructions at 1024 points and 16
-// per lane) over one exchange of the state between the XCDs.  Measured per step, two sweeps -> one:
-// 12.0 -> 8.4 us at 512^2, 25.2 -> 19.3 us at 1024^2, 9.8 -> 7.2 us at 64^2 in complex128 (calls of 50 to
-// 200 steps on a caller's buffer).  Tiles and points per lane are the schedule's.
+// Bound: two passes' worth of VALU work per launch (about 2700 wave instructions at 1024 points and 16
+// per lane) over one exchange of the state between the XCDs.  Measured per step, two sweeps -> one: 12.0
+// -> 7.8 us at 512^2, 25.2 -> 16.2 us at 1024^2, 9.8 -> 6.5 us at 64^2 in complex128 (with the transforms
+// of fft_device.hpp; calls of 50 to 200 steps on a caller's buffer).  Tiles and points per lane are the schedule's.
 #pragma once
 
 #include "line_body.hpp"

@@ -26,7 +26,7 @@ __global__ void __launch_bounds__(256) add_noise_kernel(Q* __restrict__ psi, con
 template <class Q>
 __global__ void __launch_bounds__(256) moments_kernel(const Q* __restrict__ psi, long long n,
                                                       double* __restrict__ partials) {
-  __shared__ double red[64];
+  __shared__ double red[kRedDoubles];
   double sud = 0.0, suu = 0.0, sdd = 0.0;
   for (long long i = blockIdx.x * 256LL + threadIdx.x; i < n; i += 256LL * gridDim.x) {
     const Q w = psi[i];
@@ -51,7 +51,7 @@ template <class Q>
 __global__ void __launch_bounds__(256) disk_population_kernel(const Q* __restrict__ psi, int nx, long long n,
                                                               double x0, double dx, double y0, double dy,
                                                               double r2, double* __restrict__ partials) {
-  __shared__ double red[64];
+  __shared__ double red[kRedDoubles];
   double acc = 0.0;
   for (long long i = blockIdx.x * 256LL + threadIdx.x; i < n; i += 256LL * gridDim.x) {
     const long long row = i / nx;
@@ -90,7 +90,7 @@ __device__ __forceinline__ double phase_step(double ar, double ai, double br, do
 template <class Q>
 __global__ void __launch_bounds__(256) winding_kernel(const Q* __restrict__ psi, int nx, int ny, double xmax,
                                                       double ymax, double radius, int m, double* __restrict__ out) {
-  __shared__ double red[64];
+  __shared__ double red[kRedDoubles];
   double su = 0.0, sd = 0.0;
   for (int k = threadIdx.x; k < m; k += 256) {
     const Q a = psi[circle_point(k, m, radius, nx, ny, xmax, ymax)];

@@ -264,8 +264,8 @@ __device__ __forceinline__ void row_apply_r(C (&v)[P], const A& a, int row, int 
     for (int m = 0; m < P; ++m) {
       if constexpr (IMAG && !SMALL) {
         // a branch the compiler cannot fold keeps it from running the general form of all points
-        // side by side, which takes every register there is (240 VGPRs and up, where the small form
-        // takes 168)
+        // side by side, which takes every register there is (1024 points with a spatial coupling: 243
+        // VGPRs, where the small form takes 168)
         int go = 1;
         asm volatile("" : "+s"(go));
         if (go == 0) continue;

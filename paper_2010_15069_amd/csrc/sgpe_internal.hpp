@@ -1,4 +1,4 @@
-// Internal interface between the host library (api.cpp) and the HIP kernels (kernels.hip).
+// Internal interface between the host library (*.cpp) and the HIP kernels (*.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
