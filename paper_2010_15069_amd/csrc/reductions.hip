@@ -272,7 +272,7 @@ __global__ void __launch_bounds__(512) energy_row_kernel(EnergyArgs a) {
 
 template <int N, class Q>
 __global__ void __launch_bounds__(512) energy_col_kernel(EnergyArgs a) {
-  __shared__ EnergyRed red;
+  __shared__ double red[kRedDoubles];
   energy_col_body<N, Q>(a, blockIdx.x, red);
 }
 
@@ -295,7 +295,7 @@ __global__ void __launch_bounds__(512) energy_row_kernel_batch(const EnergyArgs*
 
 template <int N, class Q>
 __global__ void __launch_bounds__(512) energy_col_kernel_batch(const EnergyArgs* __restrict__ tab) {
-  __shared__ EnergyRed red;
+  __shared__ double red[kRedDoubles];
   const EnergyArgs a = tab[blockIdx.y];
   energy_col_body<N, Q>(a, blockIdx.x, red);
 }
