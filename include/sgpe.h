@@ -466,7 +466,7 @@ sgpe_status sgpe_batch_use_persistent(sgpe_batch* batch, int32_t on);
  * 1..16) and keep the fastest.  The instances' states
  * are saved before and restored after (so results do not depend on tuning); the captured graphs
  * are dropped.  best_ms, if not NULL, receives one value per class: the chosen schedule's mean time
- * per step of that class in milliseconds.  Synchronises. */
+ * per step of that class, over both kinds of step, in milliseconds.  Synchronises. */
 sgpe_status sgpe_batch_autotune(sgpe_batch* batch, int32_t steps, double* best_ms);
 
 #ifdef __cplusplus

@@ -178,7 +178,8 @@ class Solver:
 
     # -- measurement / tuning --------------------------------------------------------------
     def profile_steps(self, n, imag=False):
-        """Mean per-launch milliseconds of (row pass, column pass) over n steady-state steps."""
+        """Mean per-launch milliseconds of (row pass, column pass) over n steady-state steps; in real
+        time, where a step is one pass, of the steps along rows and along columns."""
         r, c = ctypes.c_double(), ctypes.c_double()
         check(self._lib.sgpe_profile_steps(self._ctx, 1 if imag else 0, int(n), ctypes.byref(r),
                                            ctypes.byref(c)), "sgpe_profile_steps")
@@ -344,7 +345,7 @@ class Batch:
 
     def autotune(self, steps=10):
         """Per class: the fastest schedule over the supported set (states kept); returns the
-        chosen per-class time per step in ms."""
+        chosen per-class mean time per step, over real- and imaginary-time steps, in ms."""
         ms = (ctypes.c_double * max(1, len(self.classes())))()
         check(self._lib.sgpe_batch_autotune(self._b, int(steps), ms), "sgpe_batch_autotune")
         return list(ms)
