@@ -461,9 +461,9 @@ sgpe_status sgpe_batch_set_schedule(sgpe_batch* batch, int32_t k, const sgpe_sch
  * schedules stay).  Synchronises. */
 sgpe_status sgpe_batch_use_persistent(sgpe_batch* batch, int32_t on);
 
-/* Autotuner: for every class, time `steps` real-time and `steps` imaginary-time steps (without
- * renormalisation) under each supported schedule (points per lane 4/8/16 in each pass, column tiles
- * 1..16) and keep the fastest.  The instances' states
+/* Autotuner: for every class, time `steps` steps, half of them in real and half in imaginary time
+ * (rounded up; without renormalisation), under each supported schedule (points per lane 4/8/16 in each
+ * pass, column tiles 1..16) and keep the fastest.  The instances' states
  * are saved before and restored after (so results do not depend on tuning); the captured graphs
  * are dropped.  best_ms, if not NULL, receives one value per class: the chosen schedule's mean time
  * per step of that class, over both kinds of step, in milliseconds.  Synchronises. */

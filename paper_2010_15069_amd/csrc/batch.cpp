@@ -793,6 +793,7 @@ sgpe_status sgpe_batch_autotune(sgpe_batch* b, int32_t steps, double* best_ms) {
     return hip_status(hipErrorOutOfMemory);
   }
   sgpe_status st = SGPE_OK;
+  const int64_t half = (int64_t(steps) + 1) / 2;   // of each kind
   for (size_t ci = 0; ci < b->cls.size() && st == SGPE_OK; ++ci) {
     BatchClass& k = b->cls[ci];
     const sgpe_ctx* c0 = b->inst[k.members[0]];
@@ -825,11 +826,11 @@ sgpe_status sgpe_batch_autotune(sgpe_batch* b, int32_t steps, double* best_ms) {
           }
           if (set_class_schedule(b, k, s) != SGPE_OK) continue;  // not valid for this shape
           // both kinds of step: their kernels differ, and a class has one schedule for both
-          hipError_t e = enqueue_class_real(b, k, 2, b->stream);
-          if (e == hipSuccess) e = enqueue_class_imag(b, k, 2, b->stream, false);
+          hipError_t e = enqueue_class_real(b, k, 1, b->stream);
+          if (e == hipSuccess) e = enqueue_class_imag(b, k, 1, b->stream, false);
           if (e == hipSuccess) e = hipEventRecord(t0, b->stream);
-          if (e == hipSuccess) e = enqueue_class_real(b, k, steps, b->stream);
-          if (e == hipSuccess) e = enqueue_class_imag(b, k, steps, b->stream, false);
+          if (e == hipSuccess) e = enqueue_class_real(b, k, half, b->stream);
+          if (e == hipSuccess) e = enqueue_class_imag(b, k, half, b->stream, false);
           if (e == hipSuccess) e = hipEventRecord(t1, b->stream);
           if (e == hipSuccess) e = hipEventSynchronize(t1);
           float ms = 0.0f;
@@ -844,7 +845,7 @@ sgpe_status sgpe_batch_autotune(sgpe_batch* b, int32_t steps, double* best_ms) {
           }
         }
     if (st == SGPE_OK) st = set_class_schedule(b, k, best_t < 0.0f ? start : best);
-    if (best_ms && best_t >= 0.0f) best_ms[ci] = double(best_t) / (2.0 * double(steps));
+    if (best_ms && best_t >= 0.0f) best_ms[ci] = double(best_t) / (2.0 * double(half));
     for (size_t j = 0; j < k.members.size(); ++j) {
       if (saved[j]) {
         if (st == SGPE_OK &&
